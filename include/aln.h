@@ -201,9 +201,11 @@ typedef struct {
                              pipeline, 4 rows), 8, 16, 24 or 32               */
   int32_t xdrop_rows;     /* 2, 4 or 8                                        */
   int32_t xdrop_sides;    /* 1, 4 (with xdrop_rows 8) or 16 (with xdrop_rows
-                             4: 16 sides of 4 lanes, 64 cells per side and
-                             antidiagonal; X-drop without CIGAR under
-                             match / mismatch scoring, else as 4x1)       */
+                             4: the lanes kernel, 64 cells per side and
+                             antidiagonal, 16 sides of 4 lanes, or 8 or 4
+                             sides where the batch is small; X-drop or
+                             Z-drop under match / mismatch scoring, else as
+                             4x1)                                         */
   int32_t sw16_wide_pct;  /* 0 (default 80), -1 (never) or 1..10000          */
   double sw16_ms[4];      /* candidates 16, 12, 8, 4 (each: best of the wide
                              thresholds 25, 40, 60, 80 it was timed with)    */

@@ -242,11 +242,24 @@ aln_status aln_set_scoring(aln_ctx *ctx, const aln_scoring *sc, int32_t *scoring
 
 } // extern "C"
 
-// Resident wavefronts per CU of the sixteen-sides X-drop kernel: the
-// device's occupancy, or three per SIMD (its register count) without one.
-static int lanes_waves_per_cu(const aln_ctx *ctx, bool tb) {
-  return ctx->device < 0 ? 12 : alnk::xdrop_lanes_waves_per_cu(tb);
+// Lanes a side for n X-drop sides of a 64-cell window.  Four lanes of sixteen
+// cells take the fewest instructions a cell (240 a step for sixteen sides, 150
+// for eight, 110 for four), but a step's instructions are also what the longest
+// side waits for, and a small batch is no longer than that.  So four only once
+// their wavefronts fill four slots a SIMD, sixteen while theirs take at most
+// four.  Measured, sides of 150..5 000 bp, X = 100, 16 / 8 / 4 lanes in ms:
+// 4 000 sides 4.7 / 5.6 / 8.0 (with codes 7.1 / 8.7 / 12.5), 12 000 6.2 / 6.3 /
+// 8.5 (9.0 / 10.0 / 15), 25 000 9.6 / 8.6 / 11.3 (12.4 / 12.3 / 16), 50 000
+// 15.8 / 12.5 / 13.6 (20.8 / 17.6 / 19.1), 100 000 29.0 / 20.2 / 18.4.
+static int lanes_per_side(const aln_ctx *ctx, int64_t n) {
+  const int64_t simds = 4LL * ctx->cus;
+  return n <= 16 * simds ? 16 : (n <= 64 * simds ? 8 : 4);
 }
+
+// Z-drop sides from which the lanes form (eight lanes, a window of 128 cells)
+// replaces one wavefront a side: 12 000 sides of 150..5 000 bp at Z = 100 take
+// 11.8 against 9.4 ms, 25 000 16.2 against 18.8, 100 000 43.7 against 73.1.
+static int64_t zdrop_lanes_from(const aln_ctx *ctx) { return 16LL * 4 * ctx->cus + 1; }
 
 // Interior cells (1 <= i <= M, 1 <= j <= N) of the static band: row i keeps
 // floor(iN/M) - w <= j <= floor(iN/M) + w.  Rows whose band is clipped by
@@ -703,12 +716,11 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     }
   }
   // X-drop without traceback under match / mismatch scoring on a small
-  // alphabet runs on the sixteen-sides-per-wavefront kernel when its
+  // alphabet runs on the lanes kernel (4 to 16 sides per wavefront) when its
   // arithmetic fits: offset-frame scores in one byte, the out-of-range
   // penalty (-128) below every threshold (X < 128 + 2|e|), end cells in 16
-  // bits and keys (score << 6) in 31.  Z-drop too, scores only, when tuned
-  // (its form masks removed and out-of-range cells itself, so Z has no
-  // bound).
+  // bits and keys (score << 6, or 7) in 31.  Z-drop too, scores only (its form
+  // masks removed and out-of-range cells itself, so Z has no bound).
   const bool zd = p.prune == ALN_ZDROP;
   const bool lanes_fit =
       (p.prune == ALN_XDROP || zd) && hs.match_mismatch && hs.alphabet <= 4 &&
@@ -739,16 +751,22 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     L.rows = items[k].rows;
     L.mode = p.mode;
     if (L.kind == K_DIAG && dyn_prune) {
-      // Z-drop takes the sixteen-sides form only when tuned: its regions
-      // often outgrow the 64-cell window (at Z = 100, e = -2 nearly every
-      // side, 345 ms against 300 on the one-side kernel)
-      L.sides = ctx->tuning.valid ? ctx->tuning.xdrop_sides : ((lanes_ok && !zd) ? 16 : 1);
+      // Z-drop takes the 64-cell window only when tuned: its regions often
+      // outgrow it (at Z = 100, e = -2 nearly every side, 345 ms against 300
+      // on the one-side kernel); by default large batches take the 128-cell
+      // window, which holds what the one-side kernel's first window holds
+      const bool zd_wide = zd && lanes_ok && !ctx->tuning.valid && !ctx->force_xdrop_sides &&
+                           (int64_t)(e - k) >= zdrop_lanes_from(ctx);
+      L.sides = ctx->tuning.valid ? ctx->tuning.xdrop_sides : ((lanes_ok && (!zd || zd_wide)) ? 16 : 1);
       if (ctx->force_xdrop_sides) L.sides = ctx->force_xdrop_sides;
       if (L.sides == 16 && !lanes_ok) L.sides = 1;
       if (L.sides == 4 && L.rows != 8) L.sides = 1;
       if (L.sides == 16) {
-        const int64_t want = ((int64_t)(e - k) + 15) / 16;
-        const int64_t fit = (int64_t)ctx->cus * lanes_waves_per_cu(ctx, false);
+        L.lps = zd ? (zd_wide ? 8 : 4) : lanes_per_side(ctx, (int64_t)(e - k));
+        L.window = zd_wide ? 128 : 64;
+        const int per = 64 / L.lps;
+        const int64_t want = ((int64_t)(e - k) + per - 1) / per;
+        const int64_t fit = (int64_t)ctx->cus * alnk::xdrop_lanes_waves(false, zd, L.lps);
         L.grid = (int)std::max<int64_t>(1, std::min(want, fit));
       }
     }
@@ -820,8 +838,10 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
                                 : (ctx->tuning.valid ? ctx->tuning.xdrop_sides : 16);
     pl->xtb_lanes = lanes_fit && !zd && tuned_sides == 16;
     if (pl->xtb_lanes) {
-      const int64_t want = ((int64_t)n + 15) / 16;
-      const int64_t fit = (int64_t)ctx->cus * lanes_waves_per_cu(ctx, true);
+      pl->xtb_lps = lanes_per_side(ctx, n);
+      const int per = 64 / pl->xtb_lps;
+      const int64_t want = ((int64_t)n + per - 1) / per;
+      const int64_t fit = (int64_t)ctx->cus * alnk::xdrop_lanes_waves(true, false, pl->xtb_lps);
       pl->xtb_grid = (int)std::max<int64_t>(1, std::min(want, fit));
     }
     std::vector<int32_t> order(n);
@@ -982,7 +1002,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   int32_t *widen_cnt = plan->xdrop ? reinterpret_cast<int32_t *>(ws + plan->widen_cnt_off) : nullptr;
   // counters: sw16 re-run queue; X-drop widening queues (2), the lanes
   // kernel's work queue (2) and its queue of pairs for the one-side pass with
-  // codes (1)
+  // codes, or Z-drop's third widening queue (1)
   alnk::ValidateArgs va{bp, plan->n, hsc.alphabet, d_res, sw16 ? rerun_cnt : widen_cnt,
                         sw16 ? 1 : (plan->xdrop ? 5 : 0)};
   HIP_TRY(ctx, timed_launch(ctx, "validate", st, [&] { return alnk::launch_validate(va, st); }));
@@ -1089,9 +1109,9 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     return da;
   };
   PairTask *wq0 = plan->xdrop ? reinterpret_cast<PairTask *>(ws + plan->widen_off[0]) : nullptr;
-  bool zd_lanes = false; // Z-drop on the sixteen-sides kernel
+  bool zd_lanes = false; // Z-drop on the 64-cell windows of the lanes kernel
   for (const LaunchDesc &L : plan->launches)
-    zd_lanes = zd_lanes || (L.kind == K_DIAG && L.sides == 16 && plan->p.prune == ALN_ZDROP);
+    zd_lanes = zd_lanes || (L.kind == K_DIAG && L.sides == 16 && L.window == 64 && plan->p.prune == ALN_ZDROP);
   PairTask *wq1 = plan->xdrop ? reinterpret_cast<PairTask *>(ws + plan->widen_off[1]) : nullptr;
   PairTask *wq2 = plan->xtb_lanes ? reinterpret_cast<PairTask *>(ws + plan->widen_off[2]) : nullptr;
   if (plan->xtb_lanes) {
@@ -1099,6 +1119,8 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     // window are recomputed with codes by the one-side pass (queue 2)
     alnk::XdlArgs xa;
     xa.zdrop = 0;
+    xa.lps = plan->xtb_lps;
+    xa.window = 64;
     xa.b = bp;
     xa.tasks = dtasks + plan->xtb_first;
     xa.ntasks = plan->xtb_count;
@@ -1133,7 +1155,8 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     // writes the traceback codes; regions that outgrow its window go to the
     // widening queue below (score only) and the walk decides their CIGAR
     auto xtb = [&](int32_t first, int32_t count) {
-      alnk::DiagArgs d = diag_args(dtasks + first, count, nullptr, 16, widen_cnt, wq0);
+      alnk::DiagArgs d = diag_args(dtasks + first, count, nullptr, plan->p.prune == ALN_ZDROP ? 8 : 16,
+                                   widen_cnt, wq0);
       return alnk::launch_diag(4, ALN_EXTEND, plan->p.prune, true, d, st);
     };
     const char *fam = plan->p.prune == ALN_ZDROP ? "zdrop_tb" : "xdrop_tb";
@@ -1146,11 +1169,13 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   for (const LaunchDesc &L : plan->launches) {
     if (L.kind == K_DIAG) {
       if (plan->xtb_count > 0) continue; // the traceback pass above replaces it
-      const int widen_rows = plan->xdrop ? (zd_lanes ? 4 : 16) : 0;
+      const int widen_rows = plan->xdrop ? (zd_lanes ? 4 : (plan->p.prune == ALN_ZDROP ? 8 : 16)) : 0;
       if (L.sides == 16) {
         alnk::XdlArgs xa;
         xa.tb = nullptr;
         xa.zdrop = plan->p.prune == ALN_ZDROP ? 1 : 0;
+        xa.lps = L.lps;
+        xa.window = L.window;
         xa.b = bp;
         xa.tasks = dtasks + L.first;
         xa.ntasks = L.count;
@@ -1237,20 +1262,30 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     }
   }
   if (plan->xdrop) {
-    // pairs whose surviving region outgrew their window: 1024 diagonals, then
-    // 2048.  Z-drop from the sixteen-sides kernel (64 cells) first tries the
-    // one-side kernel's 256 diagonals: Z-drop regions often reach about 100
-    // cells, and that window holds them at a quarter of the wider one's cost.
+    // Pairs whose surviving region outgrew their window, in wider ones.  A
+    // handful of long sides sets each pass's time, one wavefront each: Z-drop
+    // regions seldom pass 512 diagonals, where an antidiagonal takes two
+    // thirds of the 1024-diagonal kernel's (25 000 sides at Z = 100: 6.4
+    // against 9.5 ms), so that comes first; from the 64-cell lanes form even
+    // 256 diagonals hold most.
     const int pr = plan->p.prune;
     const char *fam = pr == ALN_ZDROP ? "zdrop_wide" : "xdrop_wide";
-    alnk::DiagArgs d1 = diag_args(wq0, plan->n, widen_cnt, 32, widen_cnt + 1, wq1);
-    HIP_TRY(ctx, timed_launch(ctx, fam, st, [&] {
-              return alnk::launch_diag(zd_lanes ? 4 : 16, ALN_EXTEND, pr, false, d1, st);
-            }));
-    alnk::DiagArgs d2 = diag_args(wq1, plan->n, widen_cnt + 1, 0, nullptr, nullptr);
-    HIP_TRY(ctx, timed_launch(ctx, fam, st, [&] {
-              return alnk::launch_diag(32, ALN_EXTEND, pr, false, d2, st);
-            }));
+    int rows[4] = {16, 32, 0, 0};
+    if (pr == ALN_ZDROP) {
+      rows[0] = zd_lanes ? 4 : 8;
+      rows[1] = zd_lanes ? 8 : 16;
+      rows[2] = 32;
+    }
+    int32_t *const cnt[3] = {widen_cnt, widen_cnt + 1, widen_cnt + 4};
+    PairTask *const wq[3] = {wq0, wq1, wq0}; // the first queue is read out before it is filled again
+    for (int k = 0; rows[k]; ++k) {
+      const bool last = rows[k + 1] == 0;
+      alnk::DiagArgs d = diag_args(wq[k], plan->n, cnt[k], rows[k + 1], last ? nullptr : cnt[k + 1],
+                                   last ? nullptr : wq[k + 1]);
+      HIP_TRY(ctx, timed_launch(ctx, fam, st, [&] {
+                return alnk::launch_diag(rows[k], ALN_EXTEND, pr, false, d, st);
+              }));
+    }
   }
   if (plan->p.want_cigar) {
     alnk::WalkArgs wa;
@@ -1404,7 +1439,7 @@ int64_t aln_plan_describe(const aln_plan *plan, aln_launch_info *launches, int32
     const int32_t id = nl;
     const char *fam = plan->xtb_lanes ? "xdrop_lanes_tb"
                                       : (plan->p.prune == ALN_ZDROP ? "zdrop_tb" : "xdrop_tb");
-    add_launch(fam, 4, plan->xtb_lanes ? 16 : 1, plan->xtb_first, plan->xtb_count);
+    add_launch(fam, 4, plan->xtb_lanes ? 64 / plan->xtb_lps : 1, plan->xtb_first, plan->xtb_count);
     pair_tasks(id, plan->xtb_first, plan->xtb_count);
   } else {
     for (const LaunchDesc &L : plan->launches) {
@@ -1427,7 +1462,8 @@ int64_t aln_plan_describe(const aln_plan *plan, aln_launch_info *launches, int32
           fam = L.sides == 16 ? "zdrop_lanes" : (L.sides == 4 ? "zdrop_group" : "zdrop");
         else fam = L.sides == 16 ? "xdrop_lanes" : (L.sides == 4 ? "xdrop_group" : "xdrop");
       }
-      add_launch(fam, L.rows, (L.kind == K_STRIP || L.kind == K_BAND) ? L.waves : L.sides, L.first,
+      add_launch(fam, L.rows,
+                 (L.kind == K_STRIP || L.kind == K_BAND) ? L.waves : (L.sides == 16 ? 64 / L.lps : L.sides), L.first,
                  L.count);
       pair_tasks(id, L.first, L.count);
     }

@@ -218,8 +218,8 @@ struct DiagArgs {
   int32_t match_mismatch;     // 1: the scoring is one match and one mismatch score
 };
 
-// X-drop extension, sixteen sides per wavefront (match / mismatch scoring,
-// alphabet <= 4, no traceback): a persistent grid takes tasks from a queue.
+// X-drop extension, four to sixteen sides per wavefront (match / mismatch
+// scoring, alphabet <= 4): a persistent grid takes tasks from a queue.
 struct XdlArgs {
   BatchPtrs b;
   const PairTask *tasks;     // longest first
@@ -228,12 +228,20 @@ struct XdlArgs {
   int32_t xdrop;
   int32_t gap_open, gap_extend, match, mismatch;
   aln_result *res;
-  int32_t *widen_count;      // regions wider than 64 cells per antidiagonal
+  int32_t *widen_count;      // regions wider than the window
   PairTask *widen;
   int32_t widen_rows;        // RD of the wider kernel
   uint8_t *tb;               // traceback form: code regions (task tb_off)
   int32_t zdrop;             // 1: Z-drop (xdrop holds Z), scores only
+  int32_t lps, window;       // lanes a side (4, 8, 16), cells of its window (64; Z-drop also 128)
 };
+// Wavefronts of a form that its registers let a CU hold (kernels_xdrop.hip
+// asks the compiler for at least these): 4 lanes a side 128 VGPRs, with codes
+// or Z-drop up to 168; 8 lanes of a 64-cell window 104 to 112; 16 lanes 80,
+// with codes 104.
+constexpr int xdrop_lanes_waves(bool tb, bool zdrop, int lps) {
+  return zdrop ? 12 : (lps == 16 ? (tb ? 16 : 24) : (lps == 8 ? 16 : (tb ? 12 : 16)));
+}
 
 // Score-major search for unit-cost edit distance: one workgroup per task,
 // of `waves` wavefronts (1: one F row in LDS; 4: two rows, the previous
@@ -298,11 +306,10 @@ hipError_t launch_diag(int rows, int mode, int prune, bool tb, const DiagArgs &a
 // wavefront, 8 diagonals per lane
 hipError_t launch_xdrop_group(int prune, const DiagArgs &a, hipStream_t s);
 hipError_t launch_walk_diag(const WalkArgs &a, hipStream_t s);
-// tb: the form that also writes traceback codes (4 x 8 bytes per side and
-// antidiagonal, after the window bases)
+// X-drop (Z-drop with a.zdrop), a.lps lanes a side over windows of a.window
+// cells; tb: the form that also writes traceback codes.  waves: wavefronts of
+// the persistent grid.
 hipError_t launch_xdrop_lanes(bool tb, const XdlArgs &a, int waves, hipStream_t s);
-int xdrop_lanes_waves_per_cu(bool tb); // resident wavefronts per CU
-size_t xdrop_lanes_lds_bytes();
 hipError_t launch_search(const SearchArgs &a, hipStream_t s);
 // elt_bytes 1 (uint8 triangle) or 2 (int16); block 256, 512 or 1024 threads;
 // stride one of kFoldStrides

@@ -544,7 +544,8 @@ __global__ __launch_bounds__(64) void walk_diag_wave(WalkArgs a) {
       // (the block's entry holds the base of antidiagonal 64b - 1)
       const int g0 = pre_meta & 7, g1 = (pre_meta >> 3) & 7;
       const int cnt = g1 + 1 - g0;
-      const int st = (int)(pre_meta << 24) >> 30; // the base's step / 2: 0, 1 or -1
+      int st = (int)(pre_meta << 24) >> 30; // the base's step / 2: 0, 1, -1 or (-2) a slide of 8
+      if (st == -2) st = g1 == 7 ? 8 : -8;
       // both sums in one (counts stay below 2^16), an inclusive DPP scan:
       // within rows of 16 lanes, then across rows
       int v = cnt + st * 65536;

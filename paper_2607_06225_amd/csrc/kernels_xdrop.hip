@@ -1,5 +1,5 @@
-// kernels_xdrop.hip -- X-drop seed extension on gfx950: sixteen extension
-// sides per wavefront, four lanes per side, a persistent work queue.
+// kernels_xdrop.hip -- X-drop seed extension on gfx950: sixteen, eight or four
+// extension sides per wavefront, a persistent work queue.
 //
 // The rule (Sec. 2, Sec. 5.2, Sec. 7.2) evaluated antidiagonal by
 // antidiagonal k = i + j in sheared coordinates d = j - i (Sec. 6.2): a
@@ -8,12 +8,24 @@
 // one step before the first survivor to one step after the last.
 //
 // Layout.  A side owns a window of 128 diagonals d = base + 2*pos + (k & 1),
-// pos = 0..63: the 64 cells of one antidiagonal, sixteen per lane (lane g of
-// the side's quad holds pos 16g .. 16g+15).  Per diagonal a lane keeps the
+// pos = 0..63: the 64 cells of one antidiagonal, XC = 16, 8 or 4 per lane on a
+// group of LPS = 4, 8 or 16 lanes (lane g holds pos XC g .. XC g + XC - 1).
+// (Z-drop also 256 diagonals on eight lanes.)  Per diagonal a lane keeps the
 // latest H and the E / F values it passes right / down; E comes from d - 1
 // and F from d + 1 of the previous antidiagonal (the other parity), H of the
-// diagonal predecessor from the same slot, so one quad-DPP per antidiagonal
+// diagonal predecessor from the same slot, so one DPP per antidiagonal
 // moves a value across a lane boundary.
+//
+// What bounds it: instruction issue when the wavefronts fill the SIMDs (0.2 to
+// 0.26 VALU instructions a SIMD cycle), the chain of one step's instructions
+// (about 8 cycles each for a lone wavefront) when they do not, so the step's
+// instruction count either way.  Besides the 9.5 a cell, a step takes the
+// side's bookkeeping, which the fields qi and rj below keep short (matrix
+// edges, end cell and ring addresses are one sum each), one code read, as only
+// one of the two code runs moves, and a slide of the window.  100 000 sides of
+// 150..5 000 bp at X = 100: 290 instructions a step and 21.1 ms before, 240
+// and 18.4 ms; 25 000 with codes 19.9 ms on four lanes a side before, 15.0 ms
+// (on eight).
 //
 // Offset frame.  Every stored value of antidiagonal k is kept minus k*e (e
 // the gap extension score), so a gap step adds nothing:
@@ -47,9 +59,7 @@
 // antidiagonal after the other; per antidiagonal a byte with its first and
 // last group and the window base's step, per 64 antidiagonals the stream
 // offset and the window base (the layout of xdl_tb_table / xdl_tb_stream).
-// Lane gl's groups are 2gl and 2gl + 1; cell m of a lane sits in its group
-// m >> 3 at nibble 7 - (m & 7);
-// its bits, high to low: F passed down opened from H (F-open), E passed right
+// The cell at pos p sits in group p >> 3 at nibble 7 - (p & 7); its bits, high to low: F passed down opened from H (F-open), E passed right
 // opened from H (E-open), H not from E, H not from the diagonal -- so H takes
 // the diagonal, then E, then F, and a gap opens before it extends.  The codes
 // of a survivor are those of the pruned recurrence: every value compared on
@@ -57,10 +67,11 @@
 // stale one.
 //
 // Best cell: keys (H' << 6 | pos) give, per antidiagonal, the highest score
-// and among equals the largest d (smallest i); the running best is the score
-// with a key (-i, -j) for ties.  Survivor bounds come from per-lane survivor
-// masks and quad DPP minima / maxima.  The window slides by one cell when the
-// candidate range reaches an edge; a region wider than 64 cells goes to the
+// and among equals the largest d (smallest i); over antidiagonals the running
+// best takes an equal score only at a smaller i (at the same i a later
+// antidiagonal's j is larger).  Survivor bounds come from per-lane survivor
+// masks and DPP minima / maxima.  The window slides by eight cells, or by one,
+// when the candidate range reaches an edge; a wider region goes to the
 // widening queue (the one-side kernel with wider windows).
 #include "internal.h"
 
@@ -70,53 +81,66 @@ namespace alnk {
 
 namespace {
 
-constexpr int XC = 16;             // cells per lane per antidiagonal
 constexpr int XNEG = -(1 << 22);   // minus infinity in the offset frame
 constexpr int XBIG = (1 << 29);    // threshold of an idle side: nothing survives
-constexpr int kRing = 128;         // codes per ring
-constexpr int kRingMirror = 32;    // first bytes repeated after the ring
-constexpr int kRingStride = kRing + kRingMirror;
-constexpr int kSides = 16;         // sides per wavefront
+constexpr int kRingMirror = 32;    // first bytes repeated after a ring
+constexpr int kSlide = 8;          // cells a window slides by where its candidates allow it
+constexpr int kAhead = 20;         // codes a ring is kept ahead of the window
 constexpr int kZBias = 1 << 20;    // Z-drop: bias of diagonal differences
 
-// quad DPP: lane l reads lane l-1 (shr) / l+1 (shl) of its quad; the quad's
-// edge lane gets `edge`.  quad_perm always names a lane of the quad, so every
-// lane reads a defined value and bound_ctrl changes nothing; with it and no
-// old value the compiler folds the move into the instruction that uses it.
-template <int CTRL> __device__ __forceinline__ int quad_dpp(int v) {
-  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
-}
-__device__ __forceinline__ int quad_shr1(int v, int edge, bool first) {
-  const int x = quad_dpp<0x90>(v); // quad_perm 0,0,1,2
-  return first ? edge : x;
-}
-__device__ __forceinline__ int quad_shl1(int v, int edge, bool last) {
-  const int x = quad_dpp<0xF9>(v); // quad_perm 1,2,3,3
-  return last ? edge : x;
-}
-__device__ __forceinline__ int quad_max(int v) {
-  v = max(v, quad_dpp<0xB1>(v)); // quad_perm 1,0,3,2
-  v = max(v, quad_dpp<0x4E>(v)); // quad_perm 2,3,0,1
-  return v;
-}
-__device__ __forceinline__ int quad_min(int v) {
-  v = min(v, quad_dpp<0xB1>(v));
-  v = min(v, quad_dpp<0x4E>(v));
-  return v;
-}
-__device__ __forceinline__ int quad_bcast0(int v) {
-  return quad_dpp<0x00>(v); // quad_perm 0,0,0,0
+// codes per ring: the window, its lead and a slide back fit (64 cells: 51 + 8
+// + 63 < 128, 128 cells: 51 + 8 + 127 < 256)
+constexpr int lanes_ring(int window) { return 2 * window; }
+constexpr int lanes_lds_bytes(int lps, int window) {
+  return (64 / lps) * 2 * (lanes_ring(window) + kRingMirror);
 }
 
-// 16 ring bytes from `addr` (any alignment; the mirror covers the wrap)
-__device__ __forceinline__ void ring16(const uint8_t *ring, int addr, uint32_t (&w)[4]) {
-  const uint32_t *d = reinterpret_cast<const uint32_t *>(ring + (addr & ~3));
-  uint32_t x[5];
-#pragma unroll
-  for (int k = 0; k < 5; ++k) x[k] = d[k];
-  const uint32_t sh = (uint32_t)addr & 3u;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) w[k] = __builtin_amdgcn_alignbyte(x[k + 1], x[k], sh);
+// Moves within a side's group of L lanes (4, 8 or 16: inside one DPP row).
+// quad_perm always names a lane of the quad, so every lane reads a defined
+// value and bound_ctrl changes nothing; with it and no old value the compiler
+// folds the move into the instruction that uses it.
+template <int CTRL> __device__ __forceinline__ int row_dpp(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+// lane l reads lane l-1 (shr) / l+1 (shl) of its group; the group's edge lane
+// gets `edge`
+template <int L> __device__ __forceinline__ int grp_shr1(int v, int edge, bool first) {
+  if (L == 16) return __builtin_amdgcn_update_dpp(edge, v, 0x111, 0xf, 0xf, false); // row_shr:1
+  const int x = L == 4 ? row_dpp<0x90>(v) : row_dpp<0x111>(v); // quad_perm 0,0,1,2
+  return first ? edge : x;
+}
+template <int L> __device__ __forceinline__ int grp_shl1(int v, int edge, bool last) {
+  if (L == 16) return __builtin_amdgcn_update_dpp(edge, v, 0x101, 0xf, 0xf, false); // row_shl:1
+  const int x = L == 4 ? row_dpp<0xF9>(v) : row_dpp<0x101>(v); // quad_perm 1,2,3,3
+  return last ? edge : x;
+}
+// every lane of the group: the group's maximum / minimum
+template <int L> __device__ __forceinline__ int grp_max(int v) {
+  v = max(v, row_dpp<0xB1>(v));               // quad_perm 1,0,3,2
+  v = max(v, row_dpp<0x4E>(v));               // quad_perm 2,3,0,1
+  if (L >= 8) v = max(v, row_dpp<0x141>(v));  // row_half_mirror
+  if (L >= 16) v = max(v, row_dpp<0x140>(v)); // row_mirror
+  return v;
+}
+template <int L> __device__ __forceinline__ uint32_t grp_umin(uint32_t v) {
+  v = min(v, (uint32_t)row_dpp<0xB1>((int)v));
+  v = min(v, (uint32_t)row_dpp<0x4E>((int)v));
+  if (L >= 8) v = min(v, (uint32_t)row_dpp<0x141>((int)v));
+  if (L >= 16) v = min(v, (uint32_t)row_dpp<0x140>((int)v));
+  return v;
+}
+
+// 4 NW ring bytes from `addr`, any alignment (the mirror covers the wrap): one
+// unaligned LDS read of 8 or 16 bytes; for 4 bytes two aligned dwords and a
+// byte align, which take less time (4.4 against 4.8 ms for 400 sides alone)
+template <int NW>
+__device__ __forceinline__ void ring_read(const uint8_t *ring, int addr, uint32_t (&w)[NW]) {
+  if constexpr (NW == 1) {
+    const uint32_t *d = reinterpret_cast<const uint32_t *>(ring + (addr & ~3));
+    w[0] = __builtin_amdgcn_alignbyte(d[1], d[0], (uint32_t)addr & 3u);
+  } else {
+    __builtin_memcpy(w, ring + addr, 4 * NW);
+  }
 }
 
 // v = 2 v + bit, the bit taken from a compare's lane mask as a carry
@@ -134,24 +158,31 @@ __device__ __forceinline__ uint32_t byte_reverse(uint32_t x) {
 
 } // namespace
 
-// three wavefronts per SIMD: the form with traceback needs a few registers
-// more than fit, and spills two of them on its task-start path
+// LPS lanes a side, XC cells a lane: a window of W = LPS * XC cells.
 // ZD: Z-drop (Sec. 9.3) instead of X-drop: a candidate is kept when its H
 // plus its distance |d - d_best| from the best cell's diagonal reaches the
 // threshold.  The thresholds then differ between diagonals, so the pruning
 // above is made explicit: H, E and F of a removed cell or of a cell outside
 // the candidate range are minus infinity, and only kept cells enter the
 // antidiagonal's best.
-// Four wavefronts per SIMD for the X-drop score form (128 VGPRs, no spill in
-// the step), three with codes or Z-drop (they need more registers)
-template <bool TB, bool ZD>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(TB || ZD ? 3 : 4))) void
-xdrop_lanes_kernel(XdlArgs a) {
-  extern __shared__ __align__(16) uint8_t smem[];
+template <int LPS, int XC, bool TB, bool ZD>
+__device__ __forceinline__ void lanes_body(const XdlArgs &a, uint8_t *smem) {
+  constexpr int W = LPS * XC;          // cells of a side's window
+  constexpr int PB = W == 64 ? 6 : 7;  // bits of a position
+  constexpr int NW = XC / 4;           // code dwords a lane reads
+  constexpr int kRing = lanes_ring(W);
+  constexpr int kRingStride = kRing + kRingMirror;
+  constexpr int kStageB = 32 / LPS;    // codes a lane stages at a time
+  // the candidate range of the widest antidiagonal kept here: the window for
+  // X-drop, 126 cells (a range of 250 diagonals, as the one-side kernel's
+  // first window) for the wide window
+  constexpr int kWidest = W == 64 ? 64 : 126;
+  static_assert(W == 64 || W == 128, "positions are 6 or 7 bits");
+  static_assert(!TB || W == 64, "the code layout is that of 64-cell windows");
   const int lane = threadIdx.x & 63;
-  const int gl = lane & 3;        // lane within the side's quad
-  const int side = lane >> 2;     // side slot of this wavefront
-  const bool qfirst = gl == 0, qlast = gl == 3;
+  const int gl = lane & (LPS - 1); // lane within the side's group
+  const int side = lane / LPS;     // side slot of this wavefront
+  const bool qfirst = gl == 0, qlast = gl == LPS - 1;
   uint8_t *qring = smem + side * 2 * kRingStride;
   uint8_t *rring = qring + kRingStride;
 
@@ -167,44 +198,49 @@ xdrop_lanes_kernel(XdlArgs a) {
 #pragma unroll
   for (int m = 0; m < XC; ++m) H0[m] = H1[m] = E0[m] = F0[m] = E1[m] = F1[m] = XNEG;
 
-  // side state, equal across the quad
+  // Side state, equal across the group.  qi, rj: row and column of the cell
+  // at pos 0 (pos p is cell (qi - p, rj + p) of antidiagonal k = qi + rj, on
+  // diagonal base + 2p + (k & 1), base = rj - qi - (k & 1)); an odd
+  // antidiagonal's rj, an even one's qi is one more than the antidiagonal's
+  // before.
   bool active = false, exhausted = false;
-  int task = 0, pair = 0, M = 0, N = 0, base = 0, k = 0, kE = 0, T = XBIG;
+  int task = 0, pair = 0, M = 0, N = 0, qi = 0, rj = 0;
   int plo = 1, phi = 0, qtop = 0, rtop = 0;
-  int best = 0;         // best score so far
-  uint32_t best_key = 0; // its cell: (0xffff - i) << 16 | (0xffff - j)
-  long long cells = 0;
+  int bk = XBIG;              // best score so far, in the antidiagonal's frame
+  int best_i = 0, best_j = 0; // its cell
+  int cells = 0;              // at most 126 * (M + N) < 2^31
+  // codes of this lane's cells, kept from one antidiagonal to the next
+  uint32_t qw[NW], rw[NW];
+  bool reload = true; // wave-uniform: some side's window moved, or is new
   const uint8_t *Q = nullptr, *R = nullptr;
   // traceback: one byte per antidiagonal, a table entry per 64, the codes
   uint8_t *tb_meta = nullptr; // the side's region
   int tcur = 0;               // byte offset in the region of the next code dword
-  int bprev = 0;              // window base of the antidiagonal before
+  uint32_t sbits = 0;         // the window base's step (bits 6-7 of the byte)
   uint32_t mlo = 0, mhi = 0;  // lane gl: bytes of antidiagonals 32n + 8gl .. + 7, newest on top
 
   // 32 codes per call into a ring (the query reversed), padding (4) past
-  // the sequence; lane gl stages codes top + 8gl .. top + 8gl + 7
+  // the sequence; lane gl stages kStageB of them
   auto stage = [&](const uint8_t *src, int len, uint8_t *ring, int top, bool rev) {
-    const int c0 = top + 8 * gl;
-    uint32_t lo = 0, hi = 0;
+    const int c0 = top + kStageB * gl;
+    uint32_t w[2] = {0, 0};
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < kStageB; ++b) {
       const int c = c0 + b;
       const uint32_t raw = src[min(c, len - 1)]; // clamped: issued unconditionally
       const uint32_t v = (c < len) ? min(raw, 4u) : 4u;
-      if (b < 4) lo |= v << (8 * b);
-      else hi |= v << (8 * (b - 4));
+      const int at = rev ? kStageB - 1 - b : b; // byte of the stored run
+      w[at >> 2] |= v << (8 * (at & 3));
     }
-    int at;
-    if (rev) { // code c lives at (127 - c) mod 128
-      const uint32_t rl = byte_reverse(hi), rh = byte_reverse(lo);
-      lo = rl;
-      hi = rh;
-      at = (kRing - 8 - (c0 & (kRing - 1))) & (kRing - 1);
-    } else {
-      at = c0 & (kRing - 1);
-    }
-    *reinterpret_cast<uint2 *>(ring + at) = make_uint2(lo, hi);
-    if (at < kRingMirror) *reinterpret_cast<uint2 *>(ring + kRing + at) = make_uint2(lo, hi);
+    // reversed: code c lives at (kRing - 1 - c) mod kRing
+    const int at = rev ? (kRing - kStageB - (c0 & (kRing - 1))) & (kRing - 1) : c0 & (kRing - 1);
+    auto put = [&](uint8_t *dst) {
+      if constexpr (kStageB == 8) *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
+      else if constexpr (kStageB == 4) *reinterpret_cast<uint32_t *>(dst) = w[0];
+      else *reinterpret_cast<uint16_t *>(dst) = (uint16_t)w[0];
+    };
+    put(ring + at);
+    if (at < kRingMirror) put(ring + kRing + at);
   };
 
   for (;;) {
@@ -215,7 +251,7 @@ xdrop_lanes_kernel(XdlArgs a) {
       if (need) {
         int t = 0;
         if (qfirst) t = atomicAdd(a.queue, 1);
-        t = quad_bcast0(t);
+        t = LPS == 4 ? row_dpp<0x00>(t) : __shfl(t, lane & ~(LPS - 1), 64); // the first lane's
         if (t >= a.ntasks) {
           exhausted = true;
         } else {
@@ -239,25 +275,23 @@ xdrop_lanes_kernel(XdlArgs a) {
               uint8_t *tbp = a.tb + a.tasks[t].tb_off;
               tb_meta = tbp;
               tcur = (int)xdl_tb_stream(nb);
-              bprev = -64; // the first window base, set below
+              sbits = 0;
               mlo = 0;
               mhi = 1u << 24; // antidiagonal 0: no groups (first 1, last 0)
-              if (qfirst) *reinterpret_cast<int2 *>(tbp + xdl_tb_table(nb)) = make_int2(0, -64);
+              if (qfirst) *reinterpret_cast<int2 *>(tbp + xdl_tb_table(nb)) = make_int2(0, -W);
             }
             fresh = true; // arrays reset below, outside this loop
-            base = -64;
-            k = 1;
-            kE = ge;
-            best = 0; // score 0 at (0,0)
-            best_key = 0xffffffffu;
-            T = -X - kE;
-            plo = 31; // candidates of k = 1: d = -1, 1
-            phi = 32;
+            qi = W / 2; // k = 1, base -W
+            rj = 1 - W / 2;
+            bk = -ge; // score 0 at (0,0)
+            best_i = best_j = 0;
+            plo = W / 2 - 1; // candidates of k = 1: d = -1, 1
+            phi = W / 2;
             cells = 0;
             qtop = 0;
             rtop = 0;
             // rings start as padding
-            for (int e = gl * 4; e < 2 * kRingStride; e += 16)
+            for (int e = gl * 4; e < 2 * kRingStride; e += 4 * LPS)
               *reinterpret_cast<uint32_t *>(qring + e) = 0x04040404u;
             active = true;
           }
@@ -267,13 +301,14 @@ xdrop_lanes_kernel(XdlArgs a) {
     }
     if (!__ballot(active)) break;
     // new sides: every slot minus infinity but the cell (0,0) with H = 0 at
-    // d = 0 (pos 32, parity 0), whose E and F outputs are the gap open in the
+    // d = 0 (pos W / 2, parity 0), whose E and F outputs are the gap open in the
     // frame of k = 1
     if (__ballot(fresh)) {
+      reload = true;
       if (fresh) {
 #pragma unroll
         for (int m = 0; m < XC; ++m) H0[m] = H1[m] = E0[m] = F0[m] = E1[m] = F1[m] = XNEG;
-        if (gl == 2) {
+        if (gl == LPS / 2) {
           H0[0] = 0;
           E0[0] = go;
           F0[0] = go;
@@ -281,16 +316,19 @@ xdrop_lanes_kernel(XdlArgs a) {
       }
     }
 
-    // one antidiagonal of parity P (P == k & 1 for every active side)
+    // one antidiagonal of parity P (the antidiagonal's, for every active side)
     auto step = [&](auto ptag) {
       constexpr int P = decltype(ptag)::value;
-      // ---- keep the rings ahead of the window (26 codes of margin; the
-      // window moves at most two codes per antidiagonal pair)
+      // ---- keep the rings ahead of the window: the codes read before the
+      // next check lie at most 10 past the top (a slide of 8 and one
+      // antidiagonal each way), and a ring filled to 51 past it still holds the
+      // window's last code after a slide back by 8 (51 + 8 + 63 < 128; further
+      // slides back take at least as many antidiagonals as they move)
       for (; P == 1;) {
-        const int topq = ((k - base - P) >> 1) - 1;  // query code of pos 0
-        const int topr = ((k + base + P) >> 1) + 62; // reference code of pos 63
-        const bool sq = active && qtop < topq + 26;
-        const bool sr = active && rtop < topr + 26;
+        const int topq = qi - 1;     // query code of pos 0
+        const int topr = rj + W - 2; // reference code of the last pos
+        const bool sq = active && qtop < topq + kAhead;
+        const bool sr = active && rtop < topr + kAhead;
         if (!__ballot(sq || sr)) break;
         if (sq) {
           stage(Q, M, qring, qtop, true);
@@ -301,30 +339,40 @@ xdrop_lanes_kernel(XdlArgs a) {
           rtop += 32;
         }
       }
-      // ---- this lane's codes: query i - 1 (descending) and reference j - 1
-      uint32_t qw[4], rw[4];
-      {
-        const int cq = ((k - base - P) >> 1) - 1 - XC * gl;
-        const int cr = ((k + base + P) >> 1) - 1 + XC * gl;
-        ring16(qring, (kRing - 1 - cq) & (kRing - 1), qw);
-        ring16(rring, cr & (kRing - 1), rw);
+      // ---- this lane's codes: query i - 1 (descending) and reference j - 1.
+      // One of the two runs moves by one code an antidiagonal, so it alone is
+      // read, one antidiagonal ahead (below); both after a slide.
+      auto read_q = [&](uint32_t(&w)[NW], int ahead) {
+        ring_read<NW>(qring, (kRing - (qi + ahead) + XC * gl) & (kRing - 1), w);
+      };
+      auto read_r = [&](uint32_t(&w)[NW], int ahead) {
+        ring_read<NW>(rring, (rj + ahead - 1 + XC * gl) & (kRing - 1), w);
+      };
+      if (reload) {
+        read_q(qw, 0);
+        read_r(rw, 0);
+        reload = false;
       }
       // ---- substitution bytes; cells outside [plo, phi] get the penalty
-      uint32_t sc[4], inr_rev; // inr_rev: bit 15 - m set for cells m in range
+      uint32_t sc[NW], inr_rev; // inr_rev: bit XC - 1 - m set for cells m in range
       {
         const int lo = min(max(plo - XC * gl, 0), XC);
         const int hi = min(max(phi - XC * gl + 1, 0), XC);
         // hi >= lo always (an idle side has plo = phi + 1)
-        inr_rev = ((1u << (hi - lo)) - 1u) << (XC - hi);
-        const uint32_t out = ~(((1u << (hi - lo)) - 1u) << lo);
+        const uint32_t in = (1u << (hi - lo)) - 1u;
+        inr_rev = in << (XC - hi);
+        const uint32_t out = ~(in << lo);
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < NW; ++w) {
           const uint32_t nib = (out >> (4 * w)) & 15u;
-          const uint32_t spread = (nib * 0x00204081u) & 0x01010101u;
-          const uint32_t x = (qw[w] ^ rw[w]) | (spread << 2);
-          sc[w] = __builtin_amdgcn_perm(tab_hi, tab_lo, x);
+          const uint32_t spread = __umul24(nib, 0x00810204u) & 0x04040404u; // bit 2 of each byte
+          sc[w] = __builtin_amdgcn_perm(tab_hi, tab_lo, (qw[w] ^ rw[w]) | spread);
         }
       }
+      uint32_t nw[NW]; // the run that moves next, read now
+      if (P == 1) read_q(nw, 1);
+      else read_r(nw, 1);
+      const int T = bk - X;
       // ---- the cells
       int kmax = INT32_MIN;
       uint32_t sb = 0, code0 = 0, code1 = 0;
@@ -332,11 +380,10 @@ xdrop_lanes_kernel(XdlArgs a) {
       // biased so that the distance is one unsigned difference per cell
       uint32_t zlane = 0;
       if (ZD) {
-        const int bi = 0xffff - (int)(best_key >> 16), bj = 0xffff - (int)(best_key & 0xffffu);
-        zlane = (uint32_t)(base + P + 2 * XC * gl - (bj - bi) + kZBias);
+        zlane = (uint32_t)(rj - qi + 2 * XC * gl - (best_j - best_i) + kZBias);
       }
-      const int xin = P == 0 ? quad_shr1(E1[XC - 1], XNEG, qfirst)
-                             : quad_shl1(F0[0], XNEG, qlast);
+      const int xin = P == 0 ? grp_shr1<LPS>(E1[XC - 1], XNEG, qfirst)
+                             : grp_shl1<LPS>(F0[0], XNEG, qlast);
 #pragma unroll
       for (int m = 0; m < XC; ++m) {
         const int ein = P == 0 ? (m == 0 ? xin : E1[m - 1]) : E0[m];
@@ -367,8 +414,8 @@ xdrop_lanes_kernel(XdlArgs a) {
           F1[m] = fn;
         }
         // X-drop: a removed cell never beats a kept one
-        kmax = max(kmax, (ZD && !keep) ? INT32_MIN : ((h << 6) | m));
-        // shift the survivor bit in: sb = 2 sb + keep (cell m ends at bit 15 - m)
+        kmax = max(kmax, (ZD && !keep) ? INT32_MIN : ((h << PB) | m));
+        // shift the survivor bit in: sb = 2 sb + keep (cell m ends at bit XC - 1 - m)
         shift_in(sb, keep);
         if (TB) { // the cell's code, high bit first
           uint32_t &c = m < 8 ? code0 : code1;
@@ -382,26 +429,32 @@ xdrop_lanes_kernel(XdlArgs a) {
         // only the 8-cell groups g0 .. g1 that hold candidates are stored
         // (a walk reads survivors only), after the antidiagonal before's
         const int g0 = plo >> 3, span = (phi >> 3) - g0;
-        const int e0 = 2 * gl - g0; // stream slot of this lane's first group
-        uint32_t *dst = reinterpret_cast<uint32_t *>(tb_meta + (tcur + 4 * e0));
-        if ((unsigned)e0 <= (unsigned)span) dst[0] = code0;
-        if ((unsigned)(e0 + 1) <= (unsigned)span) dst[1] = code1;
+        // stream slot of this lane's first group (4 cells a lane: the even
+        // lane holds its group's upper half)
+        const int e0 = XC * gl / 8 - g0;
+        uint8_t *dst = tb_meta + (tcur + 4 * e0);
+        if ((unsigned)e0 <= (unsigned)span) {
+          if constexpr (XC == 4) *reinterpret_cast<uint16_t *>(dst + ((gl & 1) ? 0 : 2)) = (uint16_t)code0;
+          else *reinterpret_cast<uint32_t *>(dst) = code0;
+        }
+        if (XC == 16 && (unsigned)(e0 + 1) <= (unsigned)span)
+          *reinterpret_cast<uint32_t *>(dst + 4) = code1;
         tcur += 4 * (span + 1);
         // the antidiagonal's byte: g0 (bits 0-2), g1 (3-5) and the window
         // base's step from the antidiagonal before, (base - bprev) / 2 in
         // two's complement (bits 6-7).  Lane gl collects those of its 8 of
-        // every 32 antidiagonals, and the side's four lanes store the 32
+        // every 32 antidiagonals, and the side's first four lanes store the 32
         // bytes at once (one whole memory sector: smaller stores cost as
         // much each)
-        const uint32_t mbyte = ((uint32_t)plo >> 3) | ((uint32_t)phi & 0x38u) |
-                               (((uint32_t)(base - bprev) << 5) & 0xc0u);
-        bprev = base;
+        const int k = qi + rj;
+        const uint32_t mbyte = ((uint32_t)plo >> 3) | ((uint32_t)phi & 0x38u) | sbits;
+        sbits = 0;
         if (((k >> 3) & 3) == gl) {
           mlo = __builtin_amdgcn_alignbit(mhi, mlo, 8);
           mhi = __builtin_amdgcn_alignbit(mbyte, mhi, 8);
         }
         if ((k & 31) == 31) {
-          *reinterpret_cast<uint2 *>(tb_meta + (k - 31) + 8 * gl) = make_uint2(mlo, mhi);
+          if (gl < 4) *reinterpret_cast<uint2 *>(tb_meta + (k - 31) + 8 * gl) = make_uint2(mlo, mhi);
           if ((k & 63) == 63) {
             // the next block starts on a 16-byte boundary; its entry holds
             // the base of its antidiagonal before (the table has room for
@@ -410,41 +463,44 @@ xdrop_lanes_kernel(XdlArgs a) {
             const int nb = (M + N + 64) >> 6;
             if (qfirst)
               reinterpret_cast<int2 *>(tb_meta + xdl_tb_table(nb))[(k + 1) >> 6] =
-                  make_int2((tcur - (int)xdl_tb_stream(nb)) >> 2, base);
+                  make_int2((tcur - (int)xdl_tb_stream(nb)) >> 2, rj - qi - P);
           }
         }
       }
       sb &= inr_rev;
       // ---- the antidiagonal's outcome per side
-      kmax = quad_max(kmax | (XC * gl));
-      const int fl = sb ? XC * gl + (int)__builtin_clz(sb) - 16 : 64;
-      const int ll = sb ? XC * gl + 15 - (int)__builtin_ctz(sb) : -1;
-      const int f = quad_min(fl), l = quad_max(ll);
-      const bool surv = active && f <= l;
-      if (surv) {
-        const int hs = kmax >> 6, ps = kmax & 63;
-        const int d = base + 2 * ps + P;
-        const int bi = (k - d) >> 1, bj = k - bi;
-        const uint32_t key = ((uint32_t)(0xffff - bi) << 16) | (uint32_t)(0xffff - bj);
-        const int cs = hs + kE;
-        if (cs > best || (cs == best && key > best_key)) {
-          best = cs;
-          best_key = key;
-        }
+      kmax = grp_max<LPS>(kmax | (XC * gl));
+      // first and last survivor: bit counts of an empty lane read 2^32 - 1 and
+      // saturate to a position that never wins (no survivor at all: f > l)
+      const uint32_t sb32 = sb << (32 - XC);
+      const uint32_t c1 = sb ? (uint32_t)__builtin_clz(sb32) : ~0u;
+      const uint32_t c0 = sb ? (uint32_t)__builtin_ctz(sb) : ~0u;
+      const uint32_t fl = __builtin_elementwise_add_sat((uint32_t)(XC * gl), c1);
+      const uint32_t ll = __builtin_elementwise_sub_sat((uint32_t)(XC * gl + XC - 1), c0);
+      const int f = (int)grp_umin<LPS>(fl), l = grp_max<LPS>((int)ll);
+      const bool surv = active && (uint32_t)f <= (uint32_t)l;
+      {
+        // (without survivors every score is below T <= bk)
+        const int hs = kmax >> PB, ps = kmax & (W - 1);
+        const int bi = qi - ps;
+        // equal score: the smaller i (of one i, the earlier antidiagonal's j
+        // is the smaller)
+        const bool up = hs > bk || (hs == bk && bi < best_i);
+        best_i = up ? bi : best_i;
+        best_j = up ? rj + ps : best_j;
+        bk = max(bk, hs);
       }
       // ---- next antidiagonal: candidates in the other parity's positions,
-      // clipped to the matrix
-      const int kn = k + 1;
-      const int kEn = kE + ge;
-      int nlo = P == 0 ? f - 1 : f, nhi = P == 0 ? l : l + 1;
-      const int dlo = max(-kn, kn - 2 * M), dhi = min(kn, 2 * N - kn);
-      nlo = max(nlo, (dlo - base - (1 - P)) >> 1);
-      nhi = min(nhi, (dhi - base - (1 - P)) >> 1);
-      const bool cont = surv && kn <= M + N && nlo <= nhi;
-      const bool wide = cont && nhi - nlo > 63;
+      // clipped to the matrix (0 <= i <= M, 0 <= j <= N)
+      const int qn = P == 1 ? qi + 1 : qi, rn = P == 1 ? rj : rj + 1;
+      const int nlo = max(max(P == 0 ? f - 1 : f, -rn), qn - M);
+      const int nhi = min(min(P == 0 ? l : l + 1, qn), N - rn);
+      const bool cont = surv && nlo <= nhi;
+      const bool wide = cont && nhi - nlo >= kWidest;
       if (active && (!cont || wide)) {
         // the extension ends here (or leaves for a wider window)
-        if (TB && (k & 31) != 31 && 8 * gl <= (k & 31)) { // the bytes of the last, partial 32
+        const int k = qi + rj;
+        if (TB && gl < 4 && (k & 31) != 31 && 8 * gl <= (k & 31)) { // the bytes of the last, partial 32
           const int sh = 8 * gl + 7 > (k & 31) ? 8 * (7 - (k & 7)) : 0; // a partial 8
           const unsigned long long m8 = ((unsigned long long)mhi << 32 | mlo) >> sh;
           *reinterpret_cast<uint2 *>(tb_meta + (k & ~31) + 8 * gl) =
@@ -468,79 +524,106 @@ xdrop_lanes_kernel(XdlArgs a) {
             dst->aux = 0;
             if (TB) const_cast<PairTask *>(a.tasks)[task].aux = 1;
           } else {
-            res->score = best;
-            res->q_end = 0xffff - (int)(best_key >> 16);
-            res->r_end = 0xffff - (int)(best_key & 0xffffu);
+            res->score = bk + k * ge;
+            res->q_end = best_i;
+            res->r_end = best_j;
             res->cells = cells;
           }
         }
         active = false;
-        T = XBIG;
-        plo = 1;
-        phi = 0;
+        bk = XBIG;
       }
-      if (active) {
-        // interior cells (i, j >= 1) of the next antidiagonal
-        const int clo = max(nlo, (2 - kn - base - (1 - P)) >> 1);
-        const int chi = min(nhi, (kn - 2 - base - (1 - P)) >> 1);
-        cells += chi >= clo ? chi - clo + 1 : 0;
-        k = kn;
-        kE = kEn;
-        T = best - X - kEn;
-        plo = nlo;
-        phi = nhi;
+      // (an idle side keeps an empty range and a threshold nothing reaches)
+      plo = active ? nlo : 1;
+      phi = active ? nhi : 0;
+      // interior cells (i, j >= 1) of the next antidiagonal
+      cells += max(min(phi, qn - 1) - max(plo, 1 - rn) + 1, 0);
+      qi = qn;
+      rj = rn;
+      bk -= ge;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        if (P == 1) qw[w] = nw[w];
+        else rw[w] = nw[w];
       }
-      // ---- keep the candidates inside the window: slide by one cell.  The
-      // live arrays are both H and the E / F just written.
-      const bool sup = active && plo < 0, sdn = active && phi > 63;
+      // ---- keep the candidates inside the window.  The live arrays are both
+      // H and the E / F just written.  A side whose candidates leave it slides
+      // by eight cells where they still fit then, else by one: with sixteen
+      // sides a wavefront, slides of one cell came on nearly every
+      // antidiagonal and were 40% of the kernel's instructions (344 a step,
+      // 205 without them; 400 000 sides of 150..5 000 bp, X = 100).
+      const bool sup = active && plo < 0, sdn = active && phi >= W;
+      const bool sup8 = sup && phi + kSlide < W - (TB ? kSlide : 0); // TB: see mbyte
+      const bool sdn8 = sdn && plo >= kSlide;
       // The shifts are selects in place under a wave-uniform branch: a
       // branch on the side's own flag made the compiler copy every array at
       // its join on every antidiagonal (about 100 moves per lane).
-      if (__ballot(sup)) { // base -= 2: every pos moves up one
-#define XD_SLIDE_UP(A)                                                                      \
-  {                                                                                         \
-    const int c = quad_shr1(A[XC - 1], XNEG, qfirst);                                       \
-    _Pragma("unroll") for (int m = XC - 1; m > 0; --m) A[m] = sup ? A[m - 1] : A[m];        \
-    A[0] = sup ? c : A[0];                                                                  \
-  }
-        XD_SLIDE_UP(H0)
-        XD_SLIDE_UP(H1)
-        if (P == 0) {
-          XD_SLIDE_UP(E0)
-          XD_SLIDE_UP(F0)
-        } else {
-          XD_SLIDE_UP(E1)
-          XD_SLIDE_UP(F1)
+      auto slide_up = [&](int(&A)[XC], bool on, auto by_tag) { // every pos moves up
+        constexpr int S = decltype(by_tag)::value, SL = S / XC, SC = S % XC; // lanes, cells
+        int v[XC]; // moved by whole lanes
+#pragma unroll
+        for (int m = 0; m < XC; ++m) {
+          v[m] = A[m];
+#pragma unroll
+          for (int t = 0; t < SL; ++t) v[m] = grp_shr1<LPS>(v[m], XNEG, qfirst);
         }
-#undef XD_SLIDE_UP
-        if (sup) {
-          base -= 2;
-          plo += 1;
-          phi += 1;
+        int c[SC + 1];
+#pragma unroll
+        for (int m = 0; m < SC; ++m) c[m] = grp_shr1<LPS>(v[XC - SC + m], XNEG, qfirst);
+#pragma unroll
+        for (int m = XC - 1; m >= SC; --m) A[m] = on ? v[m - SC] : A[m];
+#pragma unroll
+        for (int m = 0; m < SC; ++m) A[m] = on ? c[m] : A[m];
+      };
+      auto slide_down = [&](int(&A)[XC], bool on, auto by_tag) { // every pos moves down
+        constexpr int S = decltype(by_tag)::value, SL = S / XC, SC = S % XC;
+        int v[XC];
+#pragma unroll
+        for (int m = 0; m < XC; ++m) {
+          v[m] = A[m];
+#pragma unroll
+          for (int t = 0; t < SL; ++t) v[m] = grp_shl1<LPS>(v[m], XNEG, qlast);
         }
-      }
-      if (__ballot(sdn)) { // base += 2: every pos moves down one
-#define XD_SLIDE_DOWN(A)                                                                    \
-  {                                                                                         \
-    const int c = quad_shl1(A[0], XNEG, qlast);                                             \
-    _Pragma("unroll") for (int m = 0; m < XC - 1; ++m) A[m] = sdn ? A[m + 1] : A[m];        \
-    A[XC - 1] = sdn ? c : A[XC - 1];                                                        \
-  }
-        XD_SLIDE_DOWN(H0)
-        XD_SLIDE_DOWN(H1)
-        if (P == 0) {
-          XD_SLIDE_DOWN(E0)
-          XD_SLIDE_DOWN(F0)
-        } else {
-          XD_SLIDE_DOWN(E1)
-          XD_SLIDE_DOWN(F1)
-        }
-#undef XD_SLIDE_DOWN
-        if (sdn) {
-          base += 2;
-          plo -= 1;
-          phi -= 1;
-        }
+        int c[SC + 1];
+#pragma unroll
+        for (int m = 0; m < SC; ++m) c[m] = grp_shl1<LPS>(v[m], XNEG, qlast);
+#pragma unroll
+        for (int m = 0; m < XC - SC; ++m) A[m] = on ? v[m + SC] : A[m];
+#pragma unroll
+        for (int m = 0; m < SC; ++m) A[XC - SC + m] = on ? c[m] : A[XC - SC + m];
+      };
+      using One = std::integral_constant<int, 1>;
+      using Many = std::integral_constant<int, kSlide>;
+      auto up_all = [&](bool on, auto by_tag) { // base falls
+        constexpr int S = decltype(by_tag)::value;
+        slide_up(H0, on, by_tag);
+        slide_up(H1, on, by_tag);
+        slide_up(P == 0 ? E0 : E1, on, by_tag);
+        slide_up(P == 0 ? F0 : F1, on, by_tag);
+        qi += on ? S : 0;
+        rj -= on ? S : 0;
+        plo += on ? S : 0;
+        phi += on ? S : 0;
+        if (TB) sbits = on ? (S == 1 ? 0xc0u : 0x80u) : sbits;
+      };
+      auto down_all = [&](bool on, auto by_tag) { // base rises
+        constexpr int S = decltype(by_tag)::value;
+        slide_down(H0, on, by_tag);
+        slide_down(H1, on, by_tag);
+        slide_down(P == 0 ? E0 : E1, on, by_tag);
+        slide_down(P == 0 ? F0 : F1, on, by_tag);
+        qi -= on ? S : 0;
+        rj += on ? S : 0;
+        plo -= on ? S : 0;
+        phi -= on ? S : 0;
+        if (TB) sbits = on ? (S == 1 ? 0x40u : 0x80u) : sbits;
+      };
+      if (__ballot(sup || sdn)) {
+        reload = true;
+        if (__ballot(sup8)) up_all(sup8, Many{});
+        if (__ballot(sdn8)) down_all(sdn8, Many{});
+        if (__ballot(sup && !sup8)) up_all(sup && !sup8, One{});
+        if (__ballot(sdn && !sdn8)) down_all(sdn && !sdn8, One{});
       }
     };
     step(std::integral_constant<int, 1>{});
@@ -553,29 +636,40 @@ xdrop_lanes_kernel(XdlArgs a) {
   }
 }
 
-size_t xdrop_lanes_lds_bytes() { return (size_t)kSides * 2 * kRingStride; }
+// Sixteen cells a lane: four wavefronts per SIMD for the X-drop score form
+// (128 VGPRs, no spill in the step), three with codes or Z-drop (they need more
+// registers).  Fewer cells a lane take fewer registers (xdrop_lanes_waves).
+template <int LPS, int XC, bool TB, bool ZD>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(xdrop_lanes_waves(TB, ZD, LPS) / 4))) void
+xdrop_lanes_kernel(XdlArgs a) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  lanes_body<LPS, XC, TB, ZD>(a, smem);
+}
 
-hipError_t launch_xdrop_lanes(bool tb, const XdlArgs &a, int waves, hipStream_t s) {
-  if (a.ntasks <= 0) return hipSuccess;
-  if (a.zdrop && tb) return hipErrorInvalidValue; // Z-drop codes: the one-side pass
-  if (tb)
-    hipLaunchKernelGGL((xdrop_lanes_kernel<true, false>), dim3(waves), dim3(64), xdrop_lanes_lds_bytes(), s, a);
-  else if (a.zdrop)
-    hipLaunchKernelGGL((xdrop_lanes_kernel<false, true>), dim3(waves), dim3(64), xdrop_lanes_lds_bytes(), s, a);
-  else
-    hipLaunchKernelGGL((xdrop_lanes_kernel<false, false>), dim3(waves), dim3(64), xdrop_lanes_lds_bytes(), s, a);
+template <int LPS, int XC, bool TB, bool ZD>
+static hipError_t launch_lanes(const XdlArgs &a, int waves, hipStream_t s) {
+  hipLaunchKernelGGL((xdrop_lanes_kernel<LPS, XC, TB, ZD>), dim3(waves), dim3(64),
+                     (size_t)lanes_lds_bytes(LPS, LPS * XC), s, a);
   return hipGetLastError();
 }
 
-int xdrop_lanes_waves_per_cu(bool tb) {
-  int nb = 0;
-  const hipError_t e =
-      tb ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, xdrop_lanes_kernel<true, false>, 64,
-                                                        xdrop_lanes_lds_bytes())
-         : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, xdrop_lanes_kernel<false, false>, 64,
-                                                        xdrop_lanes_lds_bytes());
-  if (e != hipSuccess) return 4;
-  return nb > 0 ? nb : 1;
+// Forms by lanes a side: 4, 8 or 16 of a 64-cell window (X-drop, with codes or
+// without; Z-drop without codes: 4), or 8 of a 128-cell window (Z-drop).
+hipError_t launch_xdrop_lanes(bool tb, const XdlArgs &a, int waves, hipStream_t s) {
+  if (a.ntasks <= 0) return hipSuccess;
+  if (a.zdrop) { // Z-drop codes: the one-side pass
+    if (tb) return hipErrorInvalidValue;
+    if (a.window == 128 && a.lps == 8) return launch_lanes<8, 16, false, true>(a, waves, s);
+    if (a.window == 64 && a.lps == 4) return launch_lanes<4, 16, false, true>(a, waves, s);
+    return hipErrorInvalidValue;
+  }
+  if (a.window != 64) return hipErrorInvalidValue;
+  switch (a.lps) {
+  case 4: return tb ? launch_lanes<4, 16, true, false>(a, waves, s) : launch_lanes<4, 16, false, false>(a, waves, s);
+  case 8: return tb ? launch_lanes<8, 8, true, false>(a, waves, s) : launch_lanes<8, 8, false, false>(a, waves, s);
+  case 16: return tb ? launch_lanes<16, 4, true, false>(a, waves, s) : launch_lanes<16, 4, false, false>(a, waves, s);
+  default: return hipErrorInvalidValue;
+  }
 }
 
 } // namespace alnk

@@ -53,7 +53,9 @@ struct LaunchDesc {
   int32_t lds_bnd;
   int32_t lds_prof;
   int sides = 1; // X-drop: extension sides per wavefront (16: the persistent lanes kernel)
-  int grid = 0;  // X-drop lanes kernel: wavefronts of the persistent grid
+  int lps = 4;     // X-drop lanes kernel: lanes a side
+  int window = 64; // and cells of a side's window
+  int grid = 0;    // and wavefronts of the persistent grid
   int waves = 1; // full matrix: wavefronts per pair (strip pipeline)
   int max_n = 0; // largest reference length of the launch
   int32_t lds_f = 0;  // search: LDS bytes of one furthest-row array
@@ -91,7 +93,7 @@ struct aln_plan {
   // X-drop with CIGAR on the sixteen-sides kernel (codes 32 B per antidiagonal);
   // pairs that outgrow its window go to the one-side pass with codes (queue 2)
   bool xtb_lanes = false;
-  int xtb_grid = 0;
+  int xtb_grid = 0, xtb_lps = 4;
   bool xdrop = false;
   int32_t n_strip_tb = 0, first_diag_tb = 0, n_diag_tb = 0; // walk ranges
   int32_t first_band_tb = 0, n_band_tb = 0;
