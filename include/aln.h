@@ -211,7 +211,9 @@ typedef struct {
                              thresholds 25, 40, 60, 80 it was timed with)    */
   double strip_ms[7];     /* candidates 0, 2, 4, 8, 16, 24, 32                */
   double xdrop_ms[4];     /* candidates 4x1, 4x16, 8x1, 8x4 (rows x sides)    */
-  int32_t band_kernel;    /* static bands: 0 (by band width), 1 (antidiagonal
+  int32_t band_kernel;    /* static bands: 0 (by band width and batch), 1
+                             (rolling row blocks where a narrow band and 16
+                             pairs or more allow them, else antidiagonal
                              windows), strips with 4 rows per lane and one (2)
                              or four (3) wavefronts per pair, or with 2 rows
                              per lane and one (4) or four (5); pairs the strip
@@ -256,12 +258,14 @@ aln_status aln_plan_create(aln_ctx *ctx, int32_t scoring_id,
 /* One kernel launch of a plan's fill (re-runs that depend on device results
  * -- widening, int32 re-runs -- and the walks are not listed). */
 typedef struct {
-  char family[24];  /* "sw16", "strip_i32", "diag_band", "band_strip",
+  char family[24];  /* "sw16", "strip_i32", "roll_i32", "diag_band",
+                       "band_strip", "band_roll", "zdrop_lanes",
                        "xdrop_lanes", "xdrop_lanes_tb", "xdrop_group", "xdrop",
                        "xdrop_tb", "zdrop", "zdrop_tb", "search",
                        "search_affine", "fold"                               */
   int32_t tile;     /* rows or window per lane (fold: triangle row stride)   */
   int32_t sides;    /* X-drop: sides per wavefront; sw16: 2 pairs per lane;
+                       rolling blocks: pairs per wavefront;
                        strips, band strips: wavefronts per pair; fold: bytes
                        per element                                           */
   int32_t first;    /* its tasks in the plan's task list                     */

@@ -38,6 +38,7 @@ namespace {
 // Rows per lane for the strip kernel: fewest padded cells plus a per-step
 // overhead of about eight cells per lane.
 int choose_strip_rows(int32_t M, int32_t N) {
+  if (M <= 512) return 8; // one strip: the fewest rows
   static const int cand[] = {8, 16, 24, 32};
   int best = 16;
   double best_cost = 1e300;
@@ -241,6 +242,33 @@ aln_status aln_set_scoring(aln_ctx *ctx, const aln_scoring *sc, int32_t *scoring
 }
 
 } // extern "C"
+
+// Batches smaller than this keep the antidiagonal kernel for bands below 256
+// diagonals (and one-strip pairs their own launch): the documented choice for a
+// handful of pairs.  From it on, strips take about a third of its time a row.
+constexpr int32_t kStripBandPairs = 4;
+// Pairs from which rolling blocks are used.
+constexpr int32_t kRollPairs = 16;
+
+// Rolling blocks for a band: rows a block and lanes a pair, 0 where none fits.
+// Two rows a block take fewest instructions a row (78, four 112) and so the
+// least time for a pair alone; on 16 lanes four pairs share them, which a band
+// of up to 15 cells either side allows.  Four rows on 16 lanes allow twice
+// that, once the pairs outnumber two wavefronts a SIMD.
+static void roll_shape(const aln_ctx *ctx, int64_t n, int32_t M, int32_t N, int32_t w, int *rows,
+                       int *lanes) {
+  *rows = *lanes = 0;
+  const bool many = n > 2LL * 4 * ctx->cus;
+  static const int shapes[4][2] = {{2, 16}, {4, 16}, {2, 64}, {4, 64}};
+  for (const auto &sh : shapes) {
+    if (sh[0] == 4 && sh[1] == 16 && !many) continue;
+    if (alnk::roll_fits(M, N, w, sh[0], sh[1])) {
+      *rows = sh[0];
+      *lanes = sh[1];
+      return;
+    }
+  }
+}
 
 // Lanes a side for n X-drop sides of a 64-cell window.  Four lanes of sixteen
 // cells take the fewest instructions a cell (240 a step for sixteen sides, 150
@@ -592,8 +620,48 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     int kind;
     int rows;
     double cost;
-    int waves = 1; // full matrix / band strips: wavefronts per pair (strip pipeline)
+    int waves = 1; // full matrix / band strips: wavefronts per pair (strip pipeline);
+                   // rolling blocks: lanes per pair
     int ring = 0;  // band strips: columns of the LDS boundary ring
+    bool full = false; // rolling blocks: full matrix
+  };
+  // Launch order: by kernel and tile, each longest first, equal ones by pair
+  // (a sort of 16-byte keys: a plan of 100 000 pairs is sorted on every batch).
+  auto cls_of = [](const Item &it) {
+    return ((it.kind * 128 + it.waves) * 64 + it.rows) * 2 + (it.full ? 1 : 0);
+  };
+  std::vector<int32_t> order; // of items
+  auto sort_items = [&](const std::vector<Item> &v) {
+    struct Key {
+      double cost;
+      int32_t cls, at;
+    };
+    std::vector<Key> keys(v.size());
+    for (size_t k = 0; k < v.size(); ++k) keys[k] = Key{v[k].cost, cls_of(v[k]), (int32_t)k};
+    std::sort(keys.begin(), keys.end(), [](const Key &x, const Key &y) {
+      if (x.cls != y.cls) return x.cls < y.cls;
+      if (x.cost != y.cost) return x.cost > y.cost;
+      return x.at < y.at;
+    });
+    order.resize(v.size());
+    for (size_t k = 0; k < v.size(); ++k) order[k] = keys[k].at;
+  };
+  // by class again, the order inside each kept
+  auto regroup = [&](const std::vector<Item> &v) {
+    std::vector<int32_t> classes;
+    for (const Item &it : v)
+      if (classes.empty() ||
+          (classes.back() != cls_of(it) &&
+           std::find(classes.begin(), classes.end(), cls_of(it)) == classes.end()))
+        classes.push_back(cls_of(it));
+    if (classes.size() < 2) return;
+    std::sort(classes.begin(), classes.end());
+    std::vector<int32_t> out;
+    out.reserve(v.size());
+    for (int32_t c : classes)
+      for (int32_t k : order)
+        if (cls_of(v[(size_t)k]) == c) out.push_back(k);
+    order.swap(out);
   };
   std::vector<Item> items;
   items.reserve(n);
@@ -715,6 +783,122 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
       }
     }
   }
+  // The choice so far decides which batches are refused (strips whose rows or
+  // profiles outgrow LDS) and the order of the CIGAR slots, whichever kernel
+  // below takes a pair over: both stay what they were.
+  {
+    struct Group {
+      int32_t rows, waves, n;
+      bool multi;
+    };
+    std::vector<Group> groups;
+    for (const Item &it : items) {
+      if (it.kind != K_STRIP) continue;
+      size_t g = 0;
+      while (g < groups.size() && (groups[g].rows != it.rows || groups[g].waves != it.waves)) ++g;
+      if (g == groups.size()) groups.push_back(Group{it.rows, it.waves, 0, false});
+      groups[g].n = std::max(groups[g].n, pl->rlen[it.pair]);
+      groups[g].multi = groups[g].multi || pl->qlen[it.pair] > 64 * it.rows;
+    }
+    for (const Group &g : groups) {
+      const int bnd = g.multi ? (int)align_up((uint64_t)(g.n + 1) * 8, 16) : 0;
+      const int prof = small ? 0 : (int)align_up((uint64_t)hs.alphabet * 64 * g.rows, 16);
+      if (alnk::strip_lds_bytes(g.waves, bnd, prof, g.n) > 160 * 1024) {
+        delete pl;
+        return fail(ctx, ALN_E_UNSUPPORTED,
+                    "full-matrix pairs with N = %d and M > %d need more LDS than a CU has", g.n,
+                    64 * g.rows);
+      }
+    }
+  }
+  sort_items(items);
+  std::vector<int64_t> slot;
+  uint64_t cg_off = 0;
+  if (p.want_cigar && !dyn_prune) {
+    slot.resize(n);
+    for (int32_t k : order) {
+      const Item &it = items[(size_t)k];
+      slot[it.pair] = (int64_t)cg_off;
+      cg_off += (uint64_t)pl->qlen[it.pair] + pl->rlen[it.pair] + 1;
+    }
+  }
+  bool moved = false; // some pair runs elsewhere
+  // Narrow bands: rolling blocks where a shape fits, else the band strips.
+  // (a tuned or forced choice of the antidiagonal kernel: rolling blocks only)
+  const int band_asked = ctx->force_band_kernel ? ctx->force_band_kernel
+                                                : (ctx->tuning.valid ? ctx->tuning.band_kernel : 0);
+  if (p.prune == ALN_BAND && band_asked <= 1 && n >= kStripBandPairs)
+    for (Item &it : items) {
+      if (it.kind != K_DIAG) continue;
+      const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
+      if (M < 1 || N < 1) continue;
+      int rows = 0, lanes = 0;
+      if (small && n >= kRollPairs) roll_shape(ctx, n, M, N, p.band_w, &rows, &lanes);
+      const int64_t ring = (alnk::band_strip_cols(M, N, p.band_w, 2) + 10 + 15) / 16 * 16;
+      if (rows) {
+        moved = true;
+        it.kind = K_ROLL;
+        it.rows = rows;
+        it.waves = lanes;
+      } else if (band_asked == 0 && p.band_w < 128 && M >= 128 && ring <= 2048 && ((M + 127LL) / 128) * ((int64_t)N + 1) + N < (1LL << 31)) {
+        moved = true;
+        it.kind = K_BAND;
+        it.rows = 2;
+        it.waves = alnk::kStripPipeWaves;
+        it.ring = (int)std::max<int64_t>(64, ring);
+      }
+    }
+  // Full matrix, no strip height tuned or forced.
+  //
+  // Up to a quarter of a pair per SIMD, where a launch takes its longest
+  // pair's time, all pairs run on the band strips, so that the batch is one
+  // launch and one walk: with 2 rows per lane (128-row strips) while no pair
+  // has more than four of them.  16 pairs of 60..300 bp with paths: 124 us
+  // against 277 with the one-strip pairs in a launch of their own.
+  //
+  // Short pairs of larger batches run as rolling blocks, four to a wavefront
+  // of 16 lanes each, where a strip of 64 lanes would be a third full: 8 192
+  // reads of 150 bp against 150..320 bp windows, LOCAL with paths, 0.30 ms
+  // against 0.88.  Up to 160 rows a pair takes no longer there than on its own
+  // wavefront, of 161..256 rows (16 a lane) twice as long, so those only past
+  // two pairs a SIMD.  One launch, its rows a lane by the longest query, until
+  // eight pairs a SIMD; from there on by each pair's, and beside longer pairs.
+  if (srows == 0) {
+    int64_t n_full = 0;
+    int32_t fullM = 0, fullN = 0;
+    auto whole = [&](const Item &it) {
+      return it.kind == K_STRIP ||
+             (it.kind == K_BAND && pl->strip_band_w >= std::max(pl->qlen[it.pair], pl->rlen[it.pair]));
+    };
+    for (const Item &it : items)
+      if (whole(it)) {
+        ++n_full;
+        fullM = std::max(fullM, pl->qlen[it.pair]);
+        fullN = std::max(fullN, pl->rlen[it.pair]);
+      }
+    const int64_t simds = 4LL * ctx->cus;
+    const bool few = n >= kStripBandPairs && n_full * 4 <= simds && fullN <= 2038;
+    const bool split = n_full > 8 * simds;
+    for (Item &it : items) {
+      const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
+      if (!whole(it) || M < 1 || N < 1) continue;
+      if (few) {
+        moved = true;
+        it.kind = K_BAND;
+        it.rows = fullM <= 512 ? 2 : 4;
+        it.waves = alnk::kStripPipeWaves;
+        it.ring = (int)std::max<int64_t>(64, ((int64_t)N + 10 + 15) / 16 * 16);
+      } else if (it.kind == K_STRIP && small && n_full >= kRollPairs && N < 65536 && M <= 256 &&
+                 (split || fullM <= 160 || (fullM <= 256 && n_full > 2 * simds))) {
+        const int32_t top = split ? M : fullM;
+        moved = true;
+        it.kind = K_ROLL;
+        it.full = true;
+        it.rows = top <= 128 ? 8 : (top <= 160 ? 10 : 16);
+        it.waves = 16;
+      }
+    }
+  }
   // X-drop without traceback under match / mismatch scoring on a small
   // alphabet runs on the lanes kernel (4 to 16 sides per wavefront) when its
   // arithmetic fits: offset-frame scores in one byte, the out-of-range
@@ -728,27 +912,23 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
       hs.mismatch - 2 * hs.gap_extend >= -128 && maxM <= 65535 && maxN <= 65535 &&
       ((int64_t)maxM + maxN) * (1 - hs.gap_extend + std::max(hs.match, 0)) < (1LL << 23);
   const bool lanes_ok = lanes_fit && !p.want_cigar;
-  std::stable_sort(items.begin(), items.end(), [](const Item &a, const Item &b) {
-    if (a.kind != b.kind) return a.kind < b.kind;
-    if (a.waves != b.waves) return a.waves < b.waves;
-    if (a.rows != b.rows) return a.rows < b.rows;
-    return a.cost > b.cost;
-  });
-  uint64_t tb_off = 0, cg_off = 0;
+  if (moved) regroup(items); // longest first by the first choice's cost
+  uint64_t tb_off = 0;
+  auto at = [&](size_t k) -> const Item & { return items[(size_t)order[k]]; };
   for (size_t k = 0; k < items.size();) {
     size_t e = k;
     int32_t grpN = 0, grpRing = 0;
     bool multi = false;
-    while (e < items.size() && items[e].kind == items[k].kind && items[e].rows == items[k].rows &&
-           items[e].waves == items[k].waves) {
-      grpN = std::max(grpN, pl->rlen[items[e].pair]);
-      grpRing = std::max(grpRing, items[e].ring);
-      if (items[e].kind == K_STRIP && pl->qlen[items[e].pair] > 64 * items[e].rows) multi = true;
+    while (e < items.size() && at(e).kind == at(k).kind && at(e).rows == at(k).rows &&
+           at(e).waves == at(k).waves && at(e).full == at(k).full) {
+      grpN = std::max(grpN, pl->rlen[at(e).pair]);
+      grpRing = std::max(grpRing, at(e).ring);
+      if (at(e).kind == K_STRIP && pl->qlen[at(e).pair] > 64 * at(e).rows) multi = true;
       ++e;
     }
     LaunchDesc L{};
-    L.kind = items[k].kind;
-    L.rows = items[k].rows;
+    L.kind = at(k).kind;
+    L.rows = at(k).rows;
     L.mode = p.mode;
     if (L.kind == K_DIAG && dyn_prune) {
       // Z-drop takes the 64-cell window only when tuned: its regions often
@@ -774,7 +954,8 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     L.small = small;
     L.first = (int32_t)pl->tasks.size();
     L.count = (int32_t)(e - k);
-    L.waves = items[k].waves;
+    L.waves = at(k).waves;
+    L.full = at(k).full;
     if (L.kind == K_BAND) {
       L.lds_bnd = grpRing * 8;
       L.lds_prof = small ? 0 : (int32_t)align_up((uint64_t)hs.alphabet * 64 * L.rows, 16);
@@ -784,15 +965,9 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
       L.lds_bnd = multi ? (int32_t)align_up((uint64_t)(grpN + 1) * 8, 16) : 0;
       L.lds_prof = small ? 0 : (int32_t)align_up((uint64_t)hs.alphabet * 64 * L.rows, 16);
       L.max_n = grpN;
-      if (alnk::strip_lds_bytes(L.waves, L.lds_bnd, L.lds_prof, L.max_n) > 160 * 1024) {
-        delete pl;
-        return fail(ctx, ALN_E_UNSUPPORTED,
-                    "full-matrix pairs with N = %d and M > %d need more LDS than a CU has", grpN,
-                    64 * L.rows);
-      }
     }
     for (size_t q = k; q < e; ++q) {
-      const int32_t i = items[q].pair;
+      const int32_t i = at(q).pair;
       const int32_t M = pl->qlen[i], N = pl->rlen[i];
       PairTask t;
       memset(&t, 0, sizeof t);
@@ -809,15 +984,18 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
           bytes = (uint64_t)ns * 64ULL *
                   (uint64_t)alnk::band_code_steps(M, N, pl->strip_band_w, L.rows) *
                   (uint64_t)(L.rows / 2);
+        } else if (L.kind == K_ROLL) {
+          bytes = (uint64_t)((M + L.rows - 1) / L.rows) *
+                  (uint64_t)alnk::roll_code_steps(M, N, L.full ? 1 << 28 : p.band_w, L.rows) *
+                  (uint64_t)(L.rows / 2);
         } else {
           const uint64_t nk = (uint64_t)M + N + 1;
           bytes = (nk + 63) / 64 * 64 * 4 + ((uint64_t)(M + N) / 2 + 1) * 64 * 8;
         }
         t.tb_off = (int64_t)tb_off;
         tb_off += align_up(bytes);
-        t.cigar_off = (int64_t)cg_off;
+        t.cigar_off = slot[i];
         t.cigar_cap = M + N + 1;
-        cg_off += (uint64_t)(M + N + 1);
       }
       pl->tasks.push_back(t);
     }
@@ -878,6 +1056,10 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
       if (L.kind == K_BAND) {
         if (pl->n_band_tb == 0) pl->first_band_tb = L.first;
         pl->n_band_tb += L.count;
+      }
+      if (L.kind == K_ROLL) {
+        if (pl->n_roll_tb == 0) pl->first_roll_tb = L.first;
+        pl->n_roll_tb += L.count;
       }
     }
   }
@@ -1084,6 +1266,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     sa.lds_prof = L.lds_prof;
     sa.waves = 1;
     sa.max_n = 0;
+    sa.roll_lanes = sa.roll_full = 0;
     HIP_TRY(ctx, timed_launch(ctx, "strip_i32_rerun", st, [&] {
               return alnk::launch_strip(L.rows, L.mode, false, L.small, sa, st);
             }));
@@ -1231,11 +1414,15 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     sa.max_n = L.max_n;
     sa.band_w = plan->strip_band_w;
     sa.ring_cols = L.lds_bnd / 8;
-    if (L.kind == K_BAND) {
+    sa.roll_lanes = L.kind == K_ROLL ? L.waves : 0;
+    sa.roll_full = L.full ? 1 : 0;
+    if (L.kind == K_ROLL) sa.band_w = L.full ? 1 << 28 : plan->p.band_w;
+    const char *const bfam = L.kind == K_ROLL ? (L.full ? "roll_i32" : "band_roll") : "band_strip";
+    if (L.kind == K_BAND || L.kind == K_ROLL) {
       if (!per_pair) {
         sa.tasks = dtasks + L.first;
         sa.ntasks = L.count;
-        HIP_TRY(ctx, timed_launch(ctx, "band_strip", st, [&] {
+        HIP_TRY(ctx, timed_launch(ctx, bfam, st, [&] {
                   return alnk::launch_band_strip(L.rows, L.mode, L.tb, L.small, sa, st);
                 }));
       } else {
@@ -1303,7 +1490,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
       wa.tasks = tasks;
       wa.ntasks = nt;
       wa.layout = layout;
-      wa.band_w = layout == 2 ? plan->strip_band_w : plan->p.band_w;
+      wa.band_w = layout >= 2 ? plan->strip_band_w : plan->p.band_w;
       return layout == 1 ? alnk::launch_walk_diag(wa, st) : alnk::launch_walk(layout, wa, st);
     };
     if (!per_pair) {
@@ -1314,12 +1501,17 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
       HIP_TRY(ctx, timed_launch(ctx, "walk", st, [&] {
                 return walk(2, dtasks + plan->first_band_tb, plan->n_band_tb);
               }));
+      HIP_TRY(ctx, timed_launch(ctx, "walk", st, [&] {
+                return walk(3, dtasks + plan->first_roll_tb, plan->n_roll_tb);
+              }));
     } else {
       for (int32_t k = 0; k < plan->n_strip_tb; ++k) HIP_TRY(ctx, walk(0, dtasks + k, 1));
       for (int32_t k = 0; k < plan->n_diag_tb; ++k)
         HIP_TRY(ctx, walk(1, dtasks + plan->first_diag_tb + k, 1));
       for (int32_t k = 0; k < plan->n_band_tb; ++k)
         HIP_TRY(ctx, walk(2, dtasks + plan->first_band_tb + k, 1));
+      for (int32_t k = 0; k < plan->n_roll_tb; ++k)
+        HIP_TRY(ctx, walk(3, dtasks + plan->first_roll_tb + k, 1));
     }
     if (plan->xtb_lanes) { // the pairs the one-side pass recomputed, in its layout
       wa.diag_stride = 2;
@@ -1456,6 +1648,7 @@ int64_t aln_plan_describe(const aln_plan *plan, aln_launch_info *launches, int32
       const char *fam = "strip_i32";
       if (L.kind == K_SEARCH) fam = L.pen_x > 0 ? "search_affine" : "search";
       if (L.kind == K_BAND) fam = "band_strip";
+      if (L.kind == K_ROLL) fam = L.full ? "roll_i32" : "band_roll";
       if (L.kind == K_DIAG) {
         if (plan->p.prune == ALN_BAND) fam = "diag_band";
         else if (plan->p.prune == ALN_ZDROP)
@@ -1463,7 +1656,8 @@ int64_t aln_plan_describe(const aln_plan *plan, aln_launch_info *launches, int32
         else fam = L.sides == 16 ? "xdrop_lanes" : (L.sides == 4 ? "xdrop_group" : "xdrop");
       }
       add_launch(fam, L.rows,
-                 (L.kind == K_STRIP || L.kind == K_BAND) ? L.waves : (L.sides == 16 ? 64 / L.lps : L.sides), L.first,
+                 (L.kind == K_STRIP || L.kind == K_BAND) ? L.waves
+                 : L.kind == K_ROLL ? 64 / L.waves : (L.sides == 16 ? 64 / L.lps : L.sides), L.first,
                  L.count);
       pair_tasks(id, L.first, L.count);
     }

@@ -64,6 +64,8 @@ struct StripArgs {
   int32_t max_n;      // pipeline: largest N of the launch (reference codes in LDS)
   int32_t band_w;     // static band on strips: half-width w (band kernel only)
   int32_t ring_cols;  // band kernel: columns of one LDS boundary ring (power of two)
+  int32_t roll_lanes; // rolling blocks (kernels_roll.hip): lanes a pair, 16 or 64 (0: strips)
+  int32_t roll_full;  // 1: full matrix of one block a lane, 0: static band
 };
 
 // Wavefronts per pair of the full-matrix strip pipeline: four (4 rows per
@@ -127,6 +129,25 @@ inline size_t band_lds_bytes(int G, int ring_cols, int lds_prof) {
   return G == 1 ? 4 * slot : G * slot + (size_t)kStripCtrWords * G * sizeof(int);
 }
 
+// Rolling blocks (kernels_roll.hip): R rows a block, LG lanes a pair.
+// Codes: a window per block, as the band strips' but aligned to 8 steps (16
+// where 8 steps' codes are no multiple of 16 bytes).
+__host__ __device__ constexpr int roll_code_align(int R) { return R % 4 ? 16 : 8; }
+__host__ __device__ inline int roll_code_steps(int32_t M, int32_t N, int32_t w, int R) {
+  const int64_t al = roll_code_align(R);
+  int64_t span = 2 * (int64_t)w + 2 + ((int64_t)(R - 1) * N) / M;
+  if (span > N) span = N;
+  return (int)((span + 2 * (al - 1)) / al * al);
+}
+// Whether a lane has left a block (at most 16 steps after its last in-band
+// step) before its next block's first in-band step, and no block after the
+// first LG starts on column 0.
+inline bool roll_fits(int32_t M, int32_t N, int32_t w, int R, int LG) {
+  if (M < 1 || N < 1 || w >= (1 << 20)) return false;
+  const int64_t cols = (((int64_t)LG * R - R + 1) * N) / M; // from a last row to the next block's first
+  return LG + cols - 2 * (int64_t)w >= 16 && ((int64_t)LG * R * N) / M > w + 1;
+}
+
 // Traceback region of one side of the sixteen-sides X-drop kernel, nb =
 // ceil((M + N + 1) / 64) blocks of 64 antidiagonals: from byte 0 one byte per
 // antidiagonal (its first and last stored 8-cell group, and the window
@@ -142,7 +163,7 @@ struct WalkArgs {
   const PairTask *tasks;
   int32_t ntasks;
   int32_t mode;
-  int32_t layout;     // 0: strip layout, 1: diagonal layout, 2: band strips
+  int32_t layout;     // 0: strip layout, 1: diagonal layout, 2: band strips, 3: rolling blocks
   int32_t diag_stride; // diagonal layout: code bytes per lane and antidiagonal
                        // pair (8: bands; 2: X-drop / Z-drop, 4 diagonals per lane;
                        // 1: the sixteen-sides X-drop kernel's packed 8-cell groups)
@@ -296,9 +317,10 @@ hipError_t launch_validate(const ValidateArgs &a, hipStream_t s);
 hipError_t launch_strip(int rows, int mode, bool tb, bool small_alphabet,
                         const StripArgs &a, hipStream_t s);
 // static band on strips, 2 or 4 rows per lane; a.waves wavefronts per pair
-// (1 or kStripPipeWaves)
+// (1 or kStripPipeWaves), or on rolling blocks (a.roll_lanes)
 hipError_t launch_band_strip(int rows, int mode, bool tb, bool small_alphabet, const StripArgs &a,
                              hipStream_t s);
+hipError_t launch_roll(int rows, int mode, bool tb, const StripArgs &a, hipStream_t s);
 hipError_t launch_walk(int layout, const WalkArgs &a, hipStream_t s);
 hipError_t launch_sw16(int rows, const Sw16Args &a, hipStream_t s);
 hipError_t launch_diag(int rows, int mode, int prune, bool tb, const DiagArgs &a, hipStream_t s);

@@ -1041,6 +1041,7 @@ static hipError_t launch_band_g(int mode, bool tb, bool small, const StripArgs &
 hipError_t launch_band_strip(int rows, int mode, bool tb, bool small_alphabet, const StripArgs &a,
                              hipStream_t s) {
   if (a.ntasks <= 0) return hipSuccess;
+  if (a.roll_lanes) return small_alphabet ? launch_roll(rows, mode, tb, a, s) : hipErrorInvalidValue;
   if (a.ring_cols < 64 || a.ring_cols > 2048 || a.ring_cols % 16 != 0) return hipErrorInvalidValue;
   if (rows != 2 && rows != 4) return hipErrorInvalidValue;
   if (a.waves == kStripPipeWaves)

@@ -97,14 +97,19 @@ struct WaveCigar {
 // before in the same strip), and a run also ends at the first cell outside
 // them; the next iteration makes that cell's block resident.
 //
-// BAND: the static-band strips (columns jlo_s .. jhi_s of strip s, step t =
+// LAY 2: the static-band strips (columns jlo_s .. jhi_s of strip s, step t =
 // j - jlo_s + lane) with lane-major code windows: lane l of strip s keeps Lw
 // steps from u_l (a multiple of 16 bytes) at ((s*64 + l)*Lw + t - u_l)*(R/2).  A
 // block is TBK steps of every lane (8 KB, 128 bytes a lane), read from each
 // lane's window (zeros outside it); the window starts of the walk's strip sit
 // in LDS for the reads.
-template <bool BAND>
+//
+// LAY 3: rolling blocks (kernels_roll.hip), walked as band strips of 64 blocks:
+// the same windows with steps t = j + block, counted in a strip from the last
+// multiple of 128 at or before its first.
+template <int LAY>
 __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
+  constexpr bool BAND = LAY >= 2, ROLL = LAY == 3;
   // band strips: 8 KB blocks, so that a launch of thousands of walks stays
   // resident at once
   constexpr int BLK = BAND ? kBlockBytes / 2 : kBlockBytes;
@@ -133,19 +138,25 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
   const int R = uni(tk.rows), HB = R / 2;
   const int invR = (65536 + R - 1) / R; // v / R = (v * invR) >> 16 for 0 <= v < 64
   // log2 of the block's steps (a lane's share of a block: BLK / 64 bytes;
-  // band strips: 128 bytes, 128 steps at 2 rows per lane, 64 at 4)
-  const int LTB = BAND ? (R <= 2 ? 7 : 6) : (R <= 4 ? 7 : (R <= 8 ? 6 : (R <= 16 ? 5 : 4)));
+  // band strips: at most 128 bytes, 128 steps at 2 rows per lane, 64 at 4)
+  const int LTB = BAND ? (R <= 2 ? 7 : (R <= 4 ? 6 : (R <= 8 ? 5 : 4)))
+                       : (R <= 4 ? 7 : (R <= 8 ? 6 : (R <= 16 ? 5 : 4)));
   const int TBK = 1 << LTB;
   const int HS = 64 * R;
   const int bw = a.band_w;
   // steps of a strip (BAND: an upper bound over the strips)
-  const int T = BAND ? (int)band_strip_cols(M, N, bw, R) + 63 : N + 63;
+  const int T = BAND ? (int)band_strip_cols(M, N, bw, R) + 63 + (ROLL ? 127 : 0) : N + 63;
   const int NTB = (T + TBK - 1) >> LTB;
-  const int Lw = BAND ? band_code_steps(M, N, bw, R) : 0;
+  const int Lw = ROLL ? roll_code_steps(M, N, bw, R) : (BAND ? band_code_steps(M, N, bw, R) : 0);
+  const int al = ROLL ? roll_code_align(R) : band_code_align(R); // steps a window start is a multiple of
+  const int nparts = (TBK * HB) >> 4; // BAND: 16-byte parts of a lane's share of a block
   const bool local = a.mode == ALN_LOCAL;
   const uint8_t *codes0 = reinterpret_cast<const uint8_t *>(codes4[0]);
-  // first column of strip s
-  auto strip_jlo = [&](int s) { return BAND ? max(1, band_centre((int64_t)s * HS + 1, M, N) - bw) : 1; };
+  // the column of lane 0 at step 0 of strip s
+  auto strip_jlo = [&](int s) {
+    const int jlo = BAND ? max(1, band_centre((int64_t)s * HS + 1, M, N) - bw) : 1;
+    return ROLL ? ((jlo + 64 * s) & ~127) - 64 * s : jlo;
+  };
   int cjlo = 1; // first column of the resident strip
 
   // block cache: slots hold (cs, cb) and (cs, cb - 1); `pre` holds (cs, cb - 2)
@@ -158,10 +169,11 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
 #pragma unroll
       for (int m = 0; m < PRE; ++m) {
         const int u = lane + 64 * m;
-        const int l = u / PRE;
-        const int tp = b * TBK - ustart[l] + (u % PRE) * (16 / HB);
-        pre[m] = (tp >= 0 && tp < Lw)
-                     ? *reinterpret_cast<const uint4 *>(sb + ((size_t)l * Lw + tp) * HB)
+        const int l = u / PRE, part = u % PRE;
+        // (window starts are multiples of 16 bytes from the block's start)
+        const int bp = (b * TBK - ustart[l]) * HB + 16 * part;
+        pre[m] = (bp >= 0 && bp < Lw * HB && (!ROLL || part < nparts))
+                     ? *reinterpret_cast<const uint4 *>(sb + (size_t)l * Lw * HB + bp)
                      : make_uint4(0u, 0u, 0u, 0u);
       }
     } else {
@@ -182,8 +194,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
     if (!BAND) return;
     const int jlo = strip_jlo(s);
     const int itop = s * HS + lane * R + 1;
-    const int u = itop <= M ? (max(1, band_centre(itop, M, N) - bw) - jlo + lane) & ~(band_code_align(R) - 1)
-                            : (1 << 30);
+    const int u = itop <= M ? (max(1, band_centre(itop, M, N) - bw) - jlo + lane) & ~(al - 1) : (1 << 24);
     __syncthreads();
     ustart[lane] = u;
     __syncthreads();
@@ -268,7 +279,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
       // first clear), E opened, F opened
       const int st = t - (b << LTB);
       const uint32_t wd = reinterpret_cast<const uint32_t *>(codes0)[
-          (slot * BLK + l2 * (TBK * HB)) / 4 + (st >> 3) * R + r2];
+          (slot * BLK + l2 * (BLK / 64)) / 4 + (st >> 3) * R + r2];
       const int nib = (int)(wd >> (28 - 4 * (st & 7))) & 15;
       const int b0 = nib >> 3, b1 = (nib >> 2) & 1;
       const int hs = b0 ? (b1 ? 2 : 1) : ((local && b1) ? 3 : 0);
@@ -767,8 +778,9 @@ __global__ __launch_bounds__(64) void walk_diag_wave(WalkArgs a) {
 
 hipError_t launch_walk(int layout, const WalkArgs &a, hipStream_t s) {
   if (a.ntasks <= 0) return hipSuccess;
-  if (layout == 2) hipLaunchKernelGGL(walk_strip_wave<true>, dim3(a.ntasks), dim3(64), 0, s, a);
-  else hipLaunchKernelGGL(walk_strip_wave<false>, dim3(a.ntasks), dim3(64), 0, s, a);
+  if (layout == 3) hipLaunchKernelGGL(walk_strip_wave<3>, dim3(a.ntasks), dim3(64), 0, s, a);
+  else if (layout == 2) hipLaunchKernelGGL(walk_strip_wave<2>, dim3(a.ntasks), dim3(64), 0, s, a);
+  else hipLaunchKernelGGL(walk_strip_wave<0>, dim3(a.ntasks), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 

@@ -40,7 +40,7 @@ struct aln_ctx {
 
 namespace alnrt {
 
-enum Kind { K_STRIP = 0, K_SW16 = 1, K_RERUN = 2, K_DIAG = 3, K_SEARCH = 4, K_BAND = 5 };
+enum Kind { K_STRIP = 0, K_SW16 = 1, K_RERUN = 2, K_DIAG = 3, K_SEARCH = 4, K_BAND = 5, K_ROLL = 6 };
 
 struct LaunchDesc {
   int kind;
@@ -56,7 +56,8 @@ struct LaunchDesc {
   int lps = 4;     // X-drop lanes kernel: lanes a side
   int window = 64; // and cells of a side's window
   int grid = 0;    // and wavefronts of the persistent grid
-  int waves = 1; // full matrix: wavefronts per pair (strip pipeline)
+  int waves = 1; // full matrix: wavefronts per pair (strip pipeline); rolling blocks: lanes per pair
+  bool full = false; // rolling blocks: full matrix (one block a lane)
   int max_n = 0; // largest reference length of the launch
   int32_t lds_f = 0;  // search: LDS bytes of one furthest-row array
   int32_t pen_x = 0, pen_o = 0, pen_e = 0, ring_h = 0, ring_e = 0; // gap-affine SEARCH
@@ -97,6 +98,7 @@ struct aln_plan {
   bool xdrop = false;
   int32_t n_strip_tb = 0, first_diag_tb = 0, n_diag_tb = 0; // walk ranges
   int32_t first_band_tb = 0, n_band_tb = 0;
+  int32_t first_roll_tb = 0, n_roll_tb = 0;
   // band strips' half-width: the band's, or for full-matrix pairs on band
   // strips a width past every pair's (the band then covers the matrix)
   int32_t strip_band_w = 0;
