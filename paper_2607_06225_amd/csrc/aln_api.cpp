@@ -367,6 +367,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     maxM = std::max(maxM, pl->qlen[i]);
     maxN = std::max(maxN, pl->rlen[i]);
   }
+  pl->max_m = maxM;
   // score-major search: one workgroup per pair, longest first, both
   // sequences and the furthest-row arrays in LDS.  Unit edit costs: four
   // wavefronts share a pair when two rows fit in LDS, else one wavefront
@@ -1058,6 +1059,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
         pl->n_band_tb += L.count;
       }
       if (L.kind == K_ROLL) {
+        pl->roll_full_tb = pl->roll_full_tb || L.full;
         if (pl->n_roll_tb == 0) pl->first_roll_tb = L.first;
         pl->n_roll_tb += L.count;
       }
@@ -1165,6 +1167,20 @@ aln_status alnrt::plan_alloc_staging(aln_plan *pl) {
 }
 
 extern "C" {
+
+// Wavefronts a pair for the walks of n pairs of up to rows rows (band
+// layouts).  A walk is a serial chain, so more wavefronts shorten the launch until
+// they no longer fit the chip at once (16 a CU); each share costs up to half its
+// rows again for its guess.  Measured, 16 / 8 / 4 / 1 wavefronts in ms: 384
+// pairs of 10..100 kbp 4.2 / 5.6 / 9.6 / 15.9; 1 000 of them 8.9 / 9.1 / 9.9 /
+// 16.7; 2 048 of 1..9 kbp 1.14 / 0.82 / 0.70 / 1.20; 256 of 1 kbp 0.073 / 0.078 /
+// 0.099 / 0.147; 700 of 0.5 kbp 0.138 / 0.103 / 0.083 / 0.103.
+static int walk_shares(const aln_ctx *ctx, int64_t n, int32_t rows) {
+  const int64_t simds = 4LL * ctx->cus;
+  const int by_n = n * 2 <= simds ? 16 : (n <= simds ? 8 : (n <= 4 * simds ? 4 : 1));
+  const int by_rows = rows >= 128 * 16 ? 16 : (rows >= 128 * 7 ? 8 : (rows >= 128 * 4 ? 4 : 1));
+  return std::min(by_n, by_rows);
+}
 
 static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, void *d_ws,
                            aln_result *d_res, uint32_t *d_cigar, hipStream_t st, bool per_pair) {
@@ -1479,6 +1495,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     wa.b = bp;
     wa.mode = plan->p.mode;
     wa.layout = 0;
+    wa.shares = 1;
     wa.diag_stride = plan->xtb_lanes ? 1 : (plan->xtb_count > 0 ? 2 : 8);
     wa.dyn_ntasks = nullptr;
     wa.band_w = plan->p.band_w;
@@ -1491,6 +1508,9 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
       wa.ntasks = nt;
       wa.layout = layout;
       wa.band_w = layout >= 2 ? plan->strip_band_w : plan->p.band_w;
+      // (LOCAL paths start at no row known; full-matrix rolling blocks are short)
+      const bool one = layout < 2 || plan->p.mode == ALN_LOCAL || (layout == 3 && plan->roll_full_tb);
+      wa.shares = one ? 1 : walk_shares(ctx, nt, plan->max_m);
       return layout == 1 ? alnk::launch_walk_diag(wa, st) : alnk::launch_walk(layout, wa, st);
     };
     if (!per_pair) {

@@ -168,7 +168,9 @@ struct WalkArgs {
                        // pair (8: bands; 2: X-drop / Z-drop, 4 diagonals per lane;
                        // 1: the sixteen-sides X-drop kernel's packed 8-cell groups)
   const int32_t *dyn_ntasks; // device-side task count (a re-run queue), or null
-  int32_t band_w;            // layout 2: band half-width
+  int32_t band_w;            // layouts 2, 3: band half-width
+  int32_t shares;            // layouts 2, 3: wavefronts a pair (1, 4, 8, 16; more than
+                             // one: GLOBAL or EXTEND, at most 4 rows a lane)
   const DevScoring *sc;
   const uint8_t *tb;
   aln_result *res;

@@ -28,23 +28,57 @@ constexpr int kBlockBytes = 16384;  // one LDS code block
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 constexpr int kPre = kBlockBytes / 16 / 64; // uint4 per lane per block
 constexpr int kLook = 32;                   // cells a walk step looks ahead
+constexpr int kShareRows = 96;              // fewest rows of a wavefront's share of a walk
+constexpr int kLeadRows = 256;              // most rows a guess starts below its share
 
 __device__ __forceinline__ int ctz64(unsigned long long v) { return v ? __ffsll((long long)v) - 1 : 64; }
 
-// Run-length CIGAR written backwards from the end of the pair's slot.  The
-// state is wave-uniform; lane 0 stores.
-struct WaveCigar {
+// LDS dependences within one wavefront: its own LDS operations stay in order,
+// so only the compiler has to keep them so (several wavefronts of a workgroup
+// walk on their own, and meet at barriers of their own).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Run-length CIGAR written backwards from the end of the pair's slot: the e-th
+// word flushed goes to out[cap - 1 - e].  The state is wave-uniform; lane 0
+// stores.  A segment of a path whose place in the slot is not known yet keeps
+// its words in an LDS buffer (16 bits: runs below 4 096), or only counts them.
+constexpr int kSegWords = 512;
+template <bool BUF> struct WaveCigar {
   uint32_t *out;
-  int w, cur, run;
+  int cap;
+  int cur, run; // the pending word (cur < 0: none)
+  int e;        // words flushed
+  int first;    // first op of the path (-1: none yet)
   bool overflow;
+  uint16_t *buf; // null: to the slot
+  bool lost;     // the buffer does not hold every word
+  __device__ void put(int at, int len, int op) { // any lane
+    if (BUF && buf) {
+      if (at < kSegWords) buf[at] = (uint16_t)((len << 4) | op);
+    } else if (at < cap) {
+      out[cap - 1 - at] = ((uint32_t)len << 4) | (uint32_t)op;
+    }
+  }
   __device__ void flush(int lane) {
     if (cur < 0) return;
-    if (w > 0) {
-      --w;
-      if (lane == 0) out[w] = ((uint32_t)run << 4) | (uint32_t)cur;
-    } else {
-      overflow = true;
+    if (BUF && buf) lost = lost || e >= kSegWords || run >= 4096;
+    else if (e >= cap) overflow = true;
+    if (lane == 0) put(e, run, cur);
+    ++e;
+  }
+  __device__ void add(int op, int n, int lane) {
+    if (n <= 0) return;
+    if (op == cur) {
+      run += n;
+      return;
     }
+    flush(lane);
+    cur = op;
+    run = n;
+    if (BUF && first < 0) first = op;
   }
   // The '=' / 'X' ops of a diagonal run of L <= kLook cells, first step of
   // the walk first (bit p of mm: cell p mismatches), all at once: the same
@@ -58,21 +92,19 @@ struct WaveCigar {
     const int last = 31 - __builtin_clz(starts);
     const int op0 = (mm & 1u) ? ALN_OP_X : ALN_OP_EQ;
     const bool merge = cur == op0;
+    if (BUF && first < 0) first = op0;
     if (!merge) flush(lane); // the pending word ends here (nothing if none)
     if (lane < L && lane != last && ((starts >> lane) & 1u)) {
       const int r = __builtin_popcount(starts & ((1u << lane) - 1u)); // sub-runs before
       const uint64_t after = (uint64_t)starts >> (lane + 1);          // non-zero: not last
       int len = __builtin_ctzll(after) + 1;
       if (r == 0 && merge) len += run;
-      const int idx = w - 1 - r;
-      const int op = ((mm >> lane) & 1u) ? ALN_OP_X : ALN_OP_EQ;
-      if (idx >= 0) out[idx] = ((uint32_t)len << 4) | (uint32_t)op;
+      put(e + r, len, ((mm >> lane) & 1u) ? ALN_OP_X : ALN_OP_EQ);
     }
-    if (w - (K - 1) < 0) {
-      overflow = true;
-      w = 0;
-    } else {
-      w -= K - 1;
+    if (K > 1) {
+      if (BUF && buf) lost = lost || e + K - 1 > kSegWords || (merge && run >= 4096 - 32);
+      else if (e + K - 1 > cap) overflow = true;
+      e += K - 1;
     }
     const int len_last = L - last + ((K == 1 && merge) ? run : 0);
     cur = ((mm >> last) & 1u) ? ALN_OP_X : ALN_OP_EQ;
@@ -107,17 +139,47 @@ struct WaveCigar {
 // LAY 3: rolling blocks (kernels_roll.hip), walked as band strips of 64 blocks:
 // the same windows with steps t = j + block, counted in a strip from the last
 // multiple of 128 at or before its first.
-template <int LAY>
-__global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
+//
+// Several wavefronts a pair (S > 1; GLOBAL and EXTEND, band layouts).  The walk is
+// a serial chain, about 1.3 us a run of the path, and the longest pair's sets the
+// launch's time, so S wavefronts take a share of the rows each.  All but the
+// last start from a guess, a cell some rows below their share on the line from
+// (0, 0) to the end cell: paths from near-by cells soon meet, so where the guess's
+// path enters the share is most often where the pair's path does.  Each share
+// is walked from there into an LDS buffer; a share whose entry is not the exit
+// of the share below is walked again from that exit, until all agree (the
+// bottom one is right from the start, so after S rounds at most).  Then the
+// words go to their places, or, where a buffer could not hold a share's words,
+// the share is walked once more, into the slot.  The path, and the words, are
+// those of one walk.  384 pairs of 10..100 kbp, w = 256: 4.2 ms on sixteen
+// wavefronts against 16.6 on one; 256 pairs of 1 kbp: 75 us against 140.
+template <int LAY, int S>
+__global__ __launch_bounds__(64 * S) void walk_strip_wave(WalkArgs a) {
   constexpr bool BAND = LAY >= 2, ROLL = LAY == 3;
+  static_assert(S == 1 || BAND, "shares are walked in the band layouts");
   // band strips: 8 KB blocks, so that a launch of thousands of walks stays
-  // resident at once
-  constexpr int BLK = BAND ? kBlockBytes / 2 : kBlockBytes;
+  // resident at once; 4 KB with several wavefronts a pair
+  constexpr int BLK = S > 1 ? kBlockBytes / 4 : (BAND ? kBlockBytes / 2 : kBlockBytes);
   constexpr int PRE = BLK / 16 / 64;
-  __shared__ __align__(16) uint4 codes4[2][BLK / 16];
-  __shared__ uint8_t qwin[256], rwin[256];
-  __shared__ int ustart[64];
-  const int lane = threadIdx.x;
+  struct WaveLds {
+    uint4 codes[2][BLK / 16];
+    uint8_t qwin[256], rwin[256];
+    int ustart[64];
+    uint16_t words[S > 1 ? kSegWords : 1];
+  };
+  struct Share { // of the path's rows: entry and exit cell and state, words
+    int in_i, in_j, in_s;
+    int out_i, out_j, out_s;
+    int words, first, cur, run, lost, bad;
+  };
+  __shared__ __align__(16) WaveLds lds[S];
+  __shared__ Share share[S];
+  __shared__ int again;
+  const int lane = threadIdx.x & 63;
+  const int wave = S > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  auto &codes4 = lds[wave].codes;
+  uint8_t *const qwin = lds[wave].qwin, *const rwin = lds[wave].rwin;
+  int *const ustart = lds[wave].ustart;
   const int task = blockIdx.x;
   if (task >= a.ntasks) return;
   const PairTask tk = a.tasks[task];
@@ -126,7 +188,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
   const int status = uni(res->status);
   const int i_end = uni(res->q_end), j_end = uni(res->r_end);
   __syncthreads();
-  if (lane == 0) {
+  if (threadIdx.x == 0) {
     res->cigar_off = tk.cigar_off;
     res->cigar_len = 0;
   }
@@ -139,7 +201,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
   const int invR = (65536 + R - 1) / R; // v / R = (v * invR) >> 16 for 0 <= v < 64
   // log2 of the block's steps (a lane's share of a block: BLK / 64 bytes;
   // band strips: at most 128 bytes, 128 steps at 2 rows per lane, 64 at 4)
-  const int LTB = BAND ? (R <= 2 ? 7 : (R <= 4 ? 6 : (R <= 8 ? 5 : 4)))
+  const int LTB = BAND ? (R <= 2 ? 7 : (R <= 4 ? 6 : (R <= 8 ? 5 : 4))) - (S > 1 ? 1 : 0)
                        : (R <= 4 ? 7 : (R <= 8 ? 6 : (R <= 16 ? 5 : 4)));
   const int TBK = 1 << LTB;
   const int HS = 64 * R;
@@ -153,7 +215,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
   const bool local = a.mode == ALN_LOCAL;
   const uint8_t *codes0 = reinterpret_cast<const uint8_t *>(codes4[0]);
   // the column of lane 0 at step 0 of strip s
-  auto strip_jlo = [&](int s) {
+  auto strip_jlo = [&](int s) __attribute__((always_inline)) {
     const int jlo = BAND ? max(1, band_centre((int64_t)s * HS + 1, M, N) - bw) : 1;
     return ROLL ? ((jlo + 64 * s) & ~127) - 64 * s : jlo;
   };
@@ -162,7 +224,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
   // block cache: slots hold (cs, cb) and (cs, cb - 1); `pre` holds (cs, cb - 2)
   uint4 pre[PRE];
   int pre_key = -1, cs = -1, cb = -1;
-  auto fetch = [&](int s, int b) {
+  auto fetch = [&](int s, int b) __attribute__((always_inline)) {
     if (BAND) {
       // lane segment l = u / (PRE) of the block, 16-byte part u % PRE of it
       const uint8_t *sb = tb + (size_t)s * 64 * (size_t)Lw * HB;
@@ -190,56 +252,53 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
     pre_key = s * NTB + b;
   };
   // BAND: window starts of strip s's lanes, and its first column
-  auto enter_strip = [&](int s) {
+  auto enter_strip = [&](int s) __attribute__((always_inline)) {
     if (!BAND) return;
     const int jlo = strip_jlo(s);
     const int itop = s * HS + lane * R + 1;
     const int u = itop <= M ? (max(1, band_centre(itop, M, N) - bw) - jlo + lane) & ~(al - 1) : (1 << 24);
-    __syncthreads();
+    wave_sync();
     ustart[lane] = u;
-    __syncthreads();
+    wave_sync();
     cjlo = jlo;
   };
-  auto install = [&](int key) {
-    __syncthreads();
+  auto install = [&](int key) __attribute__((always_inline)) {
+    wave_sync();
 #pragma unroll
     for (int m = 0; m < PRE; ++m) codes4[key & 1][lane + 64 * m] = pre[m];
-    __syncthreads();
+    wave_sync();
   };
-  auto make_resident = [&](int s, int b) {
+  auto make_resident = [&](int s, int b) __attribute__((always_inline)) {
     if (s == cs && b == cb) return;
-    const int key = s * NTB + b;
-    if (s == cs && b == cb - 1) { // the common step: one block older
-      if (b >= 1) {
-        if (pre_key != key - 1) fetch(s, b - 1);
-        install(key - 1);
-      }
-    } else { // first use, or a new strip
-      if (s != cs) enter_strip(s);
-      fetch(s, b);
-      install(key);
-      if (b >= 1) {
-        fetch(s, b - 1);
-        install(key - 1);
-      }
+    // the common step: one block older, which `pre` holds; else (first use, or a
+    // new strip) both blocks.  Then the next older one into `pre`.
+    int x = s == cs && b == cb - 1 ? b - 1 : b;
+    if (s != cs) enter_strip(s);
+    for (; x >= max(b - 2, 0); --x) {
+      if (pre_key != s * NTB + x) fetch(s, x);
+      if (x >= b - 1) install(s * NTB + x);
     }
     cs = s;
     cb = b;
-    if (b >= 2) fetch(s, b - 2);
   };
-  // position of row i (while i >= 1): strip rs, lane rl, row rr; rjlo the
-  // first column of strip rs
-  int i = i_end, j = j_end;
-  int rs = 0, rl = 0, rr = 0;
-  if (i >= 1) {
-    const int within = (i - 1) % (64 * R);
-    rs = (i - 1) / (64 * R);
-    rl = within / R;
-    rr = within - rl * R;
-  }
-  int rjlo = uni(strip_jlo(rs));
+  // the walk's cell; position of row i (while i >= 1): strip rs, lane rl, row
+  // rr; rjlo the first column of strip rs
+  int i = 0, j = 0, state = 0;
+  int rs = 0, rl = 0, rr = 0, rjlo = 1;
+  auto stand = [&](int i0, int j0, int s0) __attribute__((always_inline)) {
+    i = i0;
+    j = j0;
+    state = s0;
+    if (i >= 1) {
+      const int within = (i - 1) % (64 * R);
+      rs = (i - 1) / (64 * R);
+      rl = within / R;
+      rr = within - rl * R;
+    }
+    rjlo = uni(strip_jlo(rs));
+  };
   // position of row i - m, 0 <= m <= 32 (one strip boundary at most)
-  auto rowpos = [&](int m, int &s2, int &l2, int &r2) {
+  auto rowpos = [&](int m, int &s2, int &l2, int &r2) __attribute__((always_inline)) {
     const int x = rr - m;
     s2 = rs;
     l2 = rl;
@@ -254,7 +313,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
       }
     }
   };
-  auto up_by = [&](int n) {
+  auto up_by = [&](int n) __attribute__((always_inline)) {
     int s2, l2, r2;
     rowpos(n, s2, l2, r2);
     if (BAND && s2 != rs) rjlo = uni(strip_jlo(s2));
@@ -265,7 +324,7 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
   };
   // code of the cell at (strip s2, lane l2, row r2, column jj), or -1 when
   // its block is not resident
-  auto code_at = [&](int s2, int l2, int r2, int jj) -> int {
+  auto code_at = [&](int s2, int l2, int r2, int jj) __attribute__((always_inline)) -> int {
     const int t = jj - cjlo + l2;
     const int b = t >> LTB;
     if (s2 != cs || t < 0 || b > cb || b < cb - 1) return -1;
@@ -289,139 +348,284 @@ __global__ __launch_bounds__(64) void walk_strip_wave(WalkArgs a) {
     return (codes0[byte] >> ((r2 & 1) * 4)) & 15;
   };
   int qbase = 1 << 30, rbase = 1 << 30;
-  auto cover = [&](const uint8_t *src, int len, uint8_t *win, int &base, int lo, int hi) {
+  auto cover = [&](const uint8_t *src, int len, uint8_t *win, int &base, int lo, int hi) __attribute__((always_inline)) {
     if (lo >= base && hi < base + 256) return;
     base = max(0, hi - 255);
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int pidx = base + lane * 4 + t;
       win[lane * 4 + t] = pidx < len ? src[pidx] : 0;
     }
-    __syncthreads();
+    wave_sync();
   };
 
-  WaveCigar cw{a.cigar + tk.cigar_off, tk.cigar_cap, -1, 0, false};
-  auto emit_n = [&](int op, int n) {
-    if (n <= 0) return;
-    if (op == cw.cur) {
-      cw.run += n;
-      return;
-    }
-    cw.flush(lane);
-    cw.cur = op;
-    cw.run = n;
-  };
-  int state = 0;
-  bool bad = false;
   const unsigned long long look_mask = (1ull << kLook) - 1;
-  for (int guard = 2 * (i_end + j_end) + 2; guard > 0 && !bad; --guard) {
-    if ((state == 1 && j < 1) || (state == 2 && i < 1) || i < 0 || j < 0) {
-      bad = true;
-      break;
-    }
-    if (state == 0) {
-      if (i == 0 && j == 0) break;
-      if (local && (i == 0 || j == 0)) break;
-      if (i == 0) { emit_n(ALN_OP_D, j); j = 0; continue; }
-      if (j == 0) { emit_n(ALN_OP_I, i); i = 0; continue; }
-      make_resident(rs, (j - rjlo + rl) >> LTB);
-      cover(Qs, M, qwin, qbase, max(0, i - 1 - kLook), i - 1);
-      cover(Rs, N, rwin, rbase, max(0, j - 1 - kLook), j - 1);
-      // lanes m < kLook: the cell m steps up the diagonal
-      const int m = lane;
-      const int ii = i - m, jj = j - m;
-      int c = -1;
-      bool neq = false; // the cell's letters differ (read with its code: one LDS wait)
-      if (m < kLook && ii >= 1 && jj >= 1) {
-        int s2, l2, r2;
-        rowpos(m, s2, l2, r2);
-        c = code_at(s2, l2, r2, jj);
-        neq = qwin[ii - 1 - qbase] != rwin[jj - 1 - rbase];
+  bool bad = false;
+  // S > 1: a guess's path that has left the strip's steps
+  auto off_band = [&]() __attribute__((always_inline)) {
+    return S > 1 && (unsigned)((j - rjlo + rl) >> LTB) >= (unsigned)NTB;
+  };
+  // walks from the cell it stands on until row `stop` (0: to the path's start)
+  auto walk = [&](auto &cw, const int stop) __attribute__((always_inline)) {
+    bad = false;
+    for (int guard = 2 * (i + j) + 2; guard > 0 && !bad; --guard) {
+      if (S > 1 && i <= stop && stop > 0) break; // the next share's
+      if ((state == 1 && j < 1) || (state == 2 && i < 1) || i < 0 || j < 0) {
+        bad = true;
+        break;
       }
-      const bool diag = c >= 0 && (c & 3) == 0;
-      const int L = min(ctz64(~__ballot(diag) & look_mask), kLook); // diagonal run length
-      if (L == 0) {
-        const int hs0 = uni(c) & 3; // lane 0: the walk's own cell, always resident
-        if (local && hs0 == 3) break;
-        state = hs0; // 1: E, 2: F
-        continue;
-      }
-      // '=' / 'X' of the run, first step of the walk first
-      cw.emit_diag_run((uint32_t)(__ballot(neq) & ((1ull << L) - 1)), L, lane);
-      up_by(L);
-      j -= L;
-      // the cell that ended the run is read already: take its move now
-      // instead of in a step of its own
-      // (and a gap of one, whose opening bit is in that same code)
-      const int cL = __builtin_amdgcn_readlane(c, L); // -1: not read (L = kLook, edge, block)
-      if (cL >= 0) {
-        const int hs = cL & 3;
-        if (local && hs == 3) break;
-        if (hs == 1 && (cL & 4)) { // E(i, j) opened from H(i, j-1)
-          emit_n(ALN_OP_D, 1);
-          j -= 1;
-        } else if (hs == 2 && (cL & 8)) { // F(i, j) opened from H(i-1, j)
-          emit_n(ALN_OP_I, 1);
-          up_by(1);
-        } else {
-          state = hs; // 1: E, 2: F
+      if (state == 0) {
+        if (i == 0 && j == 0) break;
+        if (local && (i == 0 || j == 0)) break;
+        // (selects: two stores of 0 would be merged into one through a pointer,
+        // and i and j kept in memory)
+        if (i == 0 || j == 0) {
+          const bool top = i == 0;
+          cw.add(top ? ALN_OP_D : ALN_OP_I, top ? j : i - stop, lane);
+          i = top ? 0 : stop;
+          j = top ? 0 : j;
+          continue;
         }
       }
-    } else if (state == 1) {
-      // D moves: E(i, j-m) opened from H(i, j-m-1) per the code of (i, j-m)
+      if (off_band()) { bad = true; break; }
       make_resident(rs, (j - rjlo + rl) >> LTB);
-      const int jj = j - lane;
-      const bool in = lane < kLook && jj >= 1;
-      const int c = in ? code_at(rs, rl, rr, jj) : -1;
-      const unsigned long long om = __ballot(c >= 0 && (c & 4)) & look_mask;
-      const unsigned long long stop = __ballot(in && c < 0) & look_mask; // not resident
-      const int first_open = ctz64(om), first_stop = ctz64(stop);
-      if (first_open < first_stop && first_open < kLook) {
-        emit_n(ALN_OP_D, first_open + 1);
-        j -= first_open + 1;
-        state = 0;
+      if (state == 0) {
+        cover(Qs, M, qwin, qbase, max(0, i - 1 - kLook), i - 1);
+        cover(Rs, N, rwin, rbase, max(0, j - 1 - kLook), j - 1);
+        // lanes m < kLook: the cell m steps up the diagonal
+        const int m = lane;
+        const int ii = i - m, jj = j - m;
+        int c = -1;
+        bool neq = false; // the cell's letters differ (read with its code: one LDS wait)
+        if (m < kLook && ii >= 1 && jj >= 1) {
+          int s2, l2, r2;
+          rowpos(m, s2, l2, r2);
+          c = code_at(s2, l2, r2, jj);
+          neq = qwin[ii - 1 - qbase] != rwin[jj - 1 - rbase];
+        }
+        const bool diag = c >= 0 && (c & 3) == 0;
+        const int run = min(ctz64(~__ballot(diag) & look_mask), kLook); // diagonal run length
+        const int L = S > 1 ? min(run, i - stop) : run;                  // (a share ends at its row)
+        if (L == 0) {
+          const int hs0 = uni(c) & 3; // lane 0: the walk's own cell, always resident
+          if (local && hs0 == 3) break;
+          if (hs0 == 3) { bad = true; break; } // no path here (a guess)
+          state = hs0; // 1: E, 2: F
+          continue;
+        }
+        // '=' / 'X' of the run, first step of the walk first
+        cw.emit_diag_run((uint32_t)(__ballot(neq) & ((1ull << L) - 1)), L, lane);
+        up_by(L);
+        j -= L;
+        // the cell that ended the run is read already: take its move now
+        // instead of in a step of its own
+        // (and a gap of one, whose opening bit is in that same code)
+        const int cL = __builtin_amdgcn_readlane(c, L); // -1: not read (L = kLook, edge, block)
+        // (S > 1: not on a share's last row, nor where the run was cut there)
+        if (cL >= 0 && (S == 1 || stop == 0 || i > stop)) {
+          const int hs = cL & 3;
+          if (local && hs == 3) break;
+          if (hs == 1 && (cL & 4)) { // E(i, j) opened from H(i, j-1)
+            cw.add(ALN_OP_D, 1, lane);
+            j -= 1;
+          } else if (hs == 2 && (cL & 8)) { // F(i, j) opened from H(i-1, j)
+            cw.add(ALN_OP_I, 1, lane);
+            up_by(1);
+          } else {
+            state = hs; // 1: E, 2: F
+          }
+        }
+      } else if (state == 1) {
+        // D moves: E(i, j-m) opened from H(i, j-m-1) per the code of (i, j-m)
+        const int jj = j - lane;
+        const bool in = lane < kLook && jj >= 1;
+        const int c = in ? code_at(rs, rl, rr, jj) : -1;
+        const unsigned long long om = __ballot(c >= 0 && (c & 4)) & look_mask;
+        const unsigned long long gone = __ballot(in && c < 0) & look_mask; // not resident
+        const int first_open = ctz64(om), first_stop = ctz64(gone);
+        if (first_open < first_stop && first_open < kLook) {
+          cw.add(ALN_OP_D, first_open + 1, lane);
+          j -= first_open + 1;
+          state = 0;
+        } else {
+          const int n = min(first_stop, min(kLook, j));
+          if (n <= 0 || (first_stop >= kLook && j < kLook)) { bad = true; break; } // must open by column 1
+          cw.add(ALN_OP_D, n, lane);
+          j -= n;
+        }
       } else {
-        const int n = min(first_stop, min(kLook, j));
-        if (n <= 0 || (first_stop >= kLook && j < kLook)) { bad = true; break; } // must open by column 1
-        emit_n(ALN_OP_D, n);
-        j -= n;
-      }
-    } else {
-      // I moves: F(i-m, j) opened from H(i-m-1, j) per the code of (i-m, j)
-      make_resident(rs, (j - rjlo + rl) >> LTB);
-      const int ii = i - lane;
-      const bool in = lane < kLook && ii >= 1;
-      int c = -1;
-      if (in) {
-        int s2, l2, r2;
-        rowpos(lane, s2, l2, r2);
-        c = code_at(s2, l2, r2, j);
-      }
-      const unsigned long long om = __ballot(c >= 0 && (c & 8)) & look_mask;
-      const unsigned long long stop = __ballot(in && c < 0) & look_mask;
-      const int first_open = ctz64(om), first_stop = ctz64(stop);
-      if (first_open < first_stop && first_open < kLook) {
-        emit_n(ALN_OP_I, first_open + 1);
-        up_by(first_open + 1);
-        state = 0;
-      } else {
-        const int n = min(first_stop, min(kLook, i));
-        if (n <= 0 || (first_stop >= kLook && i < kLook)) { bad = true; break; } // must open by row 1
-        emit_n(ALN_OP_I, n);
-        up_by(n);
+        // I moves: F(i-m, j) opened from H(i-m-1, j) per the code of (i-m, j)
+        const int ii = i - lane;
+        const bool in = lane < kLook && ii >= 1;
+        int c = -1;
+        if (in) {
+          int s2, l2, r2;
+          rowpos(lane, s2, l2, r2);
+          c = code_at(s2, l2, r2, j);
+        }
+        const unsigned long long om = __ballot(c >= 0 && (c & 8)) & look_mask;
+        const unsigned long long gone = __ballot(in && c < 0) & look_mask;
+        const int first_open = ctz64(om), first_stop = ctz64(gone);
+        if (first_open < first_stop && first_open < kLook && (S == 1 || first_open + 1 <= i - stop)) {
+          cw.add(ALN_OP_I, first_open + 1, lane);
+          up_by(first_open + 1);
+          state = 0;
+        } else {
+          const int open = S == 1 ? kLook : min(first_open, kLook); // (a share may end before it)
+          const int n = min(min(first_stop, open), min(kLook, S == 1 ? i : i - stop));
+          if (n <= 0 || (first_stop >= kLook && open >= kLook && i < kLook && (S == 1 || stop == 0))) { bad = true; break; } // must open by row 1
+          cw.add(ALN_OP_I, n, lane);
+          up_by(n);
+        }
       }
     }
-  }
-  cw.flush(lane);
-  if (lane == 0) {
-    res->q_begin = i;
-    res->r_begin = j;
-    if (bad || cw.overflow) {
-      res->status = ALN_R_CIGAR_CAP;
-    } else {
-      res->cigar_len = tk.cigar_cap - cw.w;
-      res->cigar_off = tk.cigar_off + cw.w;
+  };
+  if constexpr (S == 1) {
+    WaveCigar<false> cw{a.cigar + tk.cigar_off, tk.cigar_cap, -1, 0, 0, -1, false, nullptr, false};
+    stand(i_end, j_end, 0);
+    walk(cw, 0);
+    cw.flush(lane);
+    if (lane == 0) {
+      res->q_begin = i;
+      res->r_begin = j;
+      if (bad || cw.overflow) {
+        res->status = ALN_R_CIGAR_CAP;
+      } else {
+        res->cigar_len = cw.e;
+        res->cigar_off = tk.cigar_off + tk.cigar_cap - cw.e;
+      }
+    }
+  } else {
+    // shares of the rows, at least kShareRows each: share k is rows row(k) + 1 ..
+    // row(k + 1)
+    const int nsh = max(1, min(S, i_end / kShareRows));
+    auto row = [&](int k) __attribute__((always_inline)) { return (int)((int64_t)i_end * k / nsh); };
+    const bool mine = wave < nsh, last = wave == nsh - 1;
+    Share &sh = share[wave];
+    uint32_t *const out = a.cigar + tk.cigar_off;
+    const int cap = tk.cigar_cap;
+    int si = i_end, sj = j_end, ss = 0; // where the next walk starts
+    int at = 0, op = -1, run = 0;       // the slot's words so far, and the one pending
+    bool fail = false;
+    // Phase 0: the guess's path down to the share's entry; 1: the share; from 2
+    // on: shares whose entry was wrong, until none is; then the words.  (One
+    // call of the walk: with several the compiler keeps its state in memory.)
+    for (int phase = 0;; ++phase) {
+      bool go = false, done = false;
+      int stop = mine ? row(wave) : 0;
+      WaveCigar<true> cw{nullptr, 0, -1, 0, 0, -1, false, lds[wave].words, false};
+      if (phase == 0) {
+        go = mine && !last;
+        if (go) {
+          stop = row(wave + 1);
+          si = min(i_end, stop + min(kLeadRows, (i_end / nsh) >> 1));
+          const int c = band_centre(si, M, N);
+          sj = (int)((int64_t)j_end * si / i_end);
+          sj = min(max(sj, max(1, c - bw)), min(N, c + bw));
+        }
+      } else if (phase == 1) {
+        go = mine && sj >= 0;
+        if (mine && lane == 0) {
+          sh.in_i = si;
+          sh.in_j = sj;
+          sh.in_s = ss;
+          sh.bad = 1;
+        }
+      } else {
+        if (threadIdx.x == 0) again = 0;
+        __syncthreads();
+        if (mine && !last) {
+          const Share &below = share[wave + 1];
+          si = uni(below.out_i);
+          sj = uni(below.out_j);
+          ss = uni(below.out_s);
+          go = !uni(below.bad) &&
+               (si != uni(sh.in_i) || sj != uni(sh.in_j) || ss != uni(sh.in_s));
+        }
+        if (go && lane == 0) again = 1;
+        __syncthreads();
+        done = !uni(again);
+        if (go && lane == 0) {
+          sh.in_i = si;
+          sh.in_j = sj;
+          sh.in_s = ss;
+        }
+        if (done) {
+          // the places of this share's words: after those of the shares below,
+          // with the word pending at their end (op, run)
+          int my_at = 0, my_op = -1, my_run = 0;
+          for (int k = nsh - 1; k >= 0; --k) {
+            const Share &x = share[k];
+            if (k == wave) {
+              my_at = at;
+              my_op = op;
+              my_run = run;
+            }
+            fail = fail || uni(x.bad);
+            const int xf = uni(x.first), xw = uni(x.words);
+            if (xf < 0) continue; // no ops
+            const bool same = op == xf;
+            at += xw + (op >= 0 && !same ? 1 : 0);
+            run = uni(x.run) + (xw == 0 && same ? run : 0);
+            op = uni(x.cur);
+          }
+          if (mine && !fail) {
+            const int n = uni(sh.words), f = uni(sh.first);
+            if (uni(sh.lost)) { // walked once more, into the slot
+              go = true;
+              si = uni(sh.in_i);
+              sj = uni(sh.in_j);
+              ss = uni(sh.in_s);
+              cw = WaveCigar<true>{out, cap, my_op, my_run, my_at, -1, false, nullptr, false};
+            } else {
+              const bool same = my_op == f;
+              if (f >= 0 && my_op >= 0 && !same) {
+                if (lane == 0 && my_at < cap)
+                  out[cap - 1 - my_at] = ((uint32_t)my_run << 4) | (uint32_t)my_op;
+                ++my_at;
+              }
+              for (int k = lane; k < n; k += 64) {
+                const uint32_t word = lds[wave].words[k] + (k == 0 && same ? (uint32_t)my_run << 4 : 0u);
+                if (my_at + k < cap) out[cap - 1 - my_at - k] = word;
+              }
+            }
+          }
+        }
+      }
+      if (go) {
+        stand(si, sj, ss);
+        walk(cw, stop);
+        if (phase == 0) { // (no entry: the exit of the share below will be it)
+          si = stop;
+          sj = bad || i != stop ? -1 : j;
+          ss = state;
+        } else if (!done && lane == 0) {
+          sh.out_i = i;
+          sh.out_j = j;
+          sh.out_s = state;
+          sh.words = cw.e;
+          sh.first = cw.first;
+          sh.cur = cw.cur;
+          sh.run = cw.run;
+          sh.lost = cw.lost;
+          sh.bad = bad;
+        }
+      }
+      if (done) break;
+      if (phase >= 1) __syncthreads();
+    }
+    if (threadIdx.x == 0) { // share 0 holds the path's start
+      if (op >= 0 && at < cap && !fail) out[cap - 1 - at] = ((uint32_t)run << 4) | (uint32_t)op;
+      if (op >= 0) ++at;
+      res->q_begin = share[0].out_i;
+      res->r_begin = share[0].out_j;
+      if (fail || at > cap) {
+        res->status = ALN_R_CIGAR_CAP;
+      } else {
+        res->cigar_len = at;
+        res->cigar_off = tk.cigar_off + cap - at;
+      }
     }
   }
 }
@@ -639,17 +843,8 @@ __global__ __launch_bounds__(64) void walk_diag_wave(WalkArgs a) {
   };
 
   int i = i_end, j = j_end;
-  WaveCigar cw{a.cigar + tk.cigar_off, tk.cigar_cap, -1, 0, false};
-  auto emit_n = [&](int op, int n) {
-    if (n <= 0) return;
-    if (op == cw.cur) {
-      cw.run += n;
-      return;
-    }
-    cw.flush(lane);
-    cw.cur = op;
-    cw.run = n;
-  };
+  WaveCigar<false> cw{a.cigar + tk.cigar_off, tk.cigar_cap, -1, 0, 0, -1, false, nullptr, false};
+  auto emit_n = [&](int op, int n) { cw.add(op, n, lane); };
   int state = 0;
   bool bad = false;
   const unsigned long long look_mask = (1ull << kLook) - 1;
@@ -770,17 +965,29 @@ __global__ __launch_bounds__(64) void walk_diag_wave(WalkArgs a) {
     if (bad || cw.overflow) {
       res->status = ALN_R_CIGAR_CAP;
     } else {
-      res->cigar_len = tk.cigar_cap - cw.w;
-      res->cigar_off = tk.cigar_off + cw.w;
+      res->cigar_len = cw.e;
+      res->cigar_off = tk.cigar_off + tk.cigar_cap - cw.e;
     }
   }
 }
 
+template <int LAY>
+static hipError_t launch_walk_shares(const WalkArgs &a, hipStream_t s) {
+  switch (a.shares) {
+  case 16: hipLaunchKernelGGL((walk_strip_wave<LAY, 16>), dim3(a.ntasks), dim3(64 * 16), 0, s, a); break;
+  case 8: hipLaunchKernelGGL((walk_strip_wave<LAY, 8>), dim3(a.ntasks), dim3(64 * 8), 0, s, a); break;
+  case 4: hipLaunchKernelGGL((walk_strip_wave<LAY, 4>), dim3(a.ntasks), dim3(64 * 4), 0, s, a); break;
+  case 1: hipLaunchKernelGGL((walk_strip_wave<LAY, 1>), dim3(a.ntasks), dim3(64), 0, s, a); break;
+  default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_walk(int layout, const WalkArgs &a, hipStream_t s) {
   if (a.ntasks <= 0) return hipSuccess;
-  if (layout == 3) hipLaunchKernelGGL(walk_strip_wave<3>, dim3(a.ntasks), dim3(64), 0, s, a);
-  else if (layout == 2) hipLaunchKernelGGL(walk_strip_wave<2>, dim3(a.ntasks), dim3(64), 0, s, a);
-  else hipLaunchKernelGGL(walk_strip_wave<0>, dim3(a.ntasks), dim3(64), 0, s, a);
+  if (layout == 3) return launch_walk_shares<3>(a, s);
+  if (layout == 2) return launch_walk_shares<2>(a, s);
+  hipLaunchKernelGGL((walk_strip_wave<0, 1>), dim3(a.ntasks), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 

@@ -78,6 +78,7 @@ struct aln_plan {
   aln_params p{};
   int32_t n = 0;
   std::vector<int32_t> qlen, rlen;
+  int32_t max_m = 0; // longest query
   std::vector<alnk::PairTask> tasks;
   std::vector<alnrt::LaunchDesc> launches;
   // packed int16 path
@@ -99,6 +100,7 @@ struct aln_plan {
   int32_t n_strip_tb = 0, first_diag_tb = 0, n_diag_tb = 0; // walk ranges
   int32_t first_band_tb = 0, n_band_tb = 0;
   int32_t first_roll_tb = 0, n_roll_tb = 0;
+  bool roll_full_tb = false; // some of those are full-matrix pairs
   // band strips' half-width: the band's, or for full-matrix pairs on band
   // strips a width past every pair's (the band then covers the matrix)
   int32_t strip_band_w = 0;
