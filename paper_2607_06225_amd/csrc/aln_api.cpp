@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <functional>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -1753,37 +1754,86 @@ aln_status aln_fold_plan_create(aln_ctx *ctx, const aln_fold_params *params, int
   pl->fold = true;
   pl->fold_p = p;
   pl->qlen.assign(len_host, len_host + n);
-  // one launch per (stride, width), the widest rows first; within a launch
-  // the longest sequence first (LPT).  Threads per workgroup so that the
-  // workgroups LDS lets share a CU hold about 16 wavefronts.
   int64_t cells = 0;
+  auto add_launch = [&](const std::vector<int32_t> &idx, int elt, int stride, int block) {
+    aln_plan::FoldLaunch L;
+    L.elt = elt;
+    L.stride = stride;
+    L.block = p.block ? p.block : block;
+    L.first = (int32_t)pl->fold_tasks.size();
+    L.count = (int32_t)idx.size();
+    L.max_n = 0;
+    for (int32_t s : idx) {
+      L.max_n = std::max(L.max_n, len_host[s]);
+      pl->fold_tasks.push_back(alnk::FoldTask{s, len_host[s]});
+      cells += (int64_t)len_host[s] * (len_host[s] - 1) / 2;
+    }
+    pl->fold_launches.push_back(L);
+  };
+  auto longer = [&](int32_t x, int32_t y) { return len_host[x] > len_host[y]; };
+  // Unpruned with byte scores (tiles), the longest sequence first (LPT): one launch of
+  // those too long for two workgroups a CU (368 nt and more), whose last round
+  // leaves CUs idle, so shorter ones follow in it as long as it does not end later
+  // (its course is followed here with the time of a workgroup alone on its CU, us);
+  // and one launch of the rest, two or more workgroups a CU.  2 048 sequences of
+  // 76..500 nt: four launches by length (LDS of 128, 256, 384, 512 nt) 1 493 us, these
+  // two 1 246, with the gaps filled 1 143; a third launch for those of which eight
+  // share a CU 1 170.  Wavefronts a workgroup, by how many share a CU: 2 048 of 500 nt
+  // 4 / 8 / 16: 3.30 / 3.16 / 3.11 ms, of 180 nt 0.24 / 0.28 / 0.57.
+  const bool tiles = p.xdrop < 0;
+  if (tiles) {
+    auto per_cu = [&](int32_t s) {
+      return lds_max / (int64_t)alnk::fold_tile_lds_bytes(len_host[s], 4);
+    };
+    auto us = [&](int32_t s) {
+      const double L = len_host[s];
+      return 0.36 * L + 1.8e-6 * L * L * L;
+    };
+    std::vector<int32_t> idx, alone, shared;
+    for (int32_t s = 0; s < n; ++s)
+      if (cls[s].elt == 1) idx.push_back(s);
+    std::stable_sort(idx.begin(), idx.end(), longer);
+    const size_t cus = (size_t)ctx->cus;
+    std::vector<double> busy; // until when each CU is, a min heap
+    auto give = [&](int32_t s) {
+      if (busy.size() < cus) {
+        busy.push_back(us(s));
+      } else {
+        std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+        busy.back() += us(s);
+      }
+      std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+      alone.push_back(s);
+    };
+    size_t k = 0;
+    for (; k < idx.size() && per_cu(idx[k]) < 2; ++k) give(idx[k]);
+    const double end = busy.empty() ? 0 : *std::max_element(busy.begin(), busy.end());
+    for (; k < idx.size(); ++k) {
+      const double from = busy.size() < cus ? 0 : busy.front();
+      if (from + us(idx[k]) <= end) give(idx[k]);
+      else shared.push_back(idx[k]);
+    }
+    for (const auto *g : {&alone, &shared}) {
+      if (g->empty()) continue;
+      const int64_t share = per_cu((*g)[0]);
+      add_launch(*g, 1, 16 * alnk::fold_tile_rows(len_host[(*g)[0]]),
+                 share >= 3 ? 256 : (share == 2 ? 512 : 1024));
+    }
+  }
+  // The other forms: one launch per (stride, width), the widest rows first;
+  // within a launch the longest sequence first.  Threads per workgroup so that the
+  // workgroups LDS lets share a CU hold about 16 wavefronts.
   for (int si = 3; si >= 0; --si) {
-    for (int elt = 2; elt >= 1; --elt) {
+    for (int elt = 2; elt >= (tiles ? 2 : 1); --elt) {
       const int stride = alnk::kFoldStrides[si];
       std::vector<int32_t> idx;
-      int32_t max_n = 0;
       for (int32_t s = 0; s < n; ++s)
-        if (cls[s].stride == stride && cls[s].elt == elt) {
-          idx.push_back(s);
-          max_n = std::max(max_n, len_host[s]);
-        }
+        if (cls[s].stride == stride && cls[s].elt == elt) idx.push_back(s);
       if (idx.empty()) continue;
-      std::stable_sort(idx.begin(), idx.end(),
-                       [&](int32_t x, int32_t y) { return len_host[x] > len_host[y]; });
-      const int64_t lds = (int64_t)alnk::fold_lds_bytes(elt, stride, max_n);
+      std::stable_sort(idx.begin(), idx.end(), longer);
+      const int64_t lds = (int64_t)alnk::fold_lds_bytes(elt, stride, len_host[idx[0]]);
       const int64_t per_cu = std::max<int64_t>(1, lds_max / std::max<int64_t>(lds, 1));
-      aln_plan::FoldLaunch L;
-      L.elt = elt;
-      L.stride = stride;
-      L.block = p.block ? p.block : (per_cu >= 4 ? 256 : (per_cu >= 2 ? 512 : 1024));
-      L.first = (int32_t)pl->fold_tasks.size();
-      L.count = (int32_t)idx.size();
-      L.max_n = max_n;
-      for (int32_t s : idx) {
-        pl->fold_tasks.push_back(alnk::FoldTask{s, len_host[s]});
-        cells += (int64_t)len_host[s] * (len_host[s] - 1) / 2;
-      }
-      pl->fold_launches.push_back(L);
+      add_launch(idx, elt, stride, per_cu >= 4 ? 256 : (per_cu >= 2 ? 512 : 1024));
     }
   }
   pl->upload_bytes = sizeof(alnk::FoldTask) * pl->fold_tasks.size();

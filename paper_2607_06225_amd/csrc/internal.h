@@ -314,6 +314,18 @@ inline size_t fold_lds_bytes(int elt_bytes, int stride, int max_n) {
          (((size_t)max_n + 15) & ~(size_t)15) + ((size_t)max_n + 4 * kFoldCtlSlots) * sizeof(int);
 }
 
+// The unpruned form with byte elements (fold_tile_kernel): 16 x 16 tiles of
+// the triangle 0 <= i <= j <= n, tile rows packed, the diagonal tiles once more, a partial
+// tile a wavefront, and the codes.
+__host__ __device__ inline int fold_tile_rows(int n) { return (n + 16) >> 4; }
+__host__ __device__ inline int fold_tile_at(int I, int J, int rows) {
+  return (I * rows - I * (I - 1) / 2 + J - I) * 256;
+}
+inline size_t fold_tile_lds_bytes(int max_n, int waves) {
+  const int rows = fold_tile_rows(max_n);
+  return (size_t)(rows * (rows + 1) / 2 + rows + waves) * 256 + 16 * rows + 32;
+}
+
 // Launchers (defined in the kernel translation units).
 hipError_t launch_validate(const ValidateArgs &a, hipStream_t s);
 hipError_t launch_strip(int rows, int mode, bool tb, bool small_alphabet,

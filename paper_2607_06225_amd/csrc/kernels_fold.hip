@@ -41,6 +41,9 @@
 // infinity).  A cell with no live term reads minus infinity too.  The result
 // is the best surviving cell: highest F, then the largest span, then the
 // smallest i.
+//
+// Unpruned sequences with byte elements take a form of their own, by tiles
+// (fold_tile_kernel).
 #include "internal.h"
 
 namespace alnk {
@@ -59,14 +62,6 @@ template <bool XD> struct FoldElt<int16_t, XD> {
   __device__ static int value(int v) { return v; }
   __device__ static int inner(int in, int s) { return in + s; } // in: stored F(i+1,j-1)
   static constexpr int kAccInit = -65536;
-};
-template <> struct FoldElt<uint8_t, false> { // every cell live: plain sums
-  static constexpr int kDead = 255;
-  __device__ static int term(int l, int r) { return l + r; }
-  __device__ static bool live(int v) { return v >= 0; }
-  __device__ static int value(int v) { return v; }
-  __device__ static int inner(int in, int s) { return in + s; }
-  static constexpr int kAccInit = -1;
 };
 template <> struct FoldElt<uint8_t, true> {
   // live values 0..253, 255 = minus infinity.  A term l + r + 1 is at most
@@ -349,26 +344,333 @@ __global__ __launch_bounds__(B) void fold_kernel(FoldArgs a) {
 }
 
 
-template <typename T, bool XD, int B, int SC>
-static hipError_t launch_fold_t(const FoldArgs &a, hipStream_t s) {
-  const size_t lds = fold_lds_bytes(sizeof(T), SC, a.max_n);
-  auto kern = fold_kernel<T, XD, B, SC>;
+// ------------------------------------------------- unpruned, byte elements
+// Every cell is live and every sum of two cells of one interval fits a byte (the
+// planner bounds the scores by 253).  With intervals half open, G(i,j) = F(i,j-1),
+// G(i,i) = 0, the recurrence is
+//   G(i,j) = max( max over i < k < j of G(i,k) + G(k,j),
+//                 G(i+1,j-1) + pair(x_i, x_{j-1}) ),
+// a (max,+) closure of an upper triangle, so it runs by 16 x 16 tiles of bytes (256
+// contiguous bytes each, tile rows packed): tile (I,J) first takes the products of
+// the tiles (I,K) and (K,J), I < K < J, and is then completed by the terms that
+// read itself and the diagonal tiles (I,I) and (J,J).  The tiles of one tile
+// diagonal are independent: 2 barriers per 16 spans.
+//
+// Product of two tiles, one wavefront: a lane holds 4 rows x 4 columns and a quarter
+// of the splits k; four k are four dwords of each operand, 16 byte splats and, per
+// row and k, one 32-bit add of four sums and byte maxima by packed 16-bit ones
+// (an odd byte is the high half of its 16 bits, whose low half only breaks
+// ties; an even one is masked out first): 80 instructions and 8 LDS reads for 4096
+// terms.  Swaps of half and quarter waves join the four quarters.  The products of
+// a tile diagonal are cut evenly over the wavefronts, in tile order: a wavefront's
+// first tile may have begun in another one, then its maxima go to a buffer
+// of its own, which the completion joins.
+//
+// Completion, 16 lanes a tile (four tiles a wavefront), lane ii = row ii, 31 steps:
+// at step d lane ii is at column jj = d - 15 + ii, so j - i is the same for all.
+// The lane keeps its row's last 15 cells, nearest first, in four dwords, meets them
+// with column jj of the diagonal tile (J,J) (kept transposed and in that order), and
+// takes from lane ii + 1 the column's cells below its own, in the same order, and
+// meets them with row ii of (I,I), fixed.  Cells not there are 0, which no term that
+// counts is below.  Nothing on the chain from step to step goes through LDS.
+//
+// What bounds it: vector instructions, 0.73 a cycle and CU at 496 nt (one workgroup
+// a CU, whose completions leave SIMDs idle) and 0.81 at 367 nt (two), about 60%
+// of them in products.  2 048 sequences: 76..500 nt 5.11 -> 1.15 ms, 400..500 nt
+// 9.30 -> 2.49, 40..127 nt 0.232 -> 0.071; 4 of 400..500 nt 1.38 -> 0.37 ms (before: a
+// cell a lane and a barrier or two each span, a term two byte reads from LDS).
+using u16x2 = unsigned short __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pk_max_u16(uint32_t x, uint32_t y) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, x),
+                                                                __builtin_bit_cast(u16x2, y)));
+}
+constexpr uint32_t kEven = 0x00ff00ffu;
+// byte maxima of two dwords
+__device__ __forceinline__ uint32_t max_u8x4(uint32_t x, uint32_t y) {
+  return (pk_max_u16(x, y) & ~kEven) | pk_max_u16(x & kEven, y & kEven);
+}
+
+// This lane's parts of one pair of tiles: four rows by four splits, four splits by four columns.
+struct FoldPair {
+  uint32_t x[4], y[4];
+  __device__ __forceinline__ void load(const uint8_t *a, const uint8_t *b) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      x[r] = *reinterpret_cast<const uint32_t *>(a + 16 * r);
+      y[r] = *reinterpret_cast<const uint32_t *>(b + 16 * r);
+    }
+  }
+  __device__ __forceinline__ void join(uint32_t (&e)[4], uint32_t (&o)[4]) const {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t s = __builtin_amdgcn_perm(x[r], x[r], 0x01010101u * k) + y[k];
+        o[r] = pk_max_u16(o[r], s);
+        e[r] = pk_max_u16(e[r], s & kEven);
+      }
+  }
+};
+
+// Products of cnt >= 1 tile pairs for one tile: a, b this lane's parts of the first two,
+// bstep tiles from b's to the next, one less each time.  Returns the lane's dword of the
+// joined tile: row 4 p + r, columns 4 q .. 4 q + 3 (p, q, and r by its quarter wave).
+__device__ __forceinline__ uint32_t fold_products(const uint8_t *a, const uint8_t *b, int bstep,
+                                                  int cnt) {
+  uint32_t e[4] = {0, 0, 0, 0}, o[4] = {0, 0, 0, 0};
+  FoldPair p0, p1;
+  p0.load(a, b);
+  for (;;) { // the next pair's reads are in flight meanwhile
+    if (cnt > 1) p1.load(a + 256, b + 256 * bstep);
+    p0.join(e, o);
+    if (cnt <= 1) break;
+    a += 512;
+    b += 256 * (2 * bstep - 1);
+    bstep -= 2;
+    if (cnt > 2) p0.load(a, b);
+    p1.join(e, o);
+    cnt -= 2;
+    if (cnt <= 0) break;
+  }
+  auto join32 = [](uint32_t u, uint32_t v) __attribute__((always_inline)) {
+    const auto t = __builtin_amdgcn_permlane32_swap(u, v, false, false);
+    return pk_max_u16(t[0], t[1]);
+  };
+  auto join16 = [](uint32_t u, uint32_t v) __attribute__((always_inline)) {
+    const auto t = __builtin_amdgcn_permlane16_swap(u, v, false, false);
+    return pk_max_u16(t[0], t[1]);
+  };
+  const uint32_t eo = join16(join32(e[0], e[1]), join32(e[2], e[3]));
+  const uint32_t oo = join16(join32(o[0], o[1]), join32(o[2], o[3]));
+  return (oo & ~kEven) | eo;
+}
+
+template <int W>
+__global__ __launch_bounds__(64 * W) void fold_tile_kernel(FoldArgs args) {
+  constexpr int B = 64 * W;
+  extern __shared__ __align__(16) uint8_t smem[];
+  const FoldTask tk = args.tasks[blockIdx.x];
+  const int n = tk.n;
+  aln_fold_result *res = args.res + tk.seq;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  // LDS: tiles | transposed diagonal tiles | the wavefronts' partial tiles | 8 x codes
+  const int NB = fold_tile_rows(n);
+  uint8_t *G = smem;
+  uint8_t *dT = G + fold_tile_rows(args.max_n) * (fold_tile_rows(args.max_n) + 1) / 2 * 256;
+  uint8_t *part = dT + fold_tile_rows(args.max_n) * 256;
+  uint8_t *xs = part + W * 256;
+  __shared__ int bad;
+  __shared__ uint32_t tab[4]; // pair scores of one base with the four
+  if (tid == 0) bad = 0;
+  if (tid < 4)
+    tab[tid] = (uint32_t)args.pair[4 * tid] | ((uint32_t)args.pair[4 * tid + 1] << 8) |
+               ((uint32_t)args.pair[4 * tid + 2] << 16) | ((uint32_t)args.pair[4 * tid + 3] << 24);
+  __syncthreads();
+  const uint8_t *src = args.x + args.off[tk.seq];
+  int mine = 0;
+  for (int p = tid; p < 16 * NB + 32; p += B) {
+    const uint8_t c = p < n ? src[p] : 0;
+    mine |= c > 3;
+    xs[p] = c << 3;
+  }
+  if (mine) atomicOr(&bad, 1);
+  // diagonal tiles and their transposes; tiles (I, I + 1) have no products
+  for (int p = tid; p < 16 * NB; p += B) {
+    const int I = p >> 4, r = 16 * (p & 15);
+    *reinterpret_cast<uint4 *>(G + fold_tile_at(I, I, NB) + r) = make_uint4(0, 0, 0, 0);
+    *reinterpret_cast<uint4 *>(dT + 256 * I + r) = make_uint4(0, 0, 0, 0);
+    if (I + 1 < NB)
+      *reinterpret_cast<uint4 *>(G + fold_tile_at(I, I + 1, NB) + r) = make_uint4(0, 0, 0, 0);
+  }
+  __syncthreads();
+  if (bad || n <= 1) {
+    if (tid == 0) {
+      res->score = 0;
+      res->i = 0;
+      res->j = 0;
+      res->full = (!bad && n == 1) ? 1 : 0;
+      res->cells = 0;
+      res->terms = 0;
+      res->status = bad ? ALN_R_BAD_SYMBOL : ALN_R_OK;
+      res->reserved = 0;
+    }
+    return;
+  }
+  const int ii = lane & 15, sub = lane >> 4;
+
+  // diagonal tiles, a cell a lane and span
+  for (int I = wave * 4 + sub; I < NB; I += W * 4) {
+    uint8_t *T = G + fold_tile_at(I, I, NB), *D = dT + 256 * I;
+    const uint8_t *xi = xs + 16 * I + ii;
+    for (int t = 2; t < 16; ++t) {
+      if (ii + t < 16) {
+        int v = T[17 * ii + t + 15]; // (ii + 1, ii + t - 1)
+        if (t - 1 > args.min_loop) v += (int)((tab[xi[0] >> 3] >> xi[t - 1]) & 255u);
+        for (int u = 1; u < t; ++u)
+          v = max(v, (int)T[17 * ii + u] + (int)D[16 * (ii + t) + t - u - 1]);
+        T[17 * ii + t] = (uint8_t)v;
+        D[16 * (ii + t) + t - 1] = (uint8_t)v;
+      }
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    }
+  }
+  __syncthreads();
+
+  for (int D = 1; D < NB; ++D) {
+    const int c = NB - D, per = D - 1, units = c * per;
+    if (per > 0) {
+      int u = wave * units / W;
+      const int u1 = (wave + 1) * units / W;
+      if (u < u1) {
+        int I = u / per, kk = u - I * per;
+        const int p = (lane >> 2) & 3, q = lane & 3;
+        const int aoff = 64 * p + 4 * sub, boff = 64 * sub + 4 * q;
+        const int r = ((sub & 1) << 1) | (sub >> 1); // the row the swaps leave here
+        const int dst = 16 * (4 * p + r) + 4 * q;
+        while (u < u1) {
+          const int cnt = min(per - kk, u1 - u), K = I + 1 + kk;
+          const uint32_t v = fold_products(G + fold_tile_at(I, K, NB) + aoff,
+                                           G + fold_tile_at(K, I + D, NB) + boff, NB - K - 1, cnt);
+          uint8_t *to = kk ? part + 256 * wave : G + fold_tile_at(I, I + D, NB);
+          *reinterpret_cast<uint32_t *>(to + dst) = v;
+          u += cnt;
+          ++I;
+          kk = 0;
+        }
+      }
+      __syncthreads();
+    }
+    for (int first = wave * 4; first < c; first += 4 * W) {
+      const int I = min(first + sub, c - 1), J = I + D; // past the last: that one again
+      uint8_t *T = G + fold_tile_at(I, J, NB) + 16 * ii;
+      if (per > 0) { // wavefronts that began inside this tile's products
+        const int from = I * per, to = from + per;
+        uint4 m = *reinterpret_cast<const uint4 *>(T);
+        bool more = false;
+        for (int w = I * W / c + 1; w < W; ++w) {
+          const int s = w * units / W;
+          if (s >= to) break;
+          if (s > from && (w + 1) * units / W > s) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(part + 256 * w + 16 * ii);
+            m.x = max_u8x4(m.x, v.x);
+            m.y = max_u8x4(m.y, v.y);
+            m.z = max_u8x4(m.z, v.z);
+            m.w = max_u8x4(m.w, v.w);
+            more = true;
+          }
+        }
+        if (more) *reinterpret_cast<uint4 *>(T) = m;
+      }
+      // row ii of (I,I) from column ii + 1 (then the next row's zeros)
+      uint32_t g[4] = {0, 0, 0, 0};
+      if (ii < 15) __builtin_memcpy(g, G + fold_tile_at(I, I, NB) + 17 * ii + 1, 16);
+      const uint8_t *dt = dT + 256 * J + 16 * (ii - 15);
+      uint8_t *cell = T + ii - 15;
+      const uint8_t *xj = xs + 16 * J + ii - 16;
+      const uint8_t *top = G + fold_tile_at(I + 1, J, NB) - 1;
+      const uint32_t tabi = tab[xs[16 * I + ii] >> 3];
+      const uint32_t left = G[fold_tile_at(I, J - 1, NB) + 16 * ii + 15];
+      uint32_t corner = 0;
+      if (D > 1) corner = G[fold_tile_at(I + 1, J - 1, NB) + 15];
+      const int paired = min(args.min_loop, 4096) + 16 - 16 * D; // pairs from the step after this one
+      uint32_t row[4] = {0, 0, 0, 0}, col[4] = {0, 0, 0, 0};
+      uint32_t in1 = left, in2 = left; // last and last but one step's cells, or the one left of the tile
+      struct Ahead {
+        uint4 dt;
+        uint32_t cell, xj, top;
+      } ah[2];
+      auto fetch = [&](int d) __attribute__((always_inline)) {
+        Ahead f;
+        f.dt = *reinterpret_cast<const uint4 *>(dt + 16 * d);
+        f.cell = cell[d];
+        f.xj = xj[d];
+        f.top = d > 0 && d < 16 ? top[d] : 0;
+        return f;
+      };
+      ah[0] = fetch(0);
+      ah[1] = fetch(1);
+#pragma unroll
+      for (int d = 0; d < 31; ++d) {
+        const Ahead f = ah[d & 1];
+        if (d + 2 < 31) ah[d & 1] = fetch(d + 2);
+        // the interval inside, plus the pair
+        uint32_t in = (uint32_t)__builtin_amdgcn_update_dpp((int)(d ? f.top : corner), (int)in2,
+                                                            0x101, 0xf, 0xf, false); // row_shl:1
+        in += __builtin_amdgcn_ubfe(tabi, f.xj, d > paired ? 8 : 0);
+        uint32_t v = max(f.cell, in);
+        const int nd = min(4, (d + 3) / 4); // dwords that can hold cells by now
+        if (nd) {
+          const uint32_t dtw[4] = {f.dt.x, f.dt.y, f.dt.z, f.dt.w};
+          uint32_t e = 0, o = 0;
+#pragma unroll
+          for (int k = 3; k >= 0; --k) // the newest cells are in the first
+            if (k < nd) {
+              const uint32_t s1 = row[k] + dtw[k], s2 = col[k] + g[k];
+              o = pk_max_u16(o, pk_max_u16(s1, s2));
+              e = pk_max_u16(e, pk_max_u16(s1 & kEven, s2 & kEven));
+            }
+          e = pk_max_u16(e, (o >> 8) & kEven);
+          v = max(max(v, e >> 16), e & 0xffffu);
+        }
+        in2 = in1;
+        in1 = v;
+        if (d < 15) {
+          const bool inside = ii >= 15 - d;
+          in1 = inside ? v : left;
+          v = inside ? v : 0u;
+          if (inside) cell[d] = (uint8_t)v;
+        } else if (d == 15 || ii <= 30 - d) {
+          cell[d] = (uint8_t)v;
+        }
+#pragma unroll
+        for (int k = 3; k > 0; --k) {
+          row[k] = __builtin_amdgcn_alignbyte(row[k], row[k - 1], 3);
+          col[k] = __builtin_amdgcn_alignbyte(col[k], col[k - 1], 3);
+        }
+        row[0] = (row[0] << 8) | v;
+        col[0] = (col[0] << 8) | v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (k <= (d >> 2)) // lane 15 takes none
+            col[k] = (uint32_t)__builtin_amdgcn_mov_dpp((int)col[k], 0x101, 0xf, 0xf, true);
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) { // every cell evaluated and kept, so the whole sequence is the best interval
+    res->score = (int)G[fold_tile_at(0, n >> 4, NB) + (n & 15)];
+    res->i = 0;
+    res->j = n - 1;
+    res->full = 1;
+    res->cells = (int64_t)n * (n - 1) / 2;
+    res->terms = (int64_t)(n - 1) * n * (n + 1) / 6;
+    res->status = ALN_R_OK;
+    res->reserved = 0;
+  }
+}
+
+template <typename K>
+static hipError_t launch_fold_lds(K kern, int block, size_t lds, const FoldArgs &a, hipStream_t s) {
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void *)kern,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3(a.ntasks), dim3(B), lds, s, a);
+  hipLaunchKernelGGL(kern, dim3(a.ntasks), dim3(block), lds, s, a);
   return hipGetLastError();
 }
 
 template <typename T, bool XD, int B>
 static hipError_t launch_fold_s(int stride, const FoldArgs &a, hipStream_t s) {
+  const size_t lds = fold_lds_bytes(sizeof(T), stride, a.max_n);
   switch (stride) {
-  case 128: return launch_fold_t<T, XD, B, 128>(a, s);
-  case 256: return launch_fold_t<T, XD, B, 256>(a, s);
-  case 384: return launch_fold_t<T, XD, B, 384>(a, s);
-  case 512: return launch_fold_t<T, XD, B, 512>(a, s);
+  case 128: return launch_fold_lds(fold_kernel<T, XD, B, 128>, B, lds, a, s);
+  case 256: return launch_fold_lds(fold_kernel<T, XD, B, 256>, B, lds, a, s);
+  case 384: return launch_fold_lds(fold_kernel<T, XD, B, 384>, B, lds, a, s);
+  case 512: return launch_fold_lds(fold_kernel<T, XD, B, 512>, B, lds, a, s);
   default: return hipErrorInvalidValue;
   }
 }
@@ -383,6 +685,16 @@ static hipError_t launch_fold_b(int block, int stride, const FoldArgs &a, hipStr
   }
 }
 
+static hipError_t launch_fold_tiles(int block, const FoldArgs &a, hipStream_t s) {
+  const size_t lds = fold_tile_lds_bytes(a.max_n, block / 64);
+  switch (block) {
+  case 256: return launch_fold_lds(fold_tile_kernel<4>, block, lds, a, s);
+  case 512: return launch_fold_lds(fold_tile_kernel<8>, block, lds, a, s);
+  case 1024: return launch_fold_lds(fold_tile_kernel<16>, block, lds, a, s);
+  default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_fold(int elt_bytes, int block, int stride, const FoldArgs &a, hipStream_t s) {
   if (a.ntasks <= 0) return hipSuccess;
   if (a.max_n + 1 > stride) return hipErrorInvalidValue;
@@ -391,8 +703,7 @@ hipError_t launch_fold(int elt_bytes, int block, int stride, const FoldArgs &a, 
     return xd ? launch_fold_b<int16_t, true>(block, stride, a, s)
               : launch_fold_b<int16_t, false>(block, stride, a, s);
   if (elt_bytes == 1)
-    return xd ? launch_fold_b<uint8_t, true>(block, stride, a, s)
-              : launch_fold_b<uint8_t, false>(block, stride, a, s);
+    return xd ? launch_fold_b<uint8_t, true>(block, stride, a, s) : launch_fold_tiles(block, a, s);
   return hipErrorInvalidValue;
 }
 

@@ -124,7 +124,7 @@ struct aln_plan {
   std::vector<alnk::FoldTask> fold_tasks;
   struct FoldLaunch {
     int elt;    // bytes per triangle element
-    int stride; // row stride of the folded triangle (elements)
+    int stride; // row stride of the folded triangle (elements), or its tiles' columns
     int block;  // threads per workgroup
     int32_t first, count, max_n;
   };
