@@ -15,6 +15,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -369,10 +370,11 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     maxN = std::max(maxN, pl->rlen[i]);
   }
   pl->max_m = maxM;
+  pl->max_n = maxN;
   // score-major search: one workgroup per pair, longest first, both
-  // sequences and the furthest-row arrays in LDS.  Unit edit costs: four
+  // sequences and the furthest-row arrays in LDS.  Unit edit costs: 1 to 8
   // wavefronts share a pair when two rows fit in LDS, else one wavefront
-  // updates a single row in place.  Gap-affine penalties: four wavefronts
+  // updates a single row in place.  Gap-affine penalties: 1 to 8 wavefronts
   // over rings of past H, E and F rows.
   if (p.prune == ALN_SEARCH) {
     std::vector<int32_t> order(n);
@@ -423,6 +425,15 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
           L.lds_fc = (int32_t)align_up((uint64_t)(2 * L.dcap + 1) * 2, 16);
         }
       }
+      // Only multiples of the penalties' common divisor are scores, so the kernel
+      // counts in it, over fewer rows (what fits and the cap above stay those of
+      // the plain penalties).
+      L.pen_g = std::gcd(L.pen_x, std::gcd(L.pen_o + L.pen_e, L.pen_e));
+      L.pen_x /= L.pen_g;
+      L.pen_o /= L.pen_g;
+      L.pen_e /= L.pen_g;
+      L.ring_h = std::max(L.pen_x, L.pen_o + L.pen_e) + 1;
+      L.ring_e = L.pen_e + 1;
     }
     for (int32_t i : order) {
       PairTask t;
@@ -1209,7 +1220,12 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   if (!plan->launches.empty() && plan->launches[0].kind == K_SEARCH) {
     const LaunchDesc &L = plan->launches[0];
     alnk::SearchArgs sa{bp,      dtasks,  L.count, d_res,    L.lds_bnd, L.lds_prof, L.lds_f,
-                        L.waves, L.pen_x, L.pen_o, L.pen_e, L.ring_h,  L.ring_e,  0, 0};
+                        L.waves, L.pen_x, L.pen_o, L.pen_e, L.ring_h,  L.ring_e,  L.pen_g, 0, 0,
+                        L.waves == 1, hsc.alphabet <= 4};
+    if (sa.two_bit) { // (the plan's sizes are those of bytes)
+      sa.lds_q = (int32_t)align_up((uint64_t)plan->max_m / 4 + 8, 16);
+      sa.lds_r = (int32_t)align_up((uint64_t)plan->max_n / 4 + 8, 16);
+    }
     // gap-affine with a diagonal cap: a capped pass, then full rows for the
     // pairs it flagged
     std::pair<const char *, alnk::SearchArgs> passes[2];
@@ -1226,6 +1242,21 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     }
     for (int ip = 0; ip < npass; ++ip) {
       alnk::SearchArgs &x = passes[ip].second;
+      // Wavefronts a pair, by how many pairs a CU holds at a time: a score's diagonals
+      // are few, and what a wavefront spends on a score whatever it has to do
+      // counts where many pairs share the CU; where few do, they wait for a
+      // score's chain.  1 / 2 / 4 / 8 wavefronts, us, edit distance: 30 000 pairs of
+      // 100..200 nt (32 and more a CU) 49 / 73 / 126 / 234, 4 096 of 2 000 (eight)
+      // 187 / 161 / 169 / 273, 1 000 of 7..8 knt (two) 1 240 / 808 / 565 / 464;
+      // gap-affine, 4 096 of 2 000 (seven) 1 684 / 1 142 / 1 047 / 1 485, 64 of
+      // 2 000 628 / 398 / 276 / 221.
+      if (!x.one_row) {
+        const int64_t rows = x.pen_x > 0 ? x.ring_h + 2 * x.ring_e : 2;
+        const int64_t lds = (int64_t)x.lds_q + x.lds_r + rows * x.lds_f;
+        const int64_t held = std::min<int64_t>(ctx->lds_per_cu / lds,
+                                               per_pair ? 1 : ((int64_t)L.count + ctx->cus - 1) / ctx->cus);
+        x.waves = held >= 16 ? 1 : held >= 8 ? 2 : held >= 3 ? 4 : 8;
+      }
       if (!per_pair) {
         HIP_TRY(ctx, timed_launch(ctx, passes[ip].first, st, [&] { return alnk::launch_search(x, st); }));
       } else {

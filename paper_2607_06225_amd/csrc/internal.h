@@ -266,9 +266,9 @@ constexpr int xdrop_lanes_waves(bool tb, bool zdrop, int lps) {
   return zdrop ? 12 : (lps == 16 ? (tb ? 16 : 24) : (lps == 8 ? 16 : (tb ? 12 : 16)));
 }
 
-// Score-major search for unit-cost edit distance: one workgroup per task,
-// of `waves` wavefronts (1: one F row in LDS; 4: two rows, the previous
-// score's and the current one's).
+// Score-major search for unit-cost edit distance: one workgroup of 1, 2, 4 or 8
+// wavefronts per task, two F rows in LDS (the previous score's and the current
+// one's); or (one_row) one wavefront and one row.
 struct SearchArgs {
   BatchPtrs b;
   const PairTask *tasks;
@@ -280,11 +280,14 @@ struct SearchArgs {
   // score rows each wavefront ring keeps: H rows for s - x and s - o - e,
   // E and F rows for s - e
   int32_t pen_x, pen_o, pen_e, ring_h, ring_e;
+  int32_t pen_g; // unit of the penalties above and of the rings' scores
   // gap-affine: dcap > 0 stores diagonals -dcap..dcap only (rows of lds_f
   // bytes); a pair whose range outgrows them is flagged ALN_F_WIDENED and
   // left to a second launch with dcap = 0 (rows of every diagonal), which
   // skips unflagged pairs (pass = 1)
   int32_t dcap, pass;
+  int32_t one_row;
+  int32_t two_bit; // at most four symbols: codes packed two bits each in LDS
 };
 
 // Nussinov folding: one workgroup per sequence (tasks in LPT order).

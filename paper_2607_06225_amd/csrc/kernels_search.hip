@@ -15,15 +15,26 @@
 //
 // One workgroup per pair, with both sequences and F (int16 per diagonal,
 // -32768 for "not reached", so rows are at most 32767) in LDS.  Two forms:
-// - search_group_kernel: four wavefronts and two F rows (previous score,
+// - search_group_kernel: 1 to 8 wavefronts and two F rows (previous score,
 //   current score), used whenever both rows fit;
 // - search_edit_kernel: one wavefront updating a single row in place, for
 //   the longest pairs.  Lanes take 64 consecutive diagonals at a time; the
 //   neighbours' old values come by DPP, the chunk's left neighbour from a
 //   register saved before the previous chunk overwrote it, and its right
 //   neighbour from LDS (not yet updated).
-// Extension compares sixteen characters per step: five aligned dword reads
-// per sequence and four byte aligns, then the first differing byte.
+// Extension compares sixteen characters per step: of at most four symbols, packed two
+// bits each, from two dwords of each sequence and a funnel shift; otherwise five aligned
+// dword reads per sequence and four byte aligns, then the first differing byte.
+// (Wide LDS reads at any alignment were slower than either: a lane at a time, they
+// kept the LDS busy 73% of the time.)
+//
+// What bounds it: instructions, half of them scalar (loop, exec mask and row
+// bookkeeping; 0.41 vector and 0.70 scalar a cycle and CU in the edit distance,
+// 0.55 and 0.77 gap-affine), then the chain of one score: rows, first
+// comparison, the path's further comparisons, barrier.  4 096 pairs of 2 000 nt at 5%:
+// edit distance 249 -> 163 us (before: codes in bytes, four wavefronts always),
+// gap-affine (4, 6, 2) 3 364 -> 959 us (and every score, not the multiples of 2);
+// 30 000 of 100..200 nt 129 -> 50 and 760 -> 157 us.
 #include "internal.h"
 
 namespace alnk {
@@ -55,7 +66,7 @@ __device__ __forceinline__ void load16(const uint8_t *buf, int off, uint64_t &lo
 
 // advance row f of diagonal d while the next characters match, up to lim
 // (sixteen characters per step: one LDS round trip and one loop test)
-__device__ __forceinline__ int extend(const uint8_t *qs, const uint8_t *rs, int f, int d, int lim) {
+__device__ __forceinline__ int extend_bytes(const uint8_t *qs, const uint8_t *rs, int f, int d, int lim) {
   while (f < lim) {
     uint64_t qa, qb, ra, rb;
     load16(qs, f, qa, qb);
@@ -68,6 +79,73 @@ __device__ __forceinline__ int extend(const uint8_t *qs, const uint8_t *rs, int 
   return f;
 }
 
+// The same with codes of two bits, sixteen a dword: two dwords of each sequence and a
+// funnel shift are sixteen characters.  (Codes past a sequence's end may agree: lim
+// stops there.)
+__device__ __forceinline__ int extend_pairs(const uint32_t *qs, const uint32_t *rs, int f, int d,
+                                            int lim) {
+  for (;;) {
+    const uint32_t *q = qs + (f >> 4), *r = rs + ((f + d) >> 4);
+    const uint32_t x = __builtin_amdgcn_alignbit(q[1], q[0], 2 * f) ^
+                       __builtin_amdgcn_alignbit(r[1], r[0], 2 * (f + d));
+    const int n = (x ? __builtin_ctz(x) : 32) >> 1;
+    f = min(f + n, lim);
+    if (n < 16 || f >= lim) return f;
+  }
+}
+template <bool PK>
+__device__ __forceinline__ int extend(const uint8_t *qs, const uint8_t *rs, int f, int d, int lim) {
+  if constexpr (PK)
+    return extend_pairs(reinterpret_cast<const uint32_t *>(qs),
+                        reinterpret_cast<const uint32_t *>(rs), f, d, lim);
+  else
+    return extend_bytes(qs, rs, f, d, lim);
+}
+
+// A sequence of len codes into LDS, four (sixteen) a thread from any address; only
+// whole words inside the sequence are read as such.  Bytes: 20 bytes of padding after it.
+__device__ __forceinline__ uint32_t word_of(const uint8_t *from, int k, int len, uint8_t pad) {
+  uint32_t v = pad * 0x01010101u;
+  if (k + 4 <= len)
+    __builtin_memcpy(&v, from + k, 4);
+  else
+    for (int b = 0; b < 4; ++b)
+      if (k + b < len) v = (v & ~(255u << (8 * b))) | ((uint32_t)from[k + b] << (8 * b));
+  return v;
+}
+template <bool PK>
+__device__ __forceinline__ void stage(uint8_t *to, const uint8_t *from, int len, uint8_t pad, int tid,
+                                      int threads) {
+  if constexpr (PK) {
+    for (int k = tid; k < (len >> 4) + 2; k += threads) {
+      uint32_t z = 0;
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const uint32_t v = word_of(from, 16 * k + 4 * g, len, 0), t = v | (v >> 6);
+        z |= ((t & 15u) | ((t >> 12) & 0xf0u)) << (8 * g);
+      }
+      reinterpret_cast<uint32_t *>(to)[k] = z;
+    }
+  } else {
+    for (int k = 4 * tid; k < len + 20; k += 4 * threads) { // the buffer is whole words
+      *reinterpret_cast<uint32_t *>(to + k) = word_of(from, k, len, pad);
+    }
+  }
+}
+
+// Entries of scores 0..S when e scores share a range of diagonals |d| <= score / e,
+// clipped to -M..N.
+__device__ __forceinline__ long long entries(int M, int N, int e, int S) {
+  const int w = S / e;
+  auto below = [](int lim, int w) -> long long { // sum of min(lim, k), k < w
+    const long long m = min(lim, w - 1);
+    return w <= 0 ? 0 : m * (m + 1) / 2 + (w - 1 - m) * lim;
+  };
+  const long long all = w + below(M, w) + below(N, w);
+  return all * e + (long long)(S - w * e + 1) * (1 + min(M, w) + min(N, w));
+}
+
+template <bool PK>
 __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int lane = threadIdx.x;
@@ -86,8 +164,8 @@ __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
   uint8_t *qs = smem;
   uint8_t *rs = smem + a.lds_q;
   int16_t *F = reinterpret_cast<int16_t *>(smem + a.lds_q + a.lds_r);
-  for (int k = lane; k < M + 20; k += 64) qs[k] = k < M ? Q[k] : 0xFE;
-  for (int k = lane; k < N + 20; k += 64) rs[k] = k < N ? Rs[k] : 0xFF;
+  stage<PK>(qs, Q, M, 0xFE, lane, 64);
+  stage<PK>(rs, Rs, N, 0xFF, lane, 64);
   for (int k = lane; k <= M + N; k += 64) F[k] = kNegF16;
   __syncthreads();
 
@@ -95,7 +173,7 @@ __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
   int s = 0, dmin = 0, dmax = 0;
   long long cells = 1;
   {
-    const int f0 = extend(qs, rs, 0, 0, min(M, N));
+    const int f0 = extend<PK>(qs, rs, 0, 0, min(M, N));
     if (lane == 0) F[M] = (int16_t)f0;
   }
   __syncthreads();
@@ -120,7 +198,7 @@ __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
       if (old + 1 <= lim) f = max(f, old + 1);     // mismatch
       if (right + 1 <= lim) f = max(f, right + 1); // insertion
       if (left <= lim) f = max(f, left);           // deletion
-      if (act && f >= 0) f = extend(qs, rs, f, d, lim);
+      if (act && f >= 0) f = extend<PK>(qs, rs, f, d, lim);
       if (act) F[d + M] = f >= 0 ? (int16_t)f : kNegF16;
     }
     done = dt >= dmin && dt <= dmax && __builtin_amdgcn_readfirstlane(fload(F, dt + M)) >= M;
@@ -133,7 +211,7 @@ __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
   }
 }
 
-// Several wavefronts per pair.  F(s-1, .) and F(s, .) live in two LDS rows
+// One to eight wavefronts per pair.  F(s-1, .) and F(s, .) live in two LDS rows
 // that swap roles every score, so a step reads only the previous row and
 // needs no carried neighbour: the active diagonals are cut into 64-diagonal
 // chunks dealt round-robin to the wavefronts, and one barrier per score
@@ -141,7 +219,7 @@ __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
 // outside the previous score's diagonals was never written (the active
 // diagonals only widen, and each row is written on every other score), so it
 // still reads "not reached".
-template <int NWV>
+template <int NWV, bool PK>
 __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x;
@@ -162,53 +240,58 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
   uint8_t *rs = smem + a.lds_q;
   int16_t *Fp = reinterpret_cast<int16_t *>(smem + a.lds_q + a.lds_r);
   int16_t *Fn = reinterpret_cast<int16_t *>(smem + a.lds_q + a.lds_r + a.lds_f);
-  for (int k = tid; k < M + 20; k += 64 * NWV) qs[k] = k < M ? Q[k] : 0xFE;
-  for (int k = tid; k < N + 20; k += 64 * NWV) rs[k] = k < N ? Rs[k] : 0xFF;
-  for (int k = tid; k <= M + N; k += 64 * NWV) {
-    Fp[k] = kNegF16;
-    Fn[k] = kNegF16;
+  stage<PK>(qs, Q, M, 0xFE, tid, 64 * NWV);
+  stage<PK>(rs, Rs, N, 0xFF, tid, 64 * NWV);
+  for (int k = 8 * tid; k < a.lds_f / 2; k += 8 * 64 * NWV) { // rows are whole 16 bytes
+    *reinterpret_cast<uint4 *>(Fp + k) = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
+    *reinterpret_cast<uint4 *>(Fn + k) = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
   }
   __syncthreads();
-  if (tid == 0) Fp[M] = (int16_t)extend(qs, rs, 0, 0, min(M, N));
+  if (tid == 0) Fp[M] = (int16_t)extend<PK>(qs, rs, 0, 0, min(M, N));
   __syncthreads();
 
   const int dt = N - M;
   int s = 0, dmin = 0, dmax = 0;
-  long long cells = 1;
-  bool done = dt == 0 && __builtin_amdgcn_readfirstlane(fload(Fp, M)) >= M;
-  while (!done && s < M + N) {
-    ++s;
-    dmin = max(dmin - 1, -M);
-    dmax = min(dmax + 1, N);
-    cells += dmax - dmin + 1;
-    for (int d0 = dmin + 64 * wave; d0 <= dmax; d0 += 64 * NWV) {
+  for (;;) {
+    // is the end cell reached at score s?  Known once score s + 1 is computed, whose
+    // reads need not wait for it.
+    const int end = fload(Fp, dt + M);
+    const int nmin = max(dmin - 1, -M), nmax = min(dmax + 1, N);
+    const bool edge = nmin == -M || nmax == N;
+    for (int d0 = nmin + 64 * wave; d0 <= nmax; d0 += 64 * NWV) {
       const int d = d0 + lane;
-      const bool act = d <= dmax;
-      int old = kNegF, left = kNegF, right = kNegF;
-      if (act) {
-        old = fload(Fp, d + M);
-        if (d > -M) left = fload(Fp, d - 1 + M);
-        if (d < N) right = fload(Fp, d + 1 + M);
+      if (d <= nmax) {
+        const int16_t *src = Fp + d + M;
+        const int old = src[0];
+        int left, right;
+        if (!edge) {
+          left = src[-1];
+          right = src[1];
+        } else {
+          left = d > -M ? src[-1] : kNegF;
+          right = d < N ? src[1] : kNegF;
+        }
+        // a row past the diagonal's end stands for the end, which was reached before:
+        // every active diagonal has a row, the furthest of s edits at most
+        const int lim = min(M, N - d);
+        const int f = min(max(left, max(old, right) + 1), lim);
+        Fn[d + M] = (int16_t)extend<PK>(qs, rs, f, d, lim);
       }
-      const int lim = min(M, N - d);
-      int f = kNegF;
-      if (old + 1 <= lim) f = max(f, old + 1);     // mismatch
-      if (right + 1 <= lim) f = max(f, right + 1); // insertion
-      if (left <= lim) f = max(f, left);           // deletion
-      if (act && f >= 0) f = extend(qs, rs, f, d, lim);
-      if (act) Fn[d + M] = f >= 0 ? (int16_t)f : kNegF16;
     }
+    if (__builtin_amdgcn_readfirstlane(end) >= M || s >= M + N) break;
     __syncthreads();
+    ++s;
+    dmin = nmin;
+    dmax = nmax;
     int16_t *t = Fp;
     Fp = Fn;
     Fn = t;
-    done = dt >= dmin && dt <= dmax && __builtin_amdgcn_readfirstlane(fload(Fp, dt + M)) >= M;
   }
   if (tid == 0) {
     res->score = -s;
     res->q_end = M;
     res->r_end = N;
-    res->cells = cells;
+    res->cells = entries(M, N, 1, s);
   }
 }
 
@@ -224,8 +307,11 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
 // diagonal it moves, so the active diagonals are |d| <= s / e, clipped to the
 // matrix.  The search stops at the first s with H(s, N - M) = M: s is the
 // smallest penalty, minus the Gotoh global score under (0, -x, -o, -e).
+// Every penalty is a multiple of g = gcd(x, o + e, e), and so is every score that is
+// reached: the search counts in units of g, and the scores between, whose rows would all
+// read "not reached", only add their diagonals to the count of entries.
 // Rows for past scores live in LDS rings (H: ring_h rows, E and F: ring_e
-// rows each, slot s mod ring size); four wavefronts share a pair as in
+// rows each, slot s mod ring size); the wavefronts share a pair as in
 // search_group_kernel, one barrier per score.  A slot's earlier scores had
 // narrower diagonal ranges, all rewritten when it is reused, so an entry
 // outside a row's range still reads "not reached".
@@ -234,7 +320,7 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
 // second launch with rows of every diagonal.  A source diagonal outside the
 // stored ones was never active (the range at an earlier score was inside
 // them), so it reads "not reached".
-template <int NWV>
+template <int NWV, bool PK>
 __global__ __launch_bounds__(64 * NWV) void search_affine_kernel(SearchArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x;
@@ -250,7 +336,7 @@ __global__ __launch_bounds__(64 * NWV) void search_affine_kernel(SearchArgs a) {
   const uint8_t *Q = a.b.q + a.b.q_off[p];
   const uint8_t *Rs = a.b.r + a.b.r_off[p];
   if (a.pass == 1 && !(__builtin_amdgcn_readfirstlane(res->flags) & ALN_F_WIDENED)) return;
-  const int X = a.pen_x, O = a.pen_o, E = a.pen_e, RH = a.ring_h, RE = a.ring_e;
+  const int X = a.pen_x, O = a.pen_o, E = a.pen_e; // in units of a.pen_g
   const bool capped = a.dcap > 0;
   const int off = capped ? a.dcap : M;             // row index of diagonal 0
   const int lo_st = capped ? max(-M, -a.dcap) : -M; // stored diagonals lo_st..hi_st
@@ -258,95 +344,93 @@ __global__ __launch_bounds__(64 * NWV) void search_affine_kernel(SearchArgs a) {
 
   uint8_t *qs = smem;
   uint8_t *rs = smem + a.lds_q;
-  uint8_t *rows = smem + a.lds_q + a.lds_r;
   const int stride = a.lds_f; // bytes per row
-  // ring slots by index (the slot of score s is s mod ring size, kept
-  // incrementally below: no division in the score loop)
-  auto hrow = [&](int k) { return reinterpret_cast<int16_t *>(rows + (size_t)k * stride); };
-  auto erow = [&](int k) { return reinterpret_cast<int16_t *>(rows + (size_t)(RH + k) * stride); };
-  auto frow = [&](int k) { return reinterpret_cast<int16_t *>(rows + (size_t)(RH + RE + k) * stride); };
-  for (int k = tid; k < M + 20; k += 64 * NWV) qs[k] = k < M ? Q[k] : 0xFE;
-  for (int k = tid; k < N + 20; k += 64 * NWV) rs[k] = k < N ? Rs[k] : 0xFF;
-  {
-    int16_t *all = reinterpret_cast<int16_t *>(rows);
-    const int n16 = (RH + 2 * RE) * (stride / 2);
-    for (int k = tid; k < n16; k += 64 * NWV) all[k] = kNegF16;
-  }
+  const int wrap_h = a.ring_h * stride, wrap_e = a.ring_e * stride;
+  uint8_t *hring = smem + a.lds_q + a.lds_r;
+  uint8_t *ering = hring + wrap_h, *fring = ering + wrap_e;
+  stage<PK>(qs, Q, M, 0xFE, tid, 64 * NWV);
+  stage<PK>(rs, Rs, N, 0xFF, tid, 64 * NWV);
+  for (int k = 16 * tid; k < wrap_h + 2 * wrap_e; k += 16 * 64 * NWV) // rows are whole 16 bytes
+    *reinterpret_cast<uint4 *>(hring + k) = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
   __syncthreads();
-  if (tid == 0) hrow(0)[off] = (int16_t)extend(qs, rs, 0, 0, min(M, N));
+  if (tid == 0) reinterpret_cast<int16_t *>(hring)[off] = (int16_t)extend<PK>(qs, rs, 0, 0, min(M, N));
   __syncthreads();
 
   const int dt = N - M;
+  const bool ends = dt >= lo_st && dt <= hi_st; // the end cell's diagonal is stored
   const int smax = 2 * O + E * (M + N); // a gap of the whole query, then one of the reference
+  // Rows by byte offset, kept incrementally: of this score, of the score before, and of
+  // s - X, s - O - E, s - E (slots not yet written read "not reached").
+  auto next = [](int o, int stride, int wrap) { return o + stride == wrap ? 0 : o + stride; };
   int s = 0;
-  int sh = 0, se = 0;  // s mod RH, s mod RE
-  int w = 0, wr = 0;   // s / E, s mod E
-  long long cells = 1;
-  bool done = dt == 0 && __builtin_amdgcn_readfirstlane(fload(hrow(0), off)) >= M;
+  int hn = 0, hx = (a.ring_h - X) * stride, ho = (a.ring_h - O - E) * stride;
+  int en = 0, ee = (a.ring_e - E) * stride;
+  int w = 0, wr = 0; // s / E, s mod E
   bool outgrown = false;
-  while (!done && s < smax) {
-    ++s;
-    sh = sh + 1 == RH ? 0 : sh + 1;
-    se = se + 1 == RE ? 0 : se + 1;
+  for (;;) {
+    // is the end cell reached at score s?  Known once score s + 1 is computed, whose
+    // reads need not wait for it.
+    int end = kNegF;
+    if (ends) end = fload(reinterpret_cast<const int16_t *>(hring + hn), dt + off);
     if (++wr == E) {
       wr = 0;
       ++w;
     }
+    hn = next(hn, stride, wrap_h);
+    hx = next(hx, stride, wrap_h);
+    ho = next(ho, stride, wrap_h);
+    en = next(en, stride, wrap_e);
+    ee = next(ee, stride, wrap_e);
     const int dmin = max(-M, -w), dmax = min(N, w);
-    if (dmin < lo_st || dmax > hi_st) { // only with capped rows (uniform)
-      outgrown = true;
-      break;
-    }
-    cells += dmax - dmin + 1;
-    const bool hx = s >= X, ho = s >= O + E, ge = s >= E;
-    // slots of s - X and s - O - E (both < RH back) and s - E (< RE back)
-    const int shx = sh - X < 0 ? sh - X + RH : sh - X;
-    const int sho = sh - O - E < 0 ? sh - O - E + RH : sh - O - E;
-    const int see = se - E < 0 ? se - E + RE : se - E;
-    const int16_t *Hx = hrow(shx);
-    const int16_t *Ho = hrow(sho);
-    const int16_t *Ee = erow(see);
-    const int16_t *Fe = frow(see);
-    int16_t *Hn = hrow(sh), *En = erow(se), *Fn = frow(se);
-    for (int d0 = dmin + 64 * wave; d0 <= dmax; d0 += 64 * NWV) {
-      const int d = d0 + lane;
-      if (d <= dmax) {
-        const int lim = min(M, N - d);
-        int ev = kNegF, fv = kNegF, hv = kNegF;
-        if (d > lo_st) { // a step right from diagonal d - 1
-          int src = kNegF;
-          if (ho) src = fload(Ho, d - 1 + off);
-          if (ge) src = max(src, fload(Ee, d - 1 + off));
-          if (src >= 0 && src <= lim) ev = src;
+    outgrown = dmin < lo_st || dmax > hi_st; // only with capped rows (uniform)
+    if (!outgrown) {
+      const int16_t *Hx = reinterpret_cast<const int16_t *>(hring + hx) + off;
+      const int16_t *Ho = reinterpret_cast<const int16_t *>(hring + ho) + off;
+      const int16_t *Ee = reinterpret_cast<const int16_t *>(ering + ee) + off;
+      const int16_t *Fe = reinterpret_cast<const int16_t *>(fring + ee) + off;
+      int16_t *Hn = reinterpret_cast<int16_t *>(hring + hn) + off;
+      int16_t *En = reinterpret_cast<int16_t *>(ering + en) + off;
+      int16_t *Fn = reinterpret_cast<int16_t *>(fring + en) + off;
+      const bool edge = dmin == lo_st || dmax == hi_st;
+      for (int d0 = dmin + 64 * wave; d0 <= dmax; d0 += 64 * NWV) {
+        const int d = d0 + lane;
+        if (d <= dmax) {
+          const int lim = min(M, N - d);
+          int ev, fv, hv = Hx[d];
+          if (!edge) {
+            ev = max(Ho[d - 1], Ee[d - 1]); // a step right from diagonal d - 1
+            fv = max(Ho[d + 1], Fe[d + 1]); // a step down from diagonal d + 1
+          } else {
+            ev = d > lo_st ? max(Ho[d - 1], Ee[d - 1]) : kNegF16;
+            fv = d < hi_st ? max(Ho[d + 1], Fe[d + 1]) : kNegF16;
+          }
+          ev = ev <= lim ? ev : kNegF;
+          fv = fv >= 0 && fv < lim ? fv + 1 : kNegF;
+          hv = hv >= 0 && hv < lim ? hv + 1 : kNegF; // a mismatch on diagonal d
+          int h = max(hv, max(ev, fv));
+          En[d] = (int16_t)ev;
+          Fn[d] = (int16_t)fv;
+          if (h >= 0) h = extend<PK>(qs, rs, h, d, lim);
+          Hn[d] = (int16_t)h;
         }
-        if (d < hi_st) { // a step down from diagonal d + 1
-          int src = kNegF;
-          if (ho) src = fload(Ho, d + 1 + off);
-          if (ge) src = max(src, fload(Fe, d + 1 + off));
-          if (src >= 0 && src + 1 <= lim) fv = src + 1;
-        }
-        if (hx) { // a mismatch on diagonal d
-          const int v = fload(Hx, d + off);
-          if (v >= 0 && v + 1 <= lim) hv = v + 1;
-        }
-        int h = max(hv, max(ev, fv));
-        if (h >= 0) h = extend(qs, rs, h, d, lim);
-        En[d + off] = ev >= 0 ? (int16_t)ev : kNegF16;
-        Fn[d + off] = fv >= 0 ? (int16_t)fv : kNegF16;
-        Hn[d + off] = h >= 0 ? (int16_t)h : kNegF16;
       }
     }
+    if (__builtin_amdgcn_readfirstlane(end) >= M || s >= smax) {
+      outgrown = false;
+      break;
+    }
+    if (outgrown) break;
     __syncthreads();
-    done = dt >= dmin && dt <= dmax && __builtin_amdgcn_readfirstlane(fload(hrow(sh), dt + off)) >= M;
+    ++s;
   }
   if (tid == 0) {
     if (outgrown) {
       res->flags |= ALN_F_WIDENED;
     } else {
-      res->score = -s;
+      res->score = -s * a.pen_g;
       res->q_end = M;
       res->r_end = N;
-      res->cells = cells;
+      res->cells = entries(M, N, E * a.pen_g, s * a.pen_g);
     }
   }
 }
@@ -363,19 +447,34 @@ static hipError_t launch_search_k(K kern, int threads, size_t lds, const SearchA
   return hipGetLastError();
 }
 
+#define SEARCH_LAUNCH(K, NWV, LDS)                                        \
+  (a.two_bit ? launch_search_k((K<NWV, true>), 64 * NWV, (LDS), a, s) \
+             : launch_search_k((K<NWV, false>), 64 * NWV, (LDS), a, s))
 hipError_t launch_search(const SearchArgs &a, hipStream_t s) {
   if (a.ntasks <= 0) return hipSuccess;
   const size_t one = (size_t)a.lds_q + a.lds_r + a.lds_f;
   if (a.pen_x > 0) {
-    if (a.waves != 4 || a.pen_e <= 0 || a.ring_h < 1 || a.ring_e < 1) return hipErrorInvalidValue;
+    if (a.pen_e <= 0 || a.pen_g <= 0 || a.ring_h < 1 || a.ring_e < 1) return hipErrorInvalidValue;
     const size_t lds = (size_t)a.lds_q + a.lds_r + (size_t)(a.ring_h + 2 * a.ring_e) * a.lds_f;
-    return launch_search_k(search_affine_kernel<4>, 256, lds, a, s);
+    switch (a.waves) {
+    case 1: return SEARCH_LAUNCH(search_affine_kernel, 1, lds);
+    case 2: return SEARCH_LAUNCH(search_affine_kernel, 2, lds);
+    case 4: return SEARCH_LAUNCH(search_affine_kernel, 4, lds);
+    case 8: return SEARCH_LAUNCH(search_affine_kernel, 8, lds);
+    default: return hipErrorInvalidValue;
+    }
   }
+  if (a.one_row)
+    return a.two_bit ? launch_search_k(search_edit_kernel<true>, 64, one, a, s)
+                     : launch_search_k(search_edit_kernel<false>, 64, one, a, s);
   switch (a.waves) {
-  case 1: return launch_search_k(search_edit_kernel, 64, one, a, s);
-  case 4: return launch_search_k(search_group_kernel<4>, 256, one + a.lds_f, a, s);
+  case 1: return SEARCH_LAUNCH(search_group_kernel, 1, one + a.lds_f);
+  case 2: return SEARCH_LAUNCH(search_group_kernel, 2, one + a.lds_f);
+  case 4: return SEARCH_LAUNCH(search_group_kernel, 4, one + a.lds_f);
+  case 8: return SEARCH_LAUNCH(search_group_kernel, 8, one + a.lds_f);
   default: return hipErrorInvalidValue;
   }
 }
+#undef SEARCH_LAUNCH
 
 } // namespace alnk

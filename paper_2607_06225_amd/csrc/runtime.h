@@ -60,7 +60,8 @@ struct LaunchDesc {
   bool full = false; // rolling blocks: full matrix (one block a lane)
   int max_n = 0; // largest reference length of the launch
   int32_t lds_f = 0;  // search: LDS bytes of one furthest-row array
-  int32_t pen_x = 0, pen_o = 0, pen_e = 0, ring_h = 0, ring_e = 0; // gap-affine SEARCH
+  int32_t pen_x = 0, pen_o = 0, pen_e = 0, ring_h = 0, ring_e = 0; // gap-affine SEARCH,
+  int32_t pen_g = 1;                                               // penalties in units of pen_g
   int32_t dcap = 0, lds_fc = 0; // gap-affine: first-pass diagonal cap and its row bytes
 };
 
@@ -78,7 +79,7 @@ struct aln_plan {
   aln_params p{};
   int32_t n = 0;
   std::vector<int32_t> qlen, rlen;
-  int32_t max_m = 0; // longest query
+  int32_t max_m = 0, max_n = 0; // longest query and reference
   std::vector<alnk::PairTask> tasks;
   std::vector<alnrt::LaunchDesc> launches;
   // packed int16 path
