@@ -463,92 +463,138 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
                         4LL * (rerun_bnd + rerun_prof) <= 160 * 1024;
   if (use_sw16) {
     // rows per lane: forced while the autotuner measures, else the
-    // ALN_SW16_ROWS override, else the autotuner's choice, else 16
-    int tile = 16;
+    // ALN_SW16_ROWS override, else the autotuner's choice, else 16 or 8 (below)
+    int tile = 0;
     if (ctx->tuning.valid) tile = ctx->tuning.sw16_rows;
     if (const char *ev = getenv("ALN_SW16_ROWS")) {
       const int r = atoi(ev);
       if (r == 4 || r == 8 || r == 12 || r == 16) tile = r;
     }
     if (ctx->force_sw16_rows) tile = ctx->force_sw16_rows;
-    const int R = tile;
-    pl->sw16_rows = R;
-    const int32_t HS = 16 * R, HW = 64 * R; // strip heights: 16-lane group, wide item
     auto nstr = [](int32_t m, int32_t hs) { return (m + hs - 1) / hs; };
-    // pairs sorted by strips, then columns, longest first; consecutive
-    // pairs share a task (the two 16-bit halves), so the halves match
+    // pairs sorted by the rows a lane of all their strips, then columns, longest
+    // first; consecutive pairs share a task (the two 16-bit halves), so the halves
+    // match
     std::vector<int32_t> order(n);
-    for (int32_t i = 0; i < n; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-      const int sa = nstr(pl->qlen[a], HS), sb = nstr(pl->qlen[b], HS);
-      if (sa != sb) return sa > sb;
-      return pl->rlen[a] > pl->rlen[b];
-    });
     struct TaskDim {
       int32_t pa, pb, mmax, nmax;
     };
     std::vector<TaskDim> td;
-    for (int32_t q = 0; q < n; q += 2) {
-      TaskDim t{order[q], q + 1 < n ? order[q + 1] : -1, pl->qlen[order[q]], pl->rlen[order[q]]};
-      if (t.pb >= 0) {
-        t.mmax = std::max(t.mmax, pl->qlen[t.pb]);
-        t.nmax = std::max(t.nmax, pl->rlen[t.pb]);
+    auto make_tasks = [&](int32_t unit) {
+      for (int32_t i = 0; i < n; ++i) order[i] = i;
+      std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        const int sa = nstr(pl->qlen[a], unit), sb = nstr(pl->qlen[b], unit);
+        if (sa != sb) return sa > sb;
+        return pl->rlen[a] > pl->rlen[b];
+      });
+      td.clear();
+      for (int32_t q = 0; q < n; q += 2) {
+        TaskDim t{order[q], q + 1 < n ? order[q + 1] : -1, pl->qlen[order[q]], pl->rlen[order[q]]};
+        if (t.pb >= 0) {
+          t.mmax = std::max(t.mmax, pl->qlen[t.pb]);
+          t.nmax = std::max(t.nmax, pl->rlen[t.pb]);
+        }
+        td.push_back(t);
       }
-      td.push_back(t);
-    }
-    const int32_t nt = (int32_t)td.size();
-    // Serial column steps of one wavefront: a group of four tasks on 16-lane
-    // groups runs the largest strip count times the widest reference (plus
-    // the lane skew); a wide item runs one task in 64*R-row strips.
-    auto steps_narrow = [&](const std::vector<int32_t> &grp) {
-      int32_t ns = 0, nm = 0;
-      for (int32_t k : grp) {
-        ns = std::max(ns, nstr(td[k].mmax, HS));
-        nm = std::max(nm, td[k].nmax);
-      }
-      return (int64_t)ns * (nm + 15);
     };
-    auto steps_wide = [&](int32_t k) { return (int64_t)nstr(td[k].mmax, HW) * (td[k].nmax + 63); };
-    // Load model: one wavefront per item; LDS bounds the wavefronts per CU.
-    // A lone wavefront keeps its SIMD about 4/5 busy, so a second one on the
-    // same SIMD adds about a quarter of a wavefront's rate.
-    const size_t lds16 = alnk::sw16_lds_bytes(R, hs.alphabet);
-    const int wpc = (int)std::max<size_t>(1, std::min<size_t>(16, (size_t)ctx->lds_per_cu / lds16));
-    const double capacity =
-        (double)ctx->cus * (std::min(wpc, 4) + 0.25 * std::min(std::max(wpc - 4, 0), 4));
-    int64_t total = 0;
-    for (int32_t k = 0; k < nt; k += 4) {
-      std::vector<int32_t> grp;
-      for (int32_t q = k; q < std::min(nt, k + 4); ++q) grp.push_back(q);
-      total += steps_narrow(grp);
-    }
-    // A task whose own strips take longer than most of a wave slot's share
-    // of the launch would finish last: it runs wide.
-    int wide_pct = ctx->tuning.valid && ctx->tuning.sw16_wide_pct ? ctx->tuning.sw16_wide_pct : 80;
-    if (ctx->force_sw16_wide_pct) wide_pct = ctx->force_sw16_wide_pct;
-    const double wide_above =
-        wide_pct < 0 ? 1e300 : wide_pct / 100.0 * (double)total / capacity;
     struct Item {
-      int64_t steps;
-      std::vector<int32_t> tasks;
-      bool wide;
+      int64_t steps;      // its serial time
+      int32_t first, end; // tasks
+      int32_t wide;       // the one pair of a wide item, or -1
     };
-    std::vector<Item> items;
-    std::vector<int32_t> grp;
-    auto close_group = [&] {
-      if (grp.empty()) return;
-      items.push_back(Item{steps_narrow(grp), grp, false});
-      grp.clear();
+    struct Layout {
+      int R = 0;
+      std::vector<Item> items;
+      double time = 0;    // estimate, instructions of one wavefront
+      uint64_t bytes = 0; // boundary rows, all tasks narrow
     };
-    for (int32_t k = 0; k < nt; ++k) {
-      if ((double)nstr(td[k].mmax, HS) * (td[k].nmax + 15) > wide_above) {
-        items.push_back(Item{steps_wide(k), {k}, true});
-        continue;
+    auto lay_out = [&](int R) {
+      Layout o;
+      o.R = R;
+      const int32_t nt = (int32_t)td.size();
+      // Serial column steps of one wavefront, in sixteenths of a step of R rows a lane
+      // (the last strip's steps are shorter): a group of four tasks on 16-lane
+      // groups runs the strips of the tallest over the widest reference (plus the
+      // lane skew); a wide item runs one pair in 128*R-row strips.
+      auto strips16 = [&](int32_t m, int32_t lanes) -> int64_t {
+        const int32_t full = std::max(nstr(m, lanes * R) - 1, 0);
+        const int32_t last = std::max(4, nstr(m - full * lanes * R, 4 * lanes) * 4);
+        return 16 * full + 16 * (12 * last + 22) / (12 * R + 22);
+      };
+      auto narrow = [&](int32_t first, int32_t end) {
+        int32_t m = 0, nm = 0;
+        for (int32_t k = first; k < end; ++k) {
+          m = std::max(m, td[k].mmax);
+          nm = std::max(nm, td[k].nmax);
+        }
+        return strips16(m, 16) * (nm + 15);
+      };
+      // Load model: one wavefront per item; LDS bounds the wavefronts per CU.
+      // A lone wavefront keeps its SIMD about 4/5 busy, so a second one on the
+      // same SIMD adds about a quarter of a wavefront's rate.
+      const size_t lds16 = alnk::sw16_lds_bytes(R, hs.alphabet);
+      const int wpc = (int)std::max<size_t>(1, std::min<size_t>(16, (size_t)ctx->lds_per_cu / lds16));
+      const double capacity =
+          (double)ctx->cus * (std::min(wpc, 4) + 0.25 * std::min(std::max(wpc - 4, 0), 4));
+      int64_t total = 0;
+      for (int32_t k = 0; k < nt; k += 4) total += narrow(k, std::min(nt, k + 4));
+      // A task whose own strips take longer than most of a wave slot's share
+      // of the launch would finish last: it runs wide.
+      int wide_pct = ctx->tuning.valid && ctx->tuning.sw16_wide_pct ? ctx->tuning.sw16_wide_pct : 80;
+      if (ctx->force_sw16_wide_pct) wide_pct = ctx->force_sw16_wide_pct;
+      const double wide_above =
+          wide_pct < 0 ? 1e300 : wide_pct / 100.0 * (double)total / capacity;
+      // Narrow items hold up to four consecutive tasks that are not wide (a wide task
+      // between them ends an item: the tallest come first, so there are few).
+      int32_t open = -1;
+      auto close = [&](int32_t end) {
+        if (open >= 0) o.items.push_back(Item{narrow(open, end), open, end, -1});
+        open = -1;
+      };
+      for (int32_t k = 0; k < nt; ++k) {
+        if (nstr(td[k].mmax, 16 * R) > 1) o.bytes += align_up((uint64_t)(td[k].nmax + 1) * 8, 16);
+        if ((double)narrow(k, k + 1) > wide_above) {
+          close(k);
+          for (int32_t pair : {td[k].pa, td[k].pb})
+            if (pair >= 0)
+              o.items.push_back(Item{strips16(pl->qlen[pair], 128) * (pl->rlen[pair] + 127), k, k + 1,
+                                     pair});
+          continue;
+        }
+        if (open < 0) open = k;
+        if (k + 1 - open == 4) close(k + 1);
       }
-      grp.push_back(k);
-      if (grp.size() == 4) close_group();
+      close(nt);
+      int64_t longest = 0, all = 0;
+      for (const Item &it : o.items) {
+        longest = std::max(longest, it.steps);
+        all += it.steps;
+      }
+      o.time = std::max((double)longest, (double)all / capacity) * (12 * R + 22) / 16;
+      return o;
+    };
+    make_tasks(64);
+    Layout lay = lay_out(tile ? tile : 16);
+    if (!tile && alnk::sw16_lds_bytes(16, hs.alphabet) * 4 > (size_t)ctx->lds_per_cu) {
+      // Profiles of 16 rows a lane leave SIMDs without a wavefront (19 letters and
+      // more), ones of 8 rows take more instructions a cell: the shorter of the two, by
+      // the model above.  20 letters, 16 / 8 rows, ms: 1 024 pairs of about 350 0.70 /
+      // 0.78, 8 192 0.95 / 0.98, 16 384 1.53 / 1.21, 40 000 3.54 / 2.49; 30 000 of about
+      // 120 0.39 / 0.33.  (Four letters, 20 000 reads of 150: 0.27 / 0.35, so always 16.)
+      Layout small8 = lay_out(8);
+      if (small8.time < lay.time) lay = std::move(small8);
     }
-    close_group();
+    // More strips and a finer order may take more boundary rows than 16 rows a lane and an
+    // order by strips: not past what a call without allocation has (the rest of the
+    // workspace is less than 160 bytes a pair).
+    if (lay.bytes + 160ull * n > ALN_NOALLOC_WORKSPACE_BYTES) {
+      make_tasks(16 * (tile ? tile : 16));
+      lay = lay_out(tile ? tile : 16);
+    }
+    const int R = lay.R;
+    pl->sw16_rows = R;
+    const int32_t HS = 16 * R, HW = 128 * R; // strip heights: 16-lane group, wide item
+    std::vector<Item> &items = lay.items;
     // longest item first: workgroups are dispatched in index order
     std::stable_sort(items.begin(), items.end(),
                      [](const Item &a, const Item &b) { return a.steps > b.steps; });
@@ -562,18 +608,25 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     L.first = 0;
     for (const Item &it : items) {
       pl->sw16_items.push_back(
-          alnk::Sw16Item{(int32_t)pl->sw16_tasks.size(), it.wide ? -1 : (int32_t)it.tasks.size()});
-      pl->sw16_wide += it.wide;
-      for (int32_t k : it.tasks) {
+          alnk::Sw16Item{(int32_t)pl->sw16_tasks.size(), it.wide >= 0 ? -1 : it.end - it.first});
+      pl->sw16_wide += it.wide >= 0;
+      for (int32_t k = it.first; k < it.end; ++k) {
         const TaskDim &d = td[k];
         alnk::Sw16Task t;
-        t.pa = d.pa;
-        t.pb = d.pb;
-        t.nstrips = nstr(d.mmax, it.wide ? HW : HS);
-        t.nmax = d.nmax;
+        if (it.wide >= 0) {
+          t.pa = it.wide;
+          t.pb = -1;
+          t.nstrips = nstr(pl->qlen[it.wide], HW);
+          t.nmax = pl->rlen[it.wide];
+        } else {
+          t.pa = d.pa;
+          t.pb = d.pb;
+          t.nstrips = nstr(d.mmax, HS);
+          t.nmax = d.nmax;
+        }
         t.bnd_off = 0;
         bnd_rel.push_back(t.nstrips > 1 ? bnd_bytes : ~0ULL);
-        if (t.nstrips > 1) bnd_bytes += align_up((uint64_t)(t.nmax + 1) * 8);
+        if (t.nstrips > 1) bnd_bytes += align_up((uint64_t)(t.nmax + 1) * (it.wide >= 0 ? 4 : 8), 16);
         pl->sw16_tasks.push_back(t);
         // the same pairs one by one (per-pair runs, always wide), sharing the
         // task's boundary row: a pair alone never has more strips, nor more

@@ -186,10 +186,11 @@ struct ValidateArgs {
   int32_t n_reset;
 };
 
-// Two pairs aligned by one 16-lane group of the packed int16 kernel.
+// Two pairs aligned by one 16-lane group of the packed int16 kernel, or one pair by the
+// 64 lanes of a wide item.
 struct Sw16Task {
   int32_t pa, pb;    // pair indices (pb = -1: none)
-  int32_t nstrips;   // strips of the taller pair (16*R or, in a wide item, 64*R rows)
+  int32_t nstrips;   // strips of the taller pair (16*R or, in a wide item, 128*R rows)
   int32_t nmax;      // max(N_a, N_b)
   int64_t bnd_off;   // byte offset of the group's strip-boundary row in ws
 };
@@ -205,8 +206,8 @@ struct Sw16Item {
 // (alphabet + 1) letters x 16 lanes x R rows (equally two pairs x 64 lanes),
 // then the 32x32 int8 substitution matrix.
 inline size_t sw16_lds_bytes(int rows, int alphabet) {
-  // profiles, the int8 substitution matrix, 64 staged bottom-row entries
-  return (size_t)8 * (alphabet + 1) * 16 * rows + kMaxAlphabet * kMaxAlphabet + 64 * 8;
+  // profiles, the int8 substitution matrix
+  return (size_t)8 * (alphabet + 1) * 16 * rows + kMaxAlphabet * kMaxAlphabet;
 }
 
 struct Sw16Args {

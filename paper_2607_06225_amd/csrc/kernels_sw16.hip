@@ -1,19 +1,29 @@
 // kernels_sw16.hip -- Smith-Waterman (LOCAL, full matrix, score + end cell)
 // in packed 16-bit integers on gfx950.
 //
-// Layout.  A group of G lanes (G = 16: one DPP row; G = 64: the whole
-// wavefront) aligns two pairs at once: every 32-bit register holds pair A in
-// its low half and pair B in its high half, so each packed instruction
-// (v_pk_*_i16 / _u16) advances two cells.  Lane l of a group owns R
-// consecutive query rows of a G*R-row strip and runs one column behind lane
+// Layout.  A group of 16 lanes (one DPP row) aligns two pairs at once: every
+// 32-bit register holds pair A in its low half and pair B in its high half, so each
+// packed instruction (v_pk_*_i16 / _u16) advances two cells.  Lane l of a group owns R
+// consecutive query rows of a 16*R-row strip and runs one column behind lane
 // l-1 (an antidiagonal wavefront of R-row tiles); the bottom row's H and F
-// and the reference codes move to the next lane with one DPP shift, and lane
+// and the reference codes move to the next lane with one DPP shift, lane
 // 0 is fed the strip's top row through a ring shifted the other way, and
-// lane G-1's bottom row is staged in LDS and written out G columns at a
-// time.  A
-// wavefront runs either four 16-lane groups or one 64-lane group; the
+// lane 15's bottom row leaves through a third, written out 16 columns at a
+// time.  A wavefront runs four such groups, or (a wide item) one pair on all 64
+// lanes, in strips of 128*R rows: the low halves hold the upper 64*R rows, the high
+// halves the lower ones, 64 columns behind, fed from lane 63's low halves.  The
 // planner gives the wide form to pairs whose strips would otherwise make
 // the launch wait on one wavefront.
+//
+// The last strip takes only as many rows a lane as its longest query needs (a
+// multiple of 4), so tasks are sorted by that.
+//
+// What bounds it: vector instructions, about 12 R + 22 a step, where LDS holds
+// at least four wavefronts a CU (with 20 letters: up to 12 rows a lane; 16 rows, three
+// wavefronts, issue 0.72 a cycle), and the longest pair in smaller batches.  16 384
+// pairs of about 350 letters, 16 rows a lane: 1.95 -> 1.37 ms with shorter last strips
+// (then 1.12 with 8 rows, chosen by the planner); 1 024 pairs, the longest 2 000 x
+// 2 000: 1.38 -> 0.68 ms with one pair a wide item (two pairs in strips of 64*R: 1.12).
 //
 // Local-alignment clamp.  With E+ = max(E, 0) and F+ = max(F, 0) the local
 // recurrence is unchanged: H = max(H(i-1,j-1) + s, E+, F+), and
@@ -108,16 +118,17 @@ __device__ __forceinline__ uint32_t grp_shl1z(uint32_t v) {
 }
 
 // One work item of the packed kernel: `count` tasks (two pairs each) on the
-// four 16-lane groups of the wavefront (G = 16), or one task on all 64 lanes
-// (G = 64).  A wide item runs 64*R-row strips, so a long pair takes a
-// quarter of the strips, and of the serial time, of a 16-lane group.
+// four 16-lane groups of the wavefront (G = 16), or one pair on all 64 lanes
+// (G = 64).  A wide item runs 128*R-row strips, so a long pair takes an
+// eighth of the strips, and of the serial time, of a 16-lane group.
 template <int R, int G>
 __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const int8_t *smat,
-                                          uint2 *stage_all, int first, int count) {
+                                          int first, int count) {
   static_assert(G == 16 || G == 64, "group width");
   constexpr int NG = 64 / G;       // groups per wavefront
-  constexpr int HS = G * R;        // strip height
-  constexpr int NWD = R / 4;       // profile dwords per lane and letter
+  constexpr bool TALL = G == 64;   // one pair, the strip's lower half in the high halves
+  constexpr int FOLD = TALL ? 2 : 1;
+  constexpr int HS = FOLD * G * R; // strip height
   const int lane = threadIdx.x;
   const int g = lane / G;
   const int gl = lane % G;
@@ -130,11 +141,6 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
   const uint32_t ge16 = (uint32_t)ge & 0xffffu;
   const uint32_t ge2 = ge16 | (ge16 << 16);
 
-  // profile: [group][pair][letter][G lanes][R bytes]
-  const size_t pair_stride = (size_t)L * G * R;
-  int8_t *profA = prof + ((size_t)g * 2 + 0) * pair_stride;
-  int8_t *profB = prof + ((size_t)g * 2 + 1) * pair_stride;
-  uint2 *stage = stage_all + g * G; // lane G-1's bottom row over one G-step block
 
   Sw16Task tk;
   if (g < count) tk = a.tasks[first + g];
@@ -145,7 +151,9 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
     MA = a.b.q_len[tk.pa]; NA = a.b.r_len[tk.pa];
     QA = a.b.q + a.b.q_off[tk.pa]; RA = a.b.r + a.b.r_off[tk.pa];
   }
-  if (tk.pb >= 0) {
+  if (TALL) {
+    MB = MA; NB = NA; QB = QA; RB = RA;
+  } else if (tk.pb >= 0) {
     MB = a.b.q_len[tk.pb]; NB = a.b.r_len[tk.pb];
     QB = a.b.q + a.b.q_off[tk.pb]; RB = a.b.r + a.b.r_off[tk.pb];
   }
@@ -157,52 +165,61 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
     ns_w = max(ns_w, __builtin_amdgcn_readlane(my_ns, q * G));
     nmax_w = max(nmax_w, __builtin_amdgcn_readlane(my_nmax, q * G));
   }
-  const int T_w = nmax_w + G - 1;
-  uint2 *bnd = reinterpret_cast<uint2 *>(a.ws + tk.bnd_off);
+  const int T_w = nmax_w + FOLD * G - 1;
+  uint2 *bnd = reinterpret_cast<uint2 *>(a.ws + tk.bnd_off);       // H, F of two pairs a column
+  uint32_t *bnd1 = reinterpret_cast<uint32_t *>(a.ws + tk.bnd_off); // TALL: of one
   unsigned long long bestA = 0, bestB = 0;
 
-  for (int s = 0; s < ns_w; ++s) {
+  // One strip of G * RS rows (RS = R but for the last, see below).
+  auto strip = [&](auto rs_tag, const int s) __attribute__((always_inline)) {
+    constexpr int RS = decltype(rs_tag)::value;
+    int8_t *profA = prof + ((size_t)g * 2 + 0) * L * G * RS; // [group][pair][letter][G lanes][RS bytes]
+    int8_t *profB = prof + ((size_t)g * 2 + 1) * L * G * RS;
     const bool gact = s < my_ns;
-    const int itop = s * HS + gl * R + 1;
+    // first rows of this lane, in the low and in the high halves
+    const int itop = s * HS + gl * RS + 1;
+    const int itopB = TALL ? itop + G * RS : itop;
     // ---- query profile of this lane's rows for both pairs
     if (gact) {
-      int qa[R], qb[R];
+      int qa[RS], qb[RS];
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
+      for (int r = 0; r < RS; ++r) {
         const int i = itop + r;
+        const int ib = itopB + r;
         qa[r] = (i <= MA) ? min((int)QA[i - 1], A) : A;
-        qb[r] = (i <= MB) ? min((int)QB[i - 1], A) : A;
+        qb[r] = (ib <= MB) ? min((int)QB[ib - 1], A) : A;
       }
       for (int c = 0; c < L; ++c) {
-        uint32_t wa[NWD], wb[NWD];
+        uint32_t wa[(RS / 4)], wb[(RS / 4)];
 #pragma unroll
-        for (int k = 0; k < NWD; ++k) { wa[k] = 0; wb[k] = 0; }
+        for (int k = 0; k < (RS / 4); ++k) { wa[k] = 0; wb[k] = 0; }
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < RS; ++r) {
           wa[r >> 2] |= ((uint32_t)(uint8_t)smat[qa[r] * kMaxAlphabet + c]) << ((r & 3) * 8);
           wb[r >> 2] |= ((uint32_t)(uint8_t)smat[qb[r] * kMaxAlphabet + c]) << ((r & 3) * 8);
         }
-        uint32_t *da = reinterpret_cast<uint32_t *>(profA + ((size_t)c * G + gl) * R);
-        uint32_t *db = reinterpret_cast<uint32_t *>(profB + ((size_t)c * G + gl) * R);
+        uint32_t *da = reinterpret_cast<uint32_t *>(profA + ((size_t)c * G + gl) * RS);
+        uint32_t *db = reinterpret_cast<uint32_t *>(profB + ((size_t)c * G + gl) * RS);
 #pragma unroll
-        for (int k = 0; k < NWD; ++k) { da[k] = wa[k]; db[k] = wb[k]; }
+        for (int k = 0; k < (RS / 4); ++k) { da[k] = wa[k]; db[k] = wb[k]; }
       }
     }
     if (s > 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 
     // ---- state: H(i, j-1), E+(i, j), per-row keys
-    uint32_t Hl[R], EN[R], kA[R], kB[R];
+    uint32_t Hl[RS], EN[RS], kA[RS], kB[RS];
 #pragma unroll
-    for (int r = 0; r < R; ++r) { Hl[r] = 0; EN[r] = 0; kA[r] = 0; kB[r] = 0; }
+    for (int r = 0; r < RS; ++r) { Hl[r] = 0; EN[r] = 0; kA[r] = 0; kB[r] = 0; }
     uint32_t hd_top = 0;
     uint32_t out_h = 0, out_f = 0;
-    // reference codes travel as profile offsets, c * G * R bytes (< 2^16),
+    // reference codes travel as profile offsets, c * G * RS bytes (< 2^16),
     // pair A in the low half, pair B in the high half
-    constexpr uint32_t CS = (uint32_t)G * R;
+    constexpr uint32_t CS = (uint32_t)G * RS;
     const uint32_t padc2 = (uint32_t)PADC * CS | (((uint32_t)PADC * CS) << 16);
     auto load_c = [&](int col) -> uint32_t {
+      const int colb = TALL ? col - G : col; // the high halves run G columns behind
       const uint32_t ca = (col >= 1 && col <= NA) ? (uint32_t)min((int)RA[col - 1], PADC) : (uint32_t)PADC;
-      const uint32_t cb = (col >= 1 && col <= NB) ? (uint32_t)min((int)RB[col - 1], PADC) : (uint32_t)PADC;
+      const uint32_t cb = (colb >= 1 && colb <= NB) ? (uint32_t)min((int)RB[colb - 1], PADC) : (uint32_t)PADC;
       return ca * CS | ((cb * CS) << 16);
     };
     const bool from_bnd = gact && s > 0;
@@ -220,9 +237,15 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
       if (gact) {
         c = load_c(col);
         if (from_bnd) {
-          const uint2 v = bnd[min(col, my_nmax)];
-          h = v.x;
-          f = v.y;
+          if constexpr (TALL) {
+            const uint32_t v = bnd1[min(col, my_nmax)];
+            h = v & 0xffffu;
+            f = v >> 16;
+          } else {
+            const uint2 v = bnd[min(col, my_nmax)];
+            h = v.x;
+            f = v.y;
+          }
         }
       }
     };
@@ -231,34 +254,38 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
     load_blk(1, n1_c, n1_h, n1_f);
     load_blk(2, n2_c, n2_h, n2_f);
     const bool write_bnd = gact && (s + 1 < my_ns);
+    uint32_t done_h = 0, done_f = 0;
     auto flush = [&](int t_last, int k_done) {
-      const int col = t_last - k_done + 1 + gl + 2 - G; // entry gl: step t_last - k_done + 1 + gl
-      if (write_bnd && gl < k_done && col >= 1 && col <= my_nmax) bnd[col] = stage[gl];
+      const int col = t_last + 3 + gl - (FOLD + 1) * G; // of the step that lane gl holds
+      if (write_bnd && gl >= G - k_done && col >= 1 && col <= my_nmax) {
+        if constexpr (TALL) bnd1[col] = (done_h >> 16) | (done_f & 0xffff0000u);
+        else bnd[col] = make_uint2(done_h, done_f);
+      }
     };
 
     // Reference codes travel one lane per step; lane l's code for step t+1
     // is lane l-1's code for step t, so each step reads the profile words
     // of the next step ahead of use.
-    const int8_t *laneA = profA + (size_t)gl * R, *laneB = profB + (size_t)gl * R;
+    const int8_t *laneA = profA + (size_t)gl * RS, *laneB = profB + (size_t)gl * RS;
     auto prof_words = [&](uint32_t cc, uint32_t *wa, uint32_t *wb) {
       const uint32_t *pa = reinterpret_cast<const uint32_t *>(laneA + (cc & 0xffffu));
       const uint32_t *pb = reinterpret_cast<const uint32_t *>(laneB + (cc >> 16));
 #pragma unroll
-      for (int k = 0; k < NWD; ++k) { wa[k] = pa[k]; wb[k] = pb[k]; }
+      for (int k = 0; k < (RS / 4); ++k) { wa[k] = pa[k]; wb[k] = pb[k]; }
     };
     uint32_t cur_c = grp_shr1<G>(ring_c, padc2);
-    uint32_t wa[NWD], wb[NWD], wa2[NWD], wb2[NWD];
+    uint32_t wa[(RS / 4)], wb[(RS / 4)], wa2[(RS / 4)], wb2[(RS / 4)];
     prof_words(cur_c, wa, wb);
 
     // One column step.  (wc, wbc) hold this step's profile words, (wn, wbn)
     // receive the next step's; the loop below alternates the two buffers.
     // End-cell keys of an even step are parked in (pA, pB) and folded in
     // with the odd step's keys by one three-input max.
-    uint32_t pA[R], pB[R];
+    uint32_t pA[RS], pB[RS];
 #pragma unroll
-    for (int r = 0; r < R; ++r) { pA[r] = 0; pB[r] = 0; }
-    auto step = [&](int t, auto odd_tag, const uint32_t (&wc)[NWD], const uint32_t (&wbc)[NWD],
-                    uint32_t (&wn)[NWD], uint32_t (&wbn)[NWD]) {
+    for (int r = 0; r < RS; ++r) { pA[r] = 0; pB[r] = 0; }
+    auto step = [&](int t, auto odd_tag, const uint32_t (&wc)[(RS / 4)], const uint32_t (&wbc)[(RS / 4)],
+                    uint32_t (&wn)[(RS / 4)], uint32_t (&wbn)[(RS / 4)]) {
       constexpr bool odd = decltype(odd_tag)::value;
       const int kb = t & (G - 1);
       if (kb == 0 && t > 0) {
@@ -270,6 +297,10 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
       // the rings move first, so that lane 0's input is taken from the old
       // ring register in place
       const uint32_t nh = grp_shl1z<G>(ring_h), nf = grp_shl1z<G>(ring_f);
+      if constexpr (TALL) { // below the low half's bottom row lies the high half's top row
+        ring_h |= (uint32_t)__builtin_amdgcn_readlane((int)out_h, G - 1) << 16;
+        ring_f |= (uint32_t)__builtin_amdgcn_readlane((int)out_f, G - 1) << 16;
+      }
       const uint32_t in_h = grp_shr1<G>(ring_h, out_h);
       const uint32_t in_f = grp_shr1<G>(ring_f, out_f);
       ring_h = nh;
@@ -288,9 +319,9 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
       {
         // diagonal inputs of every row first, from H(i-1, j-1) before any
         // row overwrites its H(i, j-1)
-        uint32_t hdg[R];
+        uint32_t hdg[RS];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < RS; ++r) {
           const uint32_t hd = r == 0 ? hd_top : Hl[r - 1];
           switch (r & 3) {
           case 0: hdg[r] = add_score_bytes<0>(hd, wc[r >> 2], wbc[r >> 2]); break;
@@ -302,16 +333,17 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
         uint32_t tu = pk_subsat_u16(in_h, goe2);
         uint32_t fu = in_f;
         // 0xffff - j in the low half (the keys take only that half)
-        const uint32_t jinv = 0xffffu - (uint32_t)j;
+        const uint32_t jinv = 0xffffu - (uint32_t)(TALL ? min(j, 0xffff) : j);
+        const uint32_t jinvB = TALL ? 0xffffu - (uint32_t)(j - G) : jinv;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
+        for (int r = 0; r < RS; ++r) {
           const uint32_t f = pk_max_i16(pk_add_16(fu, ge2), tu);
           const uint32_t h = pk_max_i16(pk_max_i16(hdg[r], EN[r]), f);
           const uint32_t tt = pk_subsat_u16(h, goe2);
           const uint32_t en = pk_max_i16(pk_add_16(EN[r], ge2), tt);
           // bytes (high to low): pair A's H, then jinv; pair B's H, then jinv
           const uint32_t keyA = __builtin_amdgcn_perm(h, jinv, 0x05040100u);
-          const uint32_t keyB = __builtin_amdgcn_perm(h, jinv, 0x07060100u);
+          const uint32_t keyB = __builtin_amdgcn_perm(h, jinvB, 0x07060100u);
           if constexpr (odd) {
             kA[r] = max(kA[r], max(pA[r], keyA));
             kB[r] = max(kB[r], max(pB[r], keyB));
@@ -325,10 +357,11 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
           fu = f;
         }
         hd_top = in_h;
-        out_h = Hl[R - 1];
+        out_h = Hl[RS - 1];
         out_f = fu;
       }
-      if (gl == G - 1) stage[kb] = make_uint2(out_h, out_f);
+      done_h = grp_shl1<G>(out_h, done_h);
+      done_f = grp_shl1<G>(out_f, done_f);
       cur_c = next_c;
     };
     int t = 0;
@@ -338,7 +371,7 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
     }
     if (t < T_w) step(t, std::false_type{}, wa, wb, wa2, wb2);
 #pragma unroll
-    for (int r = 0; r < R; ++r) { // keys still parked by a final even step
+    for (int r = 0; r < RS; ++r) { // keys still parked by a final even step
       kA[r] = max(kA[r], pA[r]);
       kB[r] = max(kB[r], pB[r]);
     }
@@ -352,11 +385,12 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
     unsigned long long la = 0, lb = 0;
     if (gact) {
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
+      for (int r = 0; r < RS; ++r) {
         const int i = itop + r;
         const int ha = (int)kA[r] >> 16, hb = (int)kB[r] >> 16;
         if (i <= MA && ha > 0) la = max_u64(la, end_key(ha, i, 0xffff - (int)(kA[r] & 0xffffu)));
-        if (i <= MB && hb > 0) lb = max_u64(lb, end_key(hb, i, 0xffff - (int)(kB[r] & 0xffffu)));
+        const int ib = itopB + r;
+        if (ib <= MB && hb > 0) lb = max_u64(lb, end_key(hb, ib, 0xffff - (int)(kB[r] & 0xffffu)));
       }
     }
 #pragma unroll
@@ -366,7 +400,27 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
     }
     bestA = max_u64(bestA, la);
     bestB = max_u64(bestB, lb);
+  };
+  for (int s = 0; s < ns_w; ++s) {
+    // The last strip takes as few rows a lane as hold what is left of the longest query
+    // of the wavefront's last strips: a step costs about 12 RS + 22 instructions.
+    int rows = R;
+    if (s == ns_w - 1) {
+      int left = 0;
+#pragma unroll
+      for (int q = 0; q < NG; ++q) {
+        const int m = __builtin_amdgcn_readlane(max(MA, MB), q * G);
+        if (__builtin_amdgcn_readlane(my_ns, q * G) == ns_w) left = max(left, m - s * HS);
+      }
+      rows = min(R, (left + 4 * FOLD * G - 1) / (4 * FOLD * G) * 4);
+    }
+    if (R >= 16 && rows > 12) strip(std::integral_constant<int, R < 16 ? R : 16>{}, s);
+    else if (R >= 12 && rows > 8) strip(std::integral_constant<int, R < 12 ? R : 12>{}, s);
+    else if (R >= 8 && rows > 4) strip(std::integral_constant<int, R < 8 ? R : 8>{}, s);
+    else strip(std::integral_constant<int, 4>{}, s);
   }
+
+  if (TALL) bestA = max_u64(bestA, bestB);
 
   // ---- results
   for (int half = 0; half < 2; ++half) {
@@ -409,7 +463,6 @@ __global__ __launch_bounds__(64) void sw16_kernel(Sw16Args a) {
   // is padding: -128)
   int8_t *prof = reinterpret_cast<int8_t *>(smem);
   int8_t *smat = prof + (size_t)8 * L * 16 * R;
-  uint2 *stage = reinterpret_cast<uint2 *>(smat + kMaxAlphabet * kMaxAlphabet);
   for (int k = threadIdx.x; k < kMaxAlphabet * kMaxAlphabet; k += 64) {
     const int qa = k / kMaxAlphabet, rc = k % kMaxAlphabet;
     smat[k] = (qa < A && rc < A) ? (int8_t)a.sc->mat[k] : (int8_t)-128;
@@ -423,8 +476,8 @@ __global__ __launch_bounds__(64) void sw16_kernel(Sw16Args a) {
   } else if (item >= a.ntasks) {
     return;
   }
-  if (it.count < 0) sw16_item<R, 64>(a, prof, smat, stage, it.first, 1);
-  else sw16_item<R, 16>(a, prof, smat, stage, it.first, it.count);
+  if (it.count < 0) sw16_item<R, 64>(a, prof, smat, it.first, 1);
+  else sw16_item<R, 16>(a, prof, smat, it.first, it.count);
 }
 
 hipError_t launch_sw16(int rows, const Sw16Args &a, hipStream_t s) {
