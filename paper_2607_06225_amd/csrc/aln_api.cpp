@@ -327,9 +327,10 @@ static int64_t band_cells(int64_t M, int64_t N, int64_t w) {
   return total + (b - a - 1) * (2 * w + 1);
 }
 
-aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params *params, int32_t n,
-                             const int32_t *q_len_host, const int32_t *r_len_host,
-                             aln_plan **plan) {
+// home: every pair stays on the kernel family of its own size (see `moved` below)
+static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *params, int32_t n,
+                            const int32_t *q_len_host, const int32_t *r_len_host, bool home,
+                            aln_plan **plan) {
   if (!ctx || !params || !plan || n < 0 || (n > 0 && (!q_len_host || !r_len_host)))
     return fail(ctx, ALN_E_INVAL, "null argument or negative n");
   *plan = nullptr;
@@ -893,7 +894,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
   // (a tuned or forced choice of the antidiagonal kernel: rolling blocks only)
   const int band_asked = ctx->force_band_kernel ? ctx->force_band_kernel
                                                 : (ctx->tuning.valid ? ctx->tuning.band_kernel : 0);
-  if (p.prune == ALN_BAND && band_asked <= 1 && n >= kStripBandPairs)
+  if (!home && p.prune == ALN_BAND && band_asked <= 1 && n >= kStripBandPairs)
     for (Item &it : items) {
       if (it.kind != K_DIAG) continue;
       const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
@@ -929,7 +930,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
   // wavefront, of 161..256 rows (16 a lane) twice as long, so those only past
   // two pairs a SIMD.  One launch, its rows a lane by the longest query, until
   // eight pairs a SIMD; from there on by each pair's, and beside longer pairs.
-  if (srows == 0) {
+  if (!home && srows == 0) {
     int64_t n_full = 0;
     int32_t fullM = 0, fullN = 0;
     auto whole = [&](const Item &it) {
@@ -978,6 +979,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
       hs.mismatch - 2 * hs.gap_extend >= -128 && maxM <= 65535 && maxN <= 65535 &&
       ((int64_t)maxM + maxN) * (1 - hs.gap_extend + std::max(hs.match, 0)) < (1LL << 23);
   const bool lanes_ok = lanes_fit && !p.want_cigar;
+  pl->moved = moved;
   if (moved) regroup(items); // longest first by the first choice's cost
   uint64_t tb_off = 0;
   auto at = [&](size_t k) -> const Item & { return items[(size_t)order[k]]; };
@@ -1146,6 +1148,24 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
   pl->cigar_words = cg_off;
   *plan = pl;
   return ALN_OK;
+}
+
+aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params *params, int32_t n,
+                             const int32_t *q_len_host, const int32_t *r_len_host,
+                             aln_plan **plan) {
+  const aln_status st =
+      plan_form(ctx, scoring_id, params, n, q_len_host, r_len_host, false, plan);
+  // The other families' codes take up to three times the bytes of a pair's own (512 x 60
+  // full matrix, two rows a lane instead of eight: 2.2): not past what a call without
+  // allocation has where its own would fit.
+  constexpr uint64_t lim = ALN_NOALLOC_WORKSPACE_BYTES;
+  if (st != ALN_OK || !(*plan)->moved || (*plan)->ws_bytes <= lim || (*plan)->ws_bytes > 4 * lim)
+    return st;
+  aln_plan *own = nullptr;
+  if (plan_form(ctx, scoring_id, params, n, q_len_host, r_len_host, true, &own) != ALN_OK) return st;
+  if (own->ws_bytes <= lim) std::swap(*plan, own);
+  delete own;
+  return st;
 }
 
 void alnrt::plan_stage(const aln_plan *pl, void *dst) {
