@@ -945,6 +945,9 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       }
     const int64_t simds = 4LL * ctx->cus;
     const bool few = n >= kStripBandPairs && n_full * 4 <= simds && fullN <= 2038;
+    const bool few8 =
+        alnk::band_lds_bytes(alnk::kStripPipeWaves2, (fullN + 10 + 15) / 16 * 16,
+                             small ? 0 : (int)align_up((uint64_t)hs.alphabet * 64 * 4, 16)) <= 160 * 1024;
     const bool split = n_full > 8 * simds;
     for (Item &it : items) {
       const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
@@ -952,8 +955,18 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       if (few) {
         moved = true;
         it.kind = K_BAND;
-        it.rows = fullM <= 512 ? 2 : 4;
-        it.waves = alnk::kStripPipeWaves;
+        // as many strips at a time as there are, of the rows that run shortest: two or
+        // four rows a lane on four / eight wavefronts, M = N, fill us:
+        //   500: 139, 144 / 140, 145   600: 196, 182 / 172, 182   800: 289, 239 / 246, 238
+        //   1 000: 365, 277 / 302, 277   1 300: 633, 582 / 438, 507
+        //   1 600: 972, 718 / 682, 626   2 000: 1 484, 883 / 923, 779
+        it.rows = fullM <= 640 || (fullM > 1024 && fullM <= 1408) ? 2 : 4;
+        it.waves = fullM <= 512 || (fullM > 640 && fullM <= 1024) ? alnk::kStripPipeWaves
+                                                                  : alnk::kStripPipeWaves2;
+        if (!few8) { // eight wavefronts' rings and profiles do not fit
+          it.rows = fullM <= 512 ? 2 : 4;
+          it.waves = alnk::kStripPipeWaves;
+        }
         it.ring = (int)std::max<int64_t>(64, ((int64_t)N + 10 + 15) / 16 * 16);
       } else if (it.kind == K_STRIP && small && n_full >= kRollPairs && N < 65536 && M <= 256 &&
                  (split || fullM <= 160 || (fullM <= 256 && n_full > 2 * simds))) {

@@ -1047,8 +1047,9 @@ hipError_t launch_band_strip(int rows, int mode, bool tb, bool small_alphabet, c
   if (a.waves == kStripPipeWaves)
     return rows == 2 ? launch_band_g<2, kStripPipeWaves>(mode, tb, small_alphabet, a, s)
                      : launch_band_g<4, kStripPipeWaves>(mode, tb, small_alphabet, a, s);
-  if (a.waves == kStripPipeWaves2 && rows == 2)
-    return launch_band_g<2, kStripPipeWaves2>(mode, tb, small_alphabet, a, s);
+  if (a.waves == kStripPipeWaves2)
+    return rows == 2 ? launch_band_g<2, kStripPipeWaves2>(mode, tb, small_alphabet, a, s)
+                     : launch_band_g<4, kStripPipeWaves2>(mode, tb, small_alphabet, a, s);
   if (a.waves == 1)
     return rows == 2 ? launch_band_g<2, 1>(mode, tb, small_alphabet, a, s)
                      : launch_band_g<4, 1>(mode, tb, small_alphabet, a, s);
