@@ -1893,10 +1893,11 @@ aln_status aln_fold_plan_create(aln_ctx *ctx, const aln_fold_params *params, int
   // leaves CUs idle, so shorter ones follow in it as long as it does not end later
   // (its course is followed here with the time of a workgroup alone on its CU, us);
   // and one launch of the rest, two or more workgroups a CU.  2 048 sequences of
-  // 76..500 nt: four launches by length (LDS of 128, 256, 384, 512 nt) 1 493 us, these
-  // two 1 246, with the gaps filled 1 143; a third launch for those of which eight
-  // share a CU 1 170.  Wavefronts a workgroup, by how many share a CU: 2 048 of 500 nt
-  // 4 / 8 / 16: 3.30 / 3.16 / 3.11 ms, of 180 nt 0.24 / 0.28 / 0.57.
+  // 76..500 nt, before the products of 0 / 1 scores went to the matrix cores: four
+  // launches by length (LDS of 128, 256, 384, 512 nt) 1 493 us, these two 1 246, with the
+  // gaps filled 1 143; a third launch for those of which eight share a CU 1 170.
+  // Wavefronts a workgroup, by how many share a CU, 4 / 8 / 16, 2 048 of 500 nt: 3.10 /
+  // 2.38 / 2.29 ms, of 300 nt 0.71 / 0.66 / 1.01, of 180 nt 0.21 / 0.32 / 0.56.
   const bool tiles = p.xdrop < 0;
   if (tiles) {
     auto per_cu = [&](int32_t s) {
@@ -1904,7 +1905,7 @@ aln_status aln_fold_plan_create(aln_ctx *ctx, const aln_fold_params *params, int
     };
     auto us = [&](int32_t s) {
       const double L = len_host[s];
-      return 0.36 * L + 1.8e-6 * L * L * L;
+      return 0.36 * L + (maxpair <= 1 ? 0.9e-6 : 1.8e-6) * L * L * L;
     };
     std::vector<int32_t> idx, alone, shared;
     for (int32_t s = 0; s < n; ++s)

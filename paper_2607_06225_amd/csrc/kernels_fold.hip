@@ -44,6 +44,8 @@
 //
 // Unpruned sequences with byte elements take a form of their own, by tiles
 // (fold_tile_kernel).
+#include <algorithm>
+
 #include "internal.h"
 
 namespace alnk {
@@ -374,11 +376,13 @@ __global__ __launch_bounds__(B) void fold_kernel(FoldArgs a) {
 // meets them with row ii of (I,I), fixed.  Cells not there are 0, which no term that
 // counts is below.  Nothing on the chain from step to step goes through LDS.
 //
-// What bounds it: vector instructions, 0.73 a cycle and CU at 496 nt (one workgroup
-// a CU, whose completions leave SIMDs idle) and 0.81 at 367 nt (two), about 60%
-// of them in products.  2 048 sequences: 76..500 nt 5.11 -> 1.15 ms, 400..500 nt
-// 9.30 -> 2.49, 40..127 nt 0.232 -> 0.071; 4 of 400..500 nt 1.38 -> 0.37 ms (before: a
-// cell a lane and a barrier or two each span, a term two byte reads from LDS).
+// What bounds it: vector instructions (0.73 a cycle and CU at 496 nt, one workgroup a CU;
+// 0.81 at 367 nt, two; 60% of them in products of bytes), with products on the matrix
+// cores the completions: 31 steps of about 56 instructions a tile diagonal, in which one
+// workgroup a CU leaves SIMDs idle.  2 048 sequences, ms, before (a cell a lane and a
+// barrier or two each span, a term two byte reads from LDS) / products of bytes / matrix
+// cores: 76..500 nt 5.11 / 1.15 / 0.96, 400..500 nt 9.30 / 2.49 / 1.96, 40..127 nt
+// 0.232 / 0.071 / 0.074; 4 of 400..500 nt 1.38 / 0.37 / 0.28.
 using u16x2 = unsigned short __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_max_u16(uint32_t x, uint32_t y) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, x),
@@ -411,6 +415,71 @@ struct FoldPair {
       }
   }
 };
+
+// Pair scores of 0 and 1: on the matrix cores.  G(i,k) grows by 0 or 1 with each base,
+// so within a tile row A(i,k) - A(i,0) and within a tile column B(k,j) - B(15,j) are
+// 0..15, and 2 ^ (8 x) of them is a bf16 number; their product over k is a sum of at
+// most 16 powers 2 ^ (8 (a + b)), whose exponent's multiple of 8 is the maximum, 0..30
+// (a float's exponent field holds 8 x 30 + 4; a maximum of 0 may be flushed to
+// zero, which reads the same).  Exact, and 4096 terms take one instruction and 20-odd
+// to feed it.  The first operand is B transposed, so that a lane's result is the dword
+// of row lane & 15, columns 4 (lane >> 4) ...
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+struct FoldUnitPair {
+  uint32_t x, rb4;      // A(i, 4 kg ..), B(15, 4 kg ..)
+  uint16_t ra, rb;      // A(i, 0), B(15, j)
+  uint8_t y[4];         // B(4 kg .., j)
+  __device__ __forceinline__ void load(const uint8_t *a, const uint8_t *b, int lane) {
+    const int l = lane & 15, kg = lane >> 4;
+    x = *reinterpret_cast<const uint32_t *>(a + 16 * l + 4 * kg);
+    ra = a[16 * l];
+    rb = b[240 + l];
+    rb4 = *reinterpret_cast<const uint32_t *>(b + 240 + 4 * kg);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = b[64 * kg + 16 * r + l];
+  }
+  __device__ __forceinline__ void join(uint32_t &e, uint32_t &o) const {
+    const u16x2 scale = {1024, 1024}; // 8 << 7, a bf16 exponent of 8
+    auto power = [&](uint32_t pair, uint16_t base, int bias) __attribute__((always_inline)) {
+      const uint16_t c = (uint16_t)(bias * 128 - base * 1024);
+      const u16x2 cc = {c, c};
+      return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, pair) * scale + cc));
+    };
+    const uint32_t y01 = y[0] | ((uint32_t)y[1] << 16), y23 = y[2] | ((uint32_t)y[3] << 16);
+    const uint2 av = make_uint2(power(__builtin_amdgcn_perm(0u, x, 0x0c010c00u), ra, 64),
+                                power(__builtin_amdgcn_perm(0u, x, 0x0c030c02u), ra, 64));
+    const uint2 bv = make_uint2(power(y01, rb, 63), power(y23, rb, 63));
+    const f32x4 d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+        __builtin_bit_cast(s16x4, bv), __builtin_bit_cast(s16x4, av), f32x4{0, 0, 0, 0}, 0, 0, 0);
+    const uint32_t hi = __builtin_amdgcn_perm(__float_as_uint(d[1]), __float_as_uint(d[0]), 0x0c0c0703u) |
+                        __builtin_amdgcn_perm(__float_as_uint(d[3]), __float_as_uint(d[2]), 0x07030c0cu);
+    const uint32_t v = ((hi >> 2) & 0x3f3f3f3fu) + rb4 + __builtin_amdgcn_perm(0u, (uint32_t)ra, 0u);
+    o = pk_max_u16(o, v);
+    e = pk_max_u16(e, v & kEven);
+  }
+};
+// Products of cnt >= 1 tile pairs for one tile, from the first two on (bstep as below): the
+// dword of row lane & 15, columns 4 (lane >> 4) ... of the joined tile.
+__device__ __forceinline__ uint32_t fold_unit_products(const uint8_t *a, const uint8_t *b, int bstep,
+                                                       int cnt, int lane) {
+  uint32_t e = 0, o = 0;
+  FoldUnitPair p0, p1;
+  p0.load(a, b, lane);
+  for (;;) { // the next pair's reads are in flight meanwhile
+    if (cnt > 1) p1.load(a + 256, b + 256 * bstep, lane);
+    p0.join(e, o);
+    if (cnt <= 1) break;
+    a += 512;
+    b += 256 * (2 * bstep - 1);
+    bstep -= 2;
+    if (cnt > 2) p0.load(a, b, lane);
+    p1.join(e, o);
+    cnt -= 2;
+    if (cnt <= 0) break;
+  }
+  return (o & ~kEven) | e;
+}
 
 // Products of cnt >= 1 tile pairs for one tile: a, b this lane's parts of the first two,
 // bstep tiles from b's to the next, one less each time.  Returns the lane's dword of the
@@ -445,7 +514,7 @@ __device__ __forceinline__ uint32_t fold_products(const uint8_t *a, const uint8_
   return (oo & ~kEven) | eo;
 }
 
-template <int W>
+template <int W, bool UNIT>
 __global__ __launch_bounds__(64 * W) void fold_tile_kernel(FoldArgs args) {
   constexpr int B = 64 * W;
   extern __shared__ __align__(16) uint8_t smem[];
@@ -529,11 +598,12 @@ __global__ __launch_bounds__(64 * W) void fold_tile_kernel(FoldArgs args) {
         const int p = (lane >> 2) & 3, q = lane & 3;
         const int aoff = 64 * p + 4 * sub, boff = 64 * sub + 4 * q;
         const int r = ((sub & 1) << 1) | (sub >> 1); // the row the swaps leave here
-        const int dst = 16 * (4 * p + r) + 4 * q;
+        const int dst = UNIT ? 16 * ii + 4 * sub : 16 * (4 * p + r) + 4 * q;
         while (u < u1) {
           const int cnt = min(per - kk, u1 - u), K = I + 1 + kk;
-          const uint32_t v = fold_products(G + fold_tile_at(I, K, NB) + aoff,
-                                           G + fold_tile_at(K, I + D, NB) + boff, NB - K - 1, cnt);
+          const uint8_t *A = G + fold_tile_at(I, K, NB), *B = G + fold_tile_at(K, I + D, NB);
+          const uint32_t v = UNIT ? fold_unit_products(A, B, NB - K - 1, cnt, lane)
+                                  : fold_products(A + aoff, B + boff, NB - K - 1, cnt);
           uint8_t *to = kk ? part + 256 * wave : G + fold_tile_at(I, I + D, NB);
           *reinterpret_cast<uint32_t *>(to + dst) = v;
           u += cnt;
@@ -685,12 +755,13 @@ static hipError_t launch_fold_b(int block, int stride, const FoldArgs &a, hipStr
   }
 }
 
+template <bool UNIT>
 static hipError_t launch_fold_tiles(int block, const FoldArgs &a, hipStream_t s) {
   const size_t lds = fold_tile_lds_bytes(a.max_n, block / 64);
   switch (block) {
-  case 256: return launch_fold_lds(fold_tile_kernel<4>, block, lds, a, s);
-  case 512: return launch_fold_lds(fold_tile_kernel<8>, block, lds, a, s);
-  case 1024: return launch_fold_lds(fold_tile_kernel<16>, block, lds, a, s);
+  case 256: return launch_fold_lds(fold_tile_kernel<4, UNIT>, block, lds, a, s);
+  case 512: return launch_fold_lds(fold_tile_kernel<8, UNIT>, block, lds, a, s);
+  case 1024: return launch_fold_lds(fold_tile_kernel<16, UNIT>, block, lds, a, s);
   default: return hipErrorInvalidValue;
   }
 }
@@ -703,7 +774,9 @@ hipError_t launch_fold(int elt_bytes, int block, int stride, const FoldArgs &a, 
     return xd ? launch_fold_b<int16_t, true>(block, stride, a, s)
               : launch_fold_b<int16_t, false>(block, stride, a, s);
   if (elt_bytes == 1)
-    return xd ? launch_fold_b<uint8_t, true>(block, stride, a, s) : launch_fold_tiles(block, a, s);
+    return xd ? launch_fold_b<uint8_t, true>(block, stride, a, s)
+              : (*std::max_element(a.pair, a.pair + 16) <= 1 ? launch_fold_tiles<true>(block, a, s)
+                                                             : launch_fold_tiles<false>(block, a, s));
   return hipErrorInvalidValue;
 }
 
