@@ -288,7 +288,8 @@ static int lanes_per_side(const aln_ctx *ctx, int64_t n) {
 
 // Z-drop sides from which the lanes form (eight lanes, a window of 128 cells)
 // replaces one wavefront a side: 12 000 sides of 150..5 000 bp at Z = 100 take
-// 11.8 against 9.4 ms, 25 000 16.2 against 18.8, 100 000 43.7 against 73.1.
+// 11.8 against 9.4 ms, 25 000 15.2 against 18.8, 100 000 43.7 against 73.1 (the
+// first and last before the lanes form's step took a quarter fewer instructions).
 static int64_t zdrop_lanes_from(const aln_ctx *ctx) { return 16LL * 4 * ctx->cus + 1; }
 
 // Interior cells (1 <= i <= M, 1 <= j <= N) of the static band: row i keeps
@@ -1090,7 +1091,7 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
   if (dyn_prune && p.want_cigar) {
     pl->xtb_first = (int32_t)pl->tasks.size();
     pl->xtb_count = n;
-    // the sixteen-sides kernel writes the codes where its arithmetic fits,
+    // the lanes kernel writes the codes where its arithmetic fits,
     // unless a tuned tile other than its own asks for the one-side pass
     const int tuned_sides = ctx->force_xdrop_sides
                                 ? ctx->force_xdrop_sides
@@ -1432,7 +1433,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   PairTask *wq1 = plan->xdrop ? reinterpret_cast<PairTask *>(ws + plan->widen_off[1]) : nullptr;
   PairTask *wq2 = plan->xtb_lanes ? reinterpret_cast<PairTask *>(ws + plan->widen_off[2]) : nullptr;
   if (plan->xtb_lanes) {
-    // codes from the sixteen-sides kernel; pairs whose region outgrows its
+    // codes from the lanes kernel; pairs whose region outgrows its
     // window are recomputed with codes by the one-side pass (queue 2)
     alnk::XdlArgs xa;
     xa.zdrop = 0;

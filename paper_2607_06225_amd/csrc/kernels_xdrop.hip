@@ -25,7 +25,9 @@
 // one of the two code runs moves, and a slide of the window.  100 000 sides of
 // 150..5 000 bp at X = 100: 290 instructions a step and 21.1 ms before, 240
 // and 18.4 ms; 25 000 with codes 19.9 ms on four lanes a side before, 15.0 ms
-// (on eight).
+// (on eight).  Z-drop, eight sides of 128 cells a wavefront: 436 instructions a step
+// and 16.6 ms for 25 000 sides with the range a bit test a cell and the best key
+// selected, 335 and 15.2 with the range an add's carry and the key of the masked H.
 //
 // Offset frame.  Every stored value of antidiagonal k is kept minus k*e (e
 // the gap extension score), so a gap step adds nothing:
@@ -149,6 +151,13 @@ __device__ __forceinline__ void shift_in(uint32_t &v, bool bit) {
   unsigned long long cc;
   asm("v_addc_co_u32_e64 %0, %1, %2, %2, %3" : "=v"(v), "=s"(cc) : "v"(v), "s"(km));
   (void)cc;
+}
+
+// the lane mask of v's top bits, and v = 2 v: one add and its carry
+__device__ __forceinline__ unsigned long long shift_out(uint32_t &v) {
+  unsigned long long m;
+  asm("v_add_co_u32_e64 %0, %1, %2, %2" : "=v"(v), "=s"(m) : "v"(v));
+  return m;
 }
 
 // byte b of the result = byte 3 - b of x
@@ -378,7 +387,7 @@ __device__ __forceinline__ void lanes_body(const XdlArgs &a, uint8_t *smem) {
       uint32_t sb = 0, code0 = 0, code1 = 0;
       // Z-drop: this lane's first cell's diagonal minus the best cell's,
       // biased so that the distance is one unsigned difference per cell
-      uint32_t zlane = 0;
+      uint32_t zlane = 0, zin = inr_rev << (32 - XC); // cells in range, from the top
       if (ZD) {
         zlane = (uint32_t)(rj - qi + 2 * XC * gl - (best_j - best_i) + kZBias);
       }
@@ -396,7 +405,7 @@ __device__ __forceinline__ void lanes_body(const XdlArgs &a, uint8_t *smem) {
           // h + |d - d_best|, d = (first cell's diagonal) + 2m
           const uint32_t zc = (uint32_t)(kZBias - 2 * m);
           const int hz = (int)((max(zlane, zc) - min(zlane, zc)) + (uint32_t)h);
-          keep = hz >= T && ((inr_rev >> (XC - 1 - m)) & 1u);
+          keep = __builtin_amdgcn_inverse_ballot_w64(__builtin_amdgcn_ballot_w64(hz >= T) & shift_out(zin));
         }
         const int hm = keep ? h : XNEG;
         // X-drop: E and F may take h of a removed cell, below the threshold
@@ -413,8 +422,8 @@ __device__ __forceinline__ void lanes_body(const XdlArgs &a, uint8_t *smem) {
           E1[m] = en;
           F1[m] = fn;
         }
-        // X-drop: a removed cell never beats a kept one
-        kmax = max(kmax, (ZD && !keep) ? INT32_MIN : ((h << PB) | m));
+        // a removed cell never beats a kept one (X-drop: nor does its h)
+        kmax = max(kmax, ((ZD ? hm : h) << PB) | m);
         // shift the survivor bit in: sb = 2 sb + keep (cell m ends at bit XC - 1 - m)
         shift_in(sb, keep);
         if (TB) { // the cell's code, high bit first
