@@ -118,7 +118,7 @@ aln_status aln_autotune(aln_ctx *ctx, int32_t scoring_id, const aln_params *para
   if (p.prune == ALN_XDROP || p.prune == ALN_ZDROP) {
     // X-drop and Z-drop share the kernel family and its tile choice;
     // candidates rows x sides: 4x1, 4x16, 8x1, 8x4 (encoded rows +
-    // 100*(sides-1)); 4x16 is the sixteen-sides kernel where the plan
+    // 100*(sides-1)); 4x16 is the lanes kernel where the plan
     // qualifies, else 4x1
     static const int c[4] = {4, 1504, 8, 308};
     const int best = pick(c, 4, t.xdrop_ms, 4, [&](int code) {

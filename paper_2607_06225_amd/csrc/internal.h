@@ -148,7 +148,7 @@ inline bool roll_fits(int32_t M, int32_t N, int32_t w, int R, int LG) {
   return LG + cols - 2 * (int64_t)w >= 16 && ((int64_t)LG * R * N) / M > w + 1;
 }
 
-// Traceback region of one side of the sixteen-sides X-drop kernel, nb =
+// Traceback region of one side of the X-drop lanes kernel, nb =
 // ceil((M + N + 1) / 64) blocks of 64 antidiagonals: from byte 0 one byte per
 // antidiagonal (its first and last stored 8-cell group, and the window
 // base's step from the antidiagonal before), from xdl_tb_table(nb) per block
@@ -166,7 +166,7 @@ struct WalkArgs {
   int32_t layout;     // 0: strip layout, 1: diagonal layout, 2: band strips, 3: rolling blocks
   int32_t diag_stride; // diagonal layout: code bytes per lane and antidiagonal
                        // pair (8: bands; 2: X-drop / Z-drop, 4 diagonals per lane;
-                       // 1: the sixteen-sides X-drop kernel's packed 8-cell groups)
+                       // 1: the X-drop lanes kernel's packed 8-cell groups)
   const int32_t *dyn_ntasks; // device-side task count (a re-run queue), or null
   int32_t band_w;            // layouts 2, 3: band half-width
   int32_t shares;            // layouts 2, 3: wavefronts a pair (1, 4, 8, 16; more than
@@ -206,8 +206,8 @@ struct Sw16Item {
 // (alphabet + 1) letters x 16 lanes x R rows (equally two pairs x 64 lanes),
 // then the 32x32 int8 substitution matrix.
 inline size_t sw16_lds_bytes(int rows, int alphabet) {
-  // profiles, the int8 substitution matrix
-  return (size_t)8 * (alphabet + 1) * 16 * rows + kMaxAlphabet * kMaxAlphabet;
+  // profiles, the int8 substitution matrix, 64 staged bottom-row entries
+  return (size_t)8 * (alphabet + 1) * 16 * rows + kMaxAlphabet * kMaxAlphabet + 64 * 8;
 }
 
 struct Sw16Args {

@@ -8,7 +8,7 @@
 // l-1 (an antidiagonal wavefront of R-row tiles); the bottom row's H and F
 // and the reference codes move to the next lane with one DPP shift, lane
 // 0 is fed the strip's top row through a ring shifted the other way, and
-// lane 15's bottom row leaves through a third, written out 16 columns at a
+// lane 15's bottom row is staged in LDS and written out 16 columns at a
 // time.  A wavefront runs four such groups, or (a wide item) one pair on all 64
 // lanes, in strips of 128*R rows: the low halves hold the upper 64*R rows, the high
 // halves the lower ones, 64 columns behind, fed from lane 63's low halves.  The
@@ -123,7 +123,7 @@ __device__ __forceinline__ uint32_t grp_shl1z(uint32_t v) {
 // eighth of the strips, and of the serial time, of a 16-lane group.
 template <int R, int G>
 __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const int8_t *smat,
-                                          int first, int count) {
+                                          uint2 *stage_all, int first, int count) {
   static_assert(G == 16 || G == 64, "group width");
   constexpr int NG = 64 / G;       // groups per wavefront
   constexpr bool TALL = G == 64;   // one pair, the strip's lower half in the high halves
@@ -167,6 +167,7 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
   }
   const int T_w = nmax_w + FOLD * G - 1;
   uint2 *bnd = reinterpret_cast<uint2 *>(a.ws + tk.bnd_off);       // H, F of two pairs a column
+  uint2 *stage = stage_all + g * G; // lane G-1's bottom row over one G-step block
   uint32_t *bnd1 = reinterpret_cast<uint32_t *>(a.ws + tk.bnd_off); // TALL: of one
   unsigned long long bestA = 0, bestB = 0;
 
@@ -254,12 +255,17 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
     load_blk(1, n1_c, n1_h, n1_f);
     load_blk(2, n2_c, n2_h, n2_f);
     const bool write_bnd = gact && (s + 1 < my_ns);
+    // A wide item, which the launch waits for, collects them in two rings instead (lane k
+    // of the last lanes holds the block's step k): 5% shorter than the masked store.
     uint32_t done_h = 0, done_f = 0;
     auto flush = [&](int t_last, int k_done) {
-      const int col = t_last + 3 + gl - (FOLD + 1) * G; // of the step that lane gl holds
-      if (write_bnd && gl >= G - k_done && col >= 1 && col <= my_nmax) {
-        if constexpr (TALL) bnd1[col] = (done_h >> 16) | (done_f & 0xffff0000u);
-        else bnd[col] = make_uint2(done_h, done_f);
+      if constexpr (TALL) {
+        const int col = t_last + 3 + gl - 3 * G; // of the step that this lane holds
+        if (write_bnd && gl >= G - k_done && col >= 1 && col <= my_nmax)
+          bnd1[col] = (done_h >> 16) | (done_f & 0xffff0000u);
+      } else {
+        const int col = t_last - k_done + 1 + gl + 2 - G; // of the step staged in entry gl
+        if (write_bnd && gl < k_done && col >= 1 && col <= my_nmax) bnd[col] = stage[gl];
       }
     };
 
@@ -360,8 +366,12 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
         out_h = Hl[RS - 1];
         out_f = fu;
       }
-      done_h = grp_shl1<G>(out_h, done_h);
-      done_f = grp_shl1<G>(out_f, done_f);
+      if constexpr (TALL) {
+        done_h = grp_shl1<G>(out_h, done_h);
+        done_f = grp_shl1<G>(out_f, done_f);
+      } else if (gl == G - 1) {
+        stage[kb] = make_uint2(out_h, out_f);
+      }
       cur_c = next_c;
     };
     int t = 0;
@@ -463,6 +473,7 @@ __global__ __launch_bounds__(64) void sw16_kernel(Sw16Args a) {
   // is padding: -128)
   int8_t *prof = reinterpret_cast<int8_t *>(smem);
   int8_t *smat = prof + (size_t)8 * L * 16 * R;
+  uint2 *stage = reinterpret_cast<uint2 *>(smat + kMaxAlphabet * kMaxAlphabet);
   for (int k = threadIdx.x; k < kMaxAlphabet * kMaxAlphabet; k += 64) {
     const int qa = k / kMaxAlphabet, rc = k % kMaxAlphabet;
     smat[k] = (qa < A && rc < A) ? (int8_t)a.sc->mat[k] : (int8_t)-128;
@@ -476,8 +487,8 @@ __global__ __launch_bounds__(64) void sw16_kernel(Sw16Args a) {
   } else if (item >= a.ntasks) {
     return;
   }
-  if (it.count < 0) sw16_item<R, 64>(a, prof, smat, it.first, 1);
-  else sw16_item<R, 16>(a, prof, smat, it.first, it.count);
+  if (it.count < 0) sw16_item<R, 64>(a, prof, smat, stage, it.first, 1);
+  else sw16_item<R, 16>(a, prof, smat, stage, it.first, it.count);
 }
 
 hipError_t launch_sw16(int rows, const Sw16Args &a, hipStream_t s) {

@@ -1,8 +1,9 @@
 // kernels_walk.hip -- traceback walks on gfx950: stored 4-bit codes -> CIGAR.
 //
-// One wavefront per pair.  The path from the end cell back to the start is
-// inherently serial, so every lane runs the same walk (all control flow is
-// wave-uniform) and lane 0 writes the CIGAR words.  What the wave adds is
+// One wavefront per pair, or several that share its rows (walk_strip_wave below).
+// The path from the end cell back to the start is inherently serial, so every
+// lane runs the same walk (all control flow is wave-uniform) and lane 0 writes the
+// CIGAR words.  What the wave adds is
 // memory parallelism: the codes are read in an order that never goes
 // forward -- the antidiagonal k = i + j never grows along the path, and in the
 // strip layout neither does the skewed step t = j - 1 + lane -- so the codes
@@ -638,7 +639,7 @@ __global__ __launch_bounds__(64 * S) void walk_strip_wave(WalkArgs a) {
 // i) - dbase(k), lane e / RD, slot e mod RD.  A block is 64 antidiagonals:
 // 2048*S bytes of codes plus 64 window bases.
 //
-// S = 1 is the layout of the sixteen-sides X-drop kernel (xdl_tb_table /
+// S = 1 is the layout of the X-drop lanes kernel (xdl_tb_table /
 // xdl_tb_stream): per antidiagonal the code dwords of the 8-cell groups g0 ..
 // g1 of its 64-cell window that hold candidates, packed; a byte per
 // antidiagonal (g0, g1, the window base's step) and per 64 antidiagonals the

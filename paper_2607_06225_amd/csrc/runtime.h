@@ -94,7 +94,7 @@ struct aln_plan {
   alnrt::LaunchDesc rerun{};
   // X-drop widening queues: counters (ws offset) and two queues of n tasks
   uint64_t widen_cnt_off = 0, widen_off[3] = {0, 0, 0};
-  // X-drop with CIGAR on the sixteen-sides kernel (codes 32 B per antidiagonal);
+  // X-drop with CIGAR on the lanes kernel (codes 32 B per antidiagonal);
   // pairs that outgrow its window go to the one-side pass with codes (queue 2)
   bool xtb_lanes = false;
   int xtb_grid = 0, xtb_lps = 4;
