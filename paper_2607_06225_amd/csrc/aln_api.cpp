@@ -1022,12 +1022,21 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
     L.rows = at(k).rows;
     L.mode = p.mode;
     if (L.kind == K_DIAG && dyn_prune) {
-      // Z-drop takes the 64-cell window only when tuned: its regions often
-      // outgrow it (at Z = 100, e = -2 nearly every side, 345 ms against 300
-      // on the one-side kernel); by default large batches take the 128-cell
-      // window, which holds what the one-side kernel's first window holds
-      const bool zd_wide = zd && lanes_ok && !ctx->tuning.valid && !ctx->force_xdrop_sides &&
-                           (int64_t)(e - k) >= zdrop_lanes_from(ctx);
+      // Z-drop by default takes the 128-cell window in large batches, which holds
+      // what the one-side kernel's first window holds.  Tuned to the lanes form
+      // it takes the 64-cell window where regions fit it: they reach about (Z - |o|)
+      // / (|e| - 1) diagonals either side of the best one, so as many cells (at Z =
+      // 100, e = -2 nearly every side outgrows 64: 100 000 sides 111.5 ms there, 48.2 on
+      // 128; at Z = 40 22.6 and 40.1).
+      const bool lanes_asked =
+          (ctx->force_xdrop_sides ? ctx->force_xdrop_sides : (ctx->tuning.valid ? ctx->tuning.xdrop_sides : 0)) == 16;
+      const bool narrow = hs.gap_extend < -1 &&
+                          (int64_t)p.xdrop + hs.gap_open <= 60LL * (-hs.gap_extend - 1);
+      const bool zd_wide =
+          zd && lanes_ok &&
+          (lanes_asked ? !narrow
+                       : (!ctx->tuning.valid && !ctx->force_xdrop_sides &&
+                          (int64_t)(e - k) >= zdrop_lanes_from(ctx)));
       L.sides = ctx->tuning.valid ? ctx->tuning.xdrop_sides : ((lanes_ok && (!zd || zd_wide)) ? 16 : 1);
       if (ctx->force_xdrop_sides) L.sides = ctx->force_xdrop_sides;
       if (L.sides == 16 && !lanes_ok) L.sides = 1;
