@@ -544,7 +544,7 @@ def run_fold(args, cpu_seconds, check_seconds, machine):
                     ops_per_term=2, ops_by_class=by_class, launches_per_step=launches,
                     avg_launch_ms=round(kms / max(launches, 1), 4),
                     note="achieved = bifurcation terms x 2 (add, max) / fold kernel time; the "
-                         "kernel also spends two address adds and two LDS reads per term")
+                         "folded layout also spends two address adds and two LDS reads per term")
         if clk:
             pk = mix_peak_tops(by_class, rates, "i32", clk)
             roof.update(clock_ghz_measured=round(clk, 3), frac_at_measured_clock=round(achieved / pk, 4))
