@@ -437,6 +437,21 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       L.ring_h = std::max(L.pen_x, L.pen_o + L.pen_e) + 1;
       L.ring_e = L.pen_e + 1;
     }
+    if (unit && L.waves == 4) {
+      // A first pass with rows of the diagonals that a distance needs (of unrelated
+      // sequences of four letters about half their length; at least the lengths'
+      // difference), where LDS, and not the batch, limits the pairs a CU holds and it holds
+      // few: 4 096 of 2 000 nt 163 -> 140 us, 1 000 of 7..8 knt 447 -> 354, the second
+      // launch that looks for marked pairs included.
+      int32_t cap = (int32_t)(0.55 * std::max(maxM, maxN)) + 8;
+      for (int32_t i = 0; i < n; ++i) cap = std::max(cap, std::abs(pl->qlen[i] - pl->rlen[i]) + 8);
+      const int64_t full = (int64_t)L.lds_bnd + L.lds_prof + 2 * (int64_t)L.lds_f;
+      const int64_t fit = 160 * 1024 / full;
+      if (5LL * (2 * cap + 1) <= 4LL * (maxM + maxN + 1) && fit < 16 && n > ctx->cus * fit) {
+        L.dcap = cap;
+        L.lds_fc = (int32_t)align_up((uint64_t)(2 * cap + 1) * 2, 16);
+      }
+    }
     for (int32_t i : order) {
       PairTask t;
       memset(&t, 0, sizeof t);
@@ -1331,17 +1346,16 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
       sa.lds_q = (int32_t)align_up((uint64_t)plan->max_m / 4 + 8, 16);
       sa.lds_r = (int32_t)align_up((uint64_t)plan->max_n / 4 + 8, 16);
     }
-    // gap-affine with a diagonal cap: a capped pass, then full rows for the
-    // pairs it flagged
+    // with a diagonal cap: a capped pass, then full rows for the pairs it marked
     std::pair<const char *, alnk::SearchArgs> passes[2];
     int npass = 0;
-    if (L.pen_x > 0 && L.dcap > 0) {
+    if (L.dcap > 0) {
       alnk::SearchArgs c = sa;
       c.lds_f = L.lds_fc;
       c.dcap = L.dcap;
-      passes[npass++] = {"search_affine", c};
+      passes[npass++] = {L.pen_x > 0 ? "search_affine" : "search", c};
       sa.pass = 1;
-      passes[npass++] = {"search_affine_wide", sa};
+      passes[npass++] = {L.pen_x > 0 ? "search_affine_wide" : "search_wide", sa};
     } else {
       passes[npass++] = {L.pen_x > 0 ? "search_affine" : "search", sa};
     }
@@ -1354,13 +1368,14 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
       // 100..200 nt (32 and more a CU) 49 / 73 / 126 / 234, 4 096 of 2 000 (eight)
       // 187 / 161 / 169 / 273, 1 000 of 7..8 knt (two) 1 240 / 808 / 565 / 464;
       // gap-affine, 4 096 of 2 000 (seven) 1 684 / 1 142 / 1 047 / 1 485, 64 of
-      // 2 000 628 / 398 / 276 / 221.
+      // 2 000 628 / 398 / 276 / 221.  (Capped rows are those of long pairs, with wide
+      // scores: 4 096 of 2 000 nt, sixteen a CU, 140 / 134 us, at 20% 917 / 762.)
       if (!x.one_row) {
         const int64_t rows = x.pen_x > 0 ? x.ring_h + 2 * x.ring_e : 2;
         const int64_t lds = (int64_t)x.lds_q + x.lds_r + rows * x.lds_f;
         const int64_t held = std::min<int64_t>(ctx->lds_per_cu / lds,
                                                per_pair ? 1 : ((int64_t)L.count + ctx->cus - 1) / ctx->cus);
-        x.waves = held >= 16 ? 1 : held >= 8 ? 2 : held >= 3 ? 4 : 8;
+        x.waves = held >= (x.pen_x == 0 && x.dcap > 0 ? 24 : 16) ? 1 : held >= 8 ? 2 : held >= 3 ? 4 : 8;
       }
       if (!per_pair) {
         HIP_TRY(ctx, timed_launch(ctx, passes[ip].first, st, [&] { return alnk::launch_search(x, st); }));

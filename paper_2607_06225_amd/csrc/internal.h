@@ -282,10 +282,10 @@ struct SearchArgs {
   // E and F rows for s - e
   int32_t pen_x, pen_o, pen_e, ring_h, ring_e;
   int32_t pen_g; // unit of the penalties above and of the rings' scores
-  // gap-affine: dcap > 0 stores diagonals -dcap..dcap only (rows of lds_f
-  // bytes); a pair whose range outgrows them is flagged ALN_F_WIDENED and
-  // left to a second launch with dcap = 0 (rows of every diagonal), which
-  // skips unflagged pairs (pass = 1)
+  // dcap > 0 stores diagonals -dcap..dcap only (rows of lds_f bytes); a pair whose
+  // range outgrows them is marked (gap-affine: ALN_F_WIDENED, unit costs: a score
+  // that no pair has) and left to a second launch with dcap = 0 (rows of every
+  // diagonal), which skips unmarked pairs (pass = 1)
   int32_t dcap, pass;
   int32_t one_row;
   int32_t two_bit; // at most four symbols: codes packed two bits each in LDS

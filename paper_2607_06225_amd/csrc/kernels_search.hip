@@ -32,7 +32,8 @@
 // bookkeeping; 0.41 vector and 0.70 scalar a cycle and CU in the edit distance,
 // 0.55 and 0.77 gap-affine), then the chain of one score: rows, first
 // comparison, the path's further comparisons, barrier.  4 096 pairs of 2 000 nt at 5%:
-// edit distance 249 -> 163 us (before: codes in bytes, four wavefronts always),
+// edit distance 249 -> 134 us (before: codes in bytes, four wavefronts always, rows of
+// every diagonal),
 // gap-affine (4, 6, 2) 3 364 -> 959 us (and every score, not the multiples of 2);
 // 30 000 of 100..200 nt 129 -> 50 and 760 -> 157 us.
 #include "internal.h"
@@ -44,6 +45,7 @@ namespace alnk {
 // negative row back to -32768, so it never drifts towards a real row.
 constexpr int16_t kNegF16 = -32768;
 constexpr int kNegF = kNegF16;
+constexpr int kSearchOutgrown = INT32_MIN; // a score that no pair has
 
 __device__ __forceinline__ int fload(const int16_t *F, int idx) { return F[idx]; }
 
@@ -219,6 +221,9 @@ __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
 // outside the previous score's diagonals was never written (the active
 // diagonals only widen, and each row is written on every other score), so it
 // still reads "not reached".
+// Rows first hold diagonals -dcap..dcap only where that lets more pairs share a CU; a
+// pair whose range would leave them is marked by its score and left to a second
+// launch with rows of every diagonal.
 template <int NWV, bool PK>
 __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -236,6 +241,12 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
   const uint8_t *Q = a.b.q + a.b.q_off[p];
   const uint8_t *Rs = a.b.r + a.b.r_off[p];
 
+  if (a.pass == 1 && __builtin_amdgcn_readfirstlane(res->score) != kSearchOutgrown) return;
+  const bool capped = a.dcap > 0;
+  const int off = capped ? a.dcap : M;              // row index of diagonal 0
+  const int lo_st = capped ? max(-M, -a.dcap) : -M; // stored diagonals lo_st..hi_st
+  const int hi_st = capped ? min(N, a.dcap) : N;
+
   uint8_t *qs = smem;
   uint8_t *rs = smem + a.lds_q;
   int16_t *Fp = reinterpret_cast<int16_t *>(smem + a.lds_q + a.lds_r);
@@ -247,38 +258,46 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
     *reinterpret_cast<uint4 *>(Fn + k) = make_uint4(0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u);
   }
   __syncthreads();
-  if (tid == 0) Fp[M] = (int16_t)extend<PK>(qs, rs, 0, 0, min(M, N));
+  if (tid == 0) Fp[off] = (int16_t)extend<PK>(qs, rs, 0, 0, min(M, N));
   __syncthreads();
 
   const int dt = N - M;
+  const bool ends = dt >= lo_st && dt <= hi_st; // the end cell's diagonal is stored
   int s = 0, dmin = 0, dmax = 0;
+  bool outgrown = false;
   for (;;) {
     // is the end cell reached at score s?  Known once score s + 1 is computed, whose
     // reads need not wait for it.
-    const int end = fload(Fp, dt + M);
+    int end = kNegF;
+    if (ends) end = fload(Fp, dt + off);
     const int nmin = max(dmin - 1, -M), nmax = min(dmax + 1, N);
-    const bool edge = nmin == -M || nmax == N;
-    for (int d0 = nmin + 64 * wave; d0 <= nmax; d0 += 64 * NWV) {
+    const bool edge = nmin == lo_st || nmax == hi_st;
+    outgrown = nmin < lo_st || nmax > hi_st; // only with capped rows (uniform)
+    for (int d0 = outgrown ? nmax + 1 : nmin + 64 * wave; d0 <= nmax; d0 += 64 * NWV) {
       const int d = d0 + lane;
       if (d <= nmax) {
-        const int16_t *src = Fp + d + M;
+        const int16_t *src = Fp + d + off;
         const int old = src[0];
         int left, right;
         if (!edge) {
           left = src[-1];
           right = src[1];
         } else {
-          left = d > -M ? src[-1] : kNegF;
-          right = d < N ? src[1] : kNegF;
+          left = d > lo_st ? src[-1] : kNegF;
+          right = d < hi_st ? src[1] : kNegF;
         }
         // a row past the diagonal's end stands for the end, which was reached before:
         // every active diagonal has a row, the furthest of s edits at most
         const int lim = min(M, N - d);
         const int f = min(max(left, max(old, right) + 1), lim);
-        Fn[d + M] = (int16_t)extend<PK>(qs, rs, f, d, lim);
+        Fn[d + off] = (int16_t)extend<PK>(qs, rs, f, d, lim);
       }
     }
-    if (__builtin_amdgcn_readfirstlane(end) >= M || s >= M + N) break;
+    if (__builtin_amdgcn_readfirstlane(end) >= M || s >= M + N) {
+      outgrown = false;
+      break;
+    }
+    if (outgrown) break;
     __syncthreads();
     ++s;
     dmin = nmin;
@@ -287,7 +306,9 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
     Fp = Fn;
     Fn = t;
   }
-  if (tid == 0) {
+  if (tid == 0 && outgrown) {
+    res->score = kSearchOutgrown;
+  } else if (tid == 0) {
     res->score = -s;
     res->q_end = M;
     res->r_end = N;

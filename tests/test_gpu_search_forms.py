@@ -50,3 +50,33 @@ def test_search_forms(ctx, symbols, pen, n, longest):
     print(f"[gpu] {b.name}", flush=True)
     res, _ = aln.align(ctx, b)
     assert compare(b, res, None, oracle_batch(b)) == []
+
+
+def test_edit_distance_outgrows_capped_rows(ctx):
+    """Long pairs of a large batch first run with rows of some 0.55 of the longest length's
+    diagonals a side: pairs with no letter in common, whose distance is their length, and
+    ones close to the cap are right, and nothing is left marked in the flags."""
+    from paper_2607_06225_amd import aln
+    rng = np.random.default_rng(77)
+    qs, rs = [], []
+    for k in range(2700):
+        L = 1500 - k // 4 if k < 12 else int(rng.integers(0, 60))
+        q = rng.integers(0, 2, size=L).astype(np.uint8)
+        if k % 4 == 0:
+            r = q + 2  # no letter in common: distance L
+        elif k % 4 == 1:
+            r = q.copy()
+            r[: int(0.55 * L) + 8] += 2  # at the cap
+        elif k % 4 == 2:
+            r = rng.integers(0, 2, size=max(0, L - 40)).astype(np.uint8)
+        else:
+            r = q.copy()
+        qs.append(q)
+        rs.append(r.astype(np.uint8))
+    b = W.pack_pairs(qs, rs, W.dna_matrix(0, -1), 0, -1, W.GLOBAL, W.SEARCH, name="outgrown")
+    print(f"[gpu] {b.name}", flush=True)
+    res, _ = aln.align(ctx, b)
+    assert compare(b, res, None, oracle_batch(b)) == []
+    assert int(res["score"][0]) == -1500 and not res["flags"].any()
+    one, _ = aln.align(ctx, b, graph=True)
+    assert np.array_equal(res, one)
