@@ -1464,6 +1464,8 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   for (const LaunchDesc &L : plan->launches)
     zd_lanes = zd_lanes || (L.kind == K_DIAG && L.sides == 16 && L.window == 64 && plan->p.prune == ALN_ZDROP);
   PairTask *wq1 = plan->xdrop ? reinterpret_cast<PairTask *>(ws + plan->widen_off[1]) : nullptr;
+  // diagonals of the longest query and reference: no region is wider
+  const int64_t span = (int64_t)plan->max_m + plan->max_n;
   PairTask *wq2 = plan->xtb_lanes ? reinterpret_cast<PairTask *>(ws + plan->widen_off[2]) : nullptr;
   if (plan->xtb_lanes) {
     // codes from the lanes kernel; pairs whose region outgrows its
@@ -1498,9 +1500,10 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
       }
     }
     alnk::DiagArgs d = diag_args(wq2, plan->n, widen_cnt + 4, 16, widen_cnt, wq0);
-    HIP_TRY(ctx, timed_launch(ctx, "xdrop_tb", st, [&] {
-              return alnk::launch_diag(4, ALN_EXTEND, plan->p.prune, true, d, st);
-            }));
+    if (span > 126)
+      HIP_TRY(ctx, timed_launch(ctx, "xdrop_tb", st, [&] {
+                return alnk::launch_diag(4, ALN_EXTEND, plan->p.prune, true, d, st);
+              }));
   } else if (plan->xtb_count > 0) {
     // X-drop / Z-drop with CIGAR: one pass per pair computes the results and
     // writes the traceback codes; regions that outgrow its window go to the
@@ -1630,6 +1633,20 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
       rows[0] = zd_lanes ? 4 : 8;
       rows[1] = zd_lanes ? 8 : 16;
       rows[2] = 32;
+    }
+    // Only the passes that some region of these lengths could need (the windows hold
+    // 126 diagonals in 64 cells, else 64 rows - 6; an empty pass takes 2 us).
+    int64_t held = plan->xtb_count > 0 ? 250 : INT64_MAX;
+    for (const LaunchDesc &L : plan->launches)
+      if (L.kind == K_DIAG && plan->xtb_count == 0)
+        held = std::min<int64_t>(held, L.sides == 16 ? (L.window == 64 ? 126 : 250)
+                                                     : (L.sides == 4 ? 100 : 64 * L.rows - 6));
+    for (int k = 0; k < 4 && rows[k]; ++k) {
+      if (span <= held) {
+        rows[k] = 0;
+        break;
+      }
+      held = 64 * rows[k] - 6;
     }
     int32_t *const cnt[3] = {widen_cnt, widen_cnt + 1, widen_cnt + 4};
     PairTask *const wq[3] = {wq0, wq1, wq0}; // the first queue is read out before it is filled again
