@@ -378,7 +378,7 @@ __global__ __launch_bounds__(B) void fold_kernel(FoldArgs a) {
 //
 // What bounds it: vector instructions (0.73 a cycle and CU at 496 nt, one workgroup a CU;
 // 0.81 at 367 nt, two; 60% of them in products of bytes), with products on the matrix
-// cores the completions: 31 steps of about 56 instructions a tile diagonal, in which one
+// cores (0.52 and 0.55) the completions: 31 steps of about 56 instructions a tile diagonal, in which one
 // workgroup a CU leaves SIMDs idle.  2 048 sequences, ms, before (a cell a lane and a
 // barrier or two each span, a term two byte reads from LDS) / products of bytes / matrix
 // cores: 76..500 nt 5.11 / 1.15 / 0.96, 400..500 nt 9.30 / 2.49 / 1.96, 40..127 nt

@@ -29,8 +29,8 @@
 // kept the LDS busy 73% of the time.)
 //
 // What bounds it: instructions, half of them scalar (loop, exec mask and row
-// bookkeeping; 0.41 vector and 0.70 scalar a cycle and CU in the edit distance,
-// 0.55 and 0.77 gap-affine), then the chain of one score: rows, first
+// bookkeeping; 0.52 vector and 0.70 scalar a cycle and CU in the edit distance,
+// 0.60 and 0.71 gap-affine), then the chain of one score: rows, first
 // comparison, the path's further comparisons, barrier.  4 096 pairs of 2 000 nt at 5%:
 // edit distance 249 -> 134 us (before: codes in bytes, four wavefronts always, rows of
 // every diagonal),
