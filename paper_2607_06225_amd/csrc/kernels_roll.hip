@@ -67,7 +67,8 @@ __global__ __launch_bounds__(64) void roll_kernel(StripArgs a) {
   static_assert(LG == 16 || LG == 64, "a group is a DPP row or a wavefront");
   constexpr int AL = roll_code_align(R);
   // LOCAL / EXTEND, full matrix: a row's best as one key, the score above 0xffff
-  // - j (scores at most 127 * 256, N < 65536; a masked H gives score 0)
+  // - j (scores at most 127 * 256, N < 65536; EXTEND's of any size below zero, and
+  // a masked H, count as score 0, which is no result)
   constexpr bool KEY = !BAND && MODE != ALN_GLOBAL;
   __shared__ __align__(16) uint8_t smem[(64 / LG) * kRollGroup];
   const int lane = threadIdx.x;
@@ -273,7 +274,8 @@ __global__ __launch_bounds__(64) void roll_kernel(StripArgs a) {
         eo[r] = lanes_of(en == tt);
       }
       if (KEY) {
-        rb[r] = max(rb[r], (int)(((uint32_t)h << 16) | jkey));
+        const int hk = MODE == ALN_EXTEND ? max(h, 0) : h; // (the shift would drop a sign)
+        rb[r] = max(rb[r], (int)(((uint32_t)hk << 16) | jkey));
       } else if (MODE != ALN_GLOBAL) {
         if (h > rb[r]) {
           rb[r] = h;
