@@ -139,13 +139,21 @@ __host__ __device__ inline int roll_code_steps(int32_t M, int32_t N, int32_t w, 
   if (span > N) span = N;
   return (int)((span + 2 * (al - 1)) / al * al);
 }
-// Whether a lane has left a block (at most 16 steps after its last in-band
-// step) before its next block's first in-band step, and no block after the
-// first LG starts on column 0.
+// The step from which a lane may leave a block whose last in-band step is `last`: that
+// step's codes are stored, and its cell taken by the block below.
+__host__ __device__ inline int roll_leave(int last, int R) {
+  const int al = roll_code_align(R), stored = (last & ~(al - 1)) + al;
+  return stored > last + 2 ? stored : last + 2;
+}
+// Whether a lane takes up its next block before that block's first in-band step, at
+// every block, and no block after the first LG starts on column 0.  It may leave a
+// block (roll_leave) up to 16 steps after its last in-band step, two rows a block, or
+// 9 with four.  (Before, because the step that takes a block up has lost what the lane
+// above handed over for the diagonal of its first cell.)
 inline bool roll_fits(int32_t M, int32_t N, int32_t w, int R, int LG) {
   if (M < 1 || N < 1 || w >= (1 << 20)) return false;
   const int64_t cols = (((int64_t)LG * R - R + 1) * N) / M; // from a last row to the next block's first
-  return LG + cols - 2 * (int64_t)w >= 16 && ((int64_t)LG * R * N) / M > w + 1;
+  return LG + cols - 2 * (int64_t)w >= (R == 2 ? 17 : 16) && ((int64_t)LG * R * N) / M > w + 1;
 }
 
 // Traceback region of one side of the X-drop lanes kernel, nb =

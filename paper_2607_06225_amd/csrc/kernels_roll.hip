@@ -152,9 +152,7 @@ __global__ __launch_bounds__(64) void roll_kernel(StripArgs a) {
       bb[r] = some ? lo + b : 1 << 30; // t - bb wraps above every width
       wd[r] = some ? hi - lo : 0;
       ncells += some ? hi - lo + 1 : 0;
-      // its last 8 (16) steps' codes stored, and its last cell taken by the
-      // block below
-      if (BAND && r == R - 1) t_done = max(((hi + b) & ~(AL - 1)) + AL, hi + b + 2);
+      if (BAND && r == R - 1) t_done = roll_leave(hi + b, R);
       rowtab[r] = valid ? row_scores(code(i - 1)) : 0x80808080u;
       if (BAND) {
         c += q1;
