@@ -328,10 +328,42 @@ static int64_t band_cells(int64_t M, int64_t N, int64_t w) {
   return total + (b - a - 1) * (2 * w + 1);
 }
 
-// home: every pair stays on the kernel family of its own size (see `moved` below)
-static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *params, int32_t n,
-                            const int32_t *q_len_host, const int32_t *r_len_host, bool home,
-                            aln_plan **plan) {
+// Indices 0 .. key.size() - 1, largest key first, equal keys in index order.  By digits:
+// a plan sorts its pairs on every batch, and a comparison sort of 100 000 took half of
+// its time.
+static std::vector<int32_t> order_desc(const std::vector<uint64_t> &key) {
+  constexpr int kBits = 11, kDigits = 6; // 66 bits
+  constexpr uint32_t kMask = (1u << kBits) - 1;
+  const size_t n = key.size();
+  std::vector<int32_t> at(n);
+  std::iota(at.begin(), at.end(), 0);
+  if (n < 512) {
+    std::stable_sort(at.begin(), at.end(), [&](int32_t a, int32_t b) { return key[a] > key[b]; });
+    return at;
+  }
+  std::vector<uint32_t> count((size_t)kDigits << kBits);
+  for (const uint64_t k : key)
+    for (int d = 0; d < kDigits; ++d) ++count[((size_t)d << kBits) + ((k >> (d * kBits)) & kMask)];
+  std::vector<int32_t> to(n);
+  for (int d = 0; d < kDigits; ++d) {
+    uint32_t *const c = &count[(size_t)d << kBits];
+    auto digit = [&](int32_t k) { return (uint32_t)(key[k] >> (d * kBits)) & kMask; };
+    if (c[digit(0)] == n) continue; // the same in every key
+    uint32_t sum = 0;
+    for (int v = (int)kMask; v >= 0; --v) {
+      const uint32_t here = c[v];
+      c[v] = sum;
+      sum += here;
+    }
+    for (const int32_t k : at) to[c[digit(k)]++] = k;
+    at.swap(to);
+  }
+  return at;
+}
+
+aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params *params, int32_t n,
+                             const int32_t *q_len_host, const int32_t *r_len_host,
+                             aln_plan **plan) {
   if (!ctx || !params || !plan || n < 0 || (n > 0 && (!q_len_host || !r_len_host)))
     return fail(ctx, ALN_E_INVAL, "null argument or negative n");
   *plan = nullptr;
@@ -379,11 +411,9 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
   // updates a single row in place.  Gap-affine penalties: 1 to 8 wavefronts
   // over rings of past H, E and F rows.
   if (p.prune == ALN_SEARCH) {
-    std::vector<int32_t> order(n);
-    for (int32_t i = 0; i < n; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-      return (int64_t)pl->qlen[a] + pl->rlen[a] > (int64_t)pl->qlen[b] + pl->rlen[b];
-    });
+    std::vector<uint64_t> len(n);
+    for (int32_t i = 0; i < n; ++i) len[i] = (uint64_t)pl->qlen[i] + (uint64_t)pl->rlen[i];
+    const std::vector<int32_t> order = order_desc(len);
     LaunchDesc L{};
     L.kind = K_SEARCH;
     L.mode = ALN_GLOBAL;
@@ -492,19 +522,17 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
     // pairs sorted by the rows a lane of all their strips, then columns, longest
     // first; consecutive pairs share a task (the two 16-bit halves), so the halves
     // match
-    std::vector<int32_t> order(n);
     struct TaskDim {
       int32_t pa, pb, mmax, nmax;
     };
     std::vector<TaskDim> td;
     auto make_tasks = [&](int32_t unit) {
-      for (int32_t i = 0; i < n; ++i) order[i] = i;
-      std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-        const int sa = nstr(pl->qlen[a], unit), sb = nstr(pl->qlen[b], unit);
-        if (sa != sb) return sa > sb;
-        return pl->rlen[a] > pl->rlen[b];
-      });
+      std::vector<uint64_t> key(n);
+      for (int32_t i = 0; i < n; ++i)
+        key[i] = ((uint64_t)nstr(pl->qlen[i], unit) << 32) | (uint32_t)pl->rlen[i];
+      const std::vector<int32_t> order = order_desc(key);
       td.clear();
+      td.reserve((size_t)(n + 1) / 2);
       for (int32_t q = 0; q < n; q += 2) {
         TaskDim t{order[q], q + 1 < n ? order[q + 1] : -1, pl->qlen[order[q]], pl->rlen[order[q]]};
         if (t.pb >= 0) {
@@ -607,6 +635,7 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
     // (A batch whose rows would not fit there either keeps the faster layout: 65 536 pairs
     // of about 350 letters 5.9 / 3.4 ms.)
     if (lay.bytes + 160ull * n > ALN_NOALLOC_WORKSPACE_BYTES) {
+      std::vector<TaskDim> fine = td;
       make_tasks(16 * (tile ? tile : 16));
       Layout plain = lay_out(tile ? tile : 16);
       uint64_t least = 0; // boundary rows without those of short wide tasks
@@ -614,7 +643,7 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
         for (int32_t k = it.first; k < it.end; ++k)
           if (td[k].mmax > (it.wide >= 0 ? 64 : 16) * plain.R && (it.wide < 0 || it.wide == td[k].pa))
             least += align_up((uint64_t)(td[k].nmax + 1) * 8);
-      if (least > ALN_NOALLOC_WORKSPACE_BYTES / 10 * 11) make_tasks(64);
+      if (least > ALN_NOALLOC_WORKSPACE_BYTES / 10 * 11) td.swap(fine);
       else lay = std::move(plain);
     }
     const int R = lay.R;
@@ -622,8 +651,8 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
     const int32_t HS = 16 * R, HW = 128 * R; // strip heights: 16-lane group, wide item
     std::vector<Item> &items = lay.items;
     // longest item first: workgroups are dispatched in index order
-    std::stable_sort(items.begin(), items.end(),
-                     [](const Item &a, const Item &b) { return a.steps > b.steps; });
+    std::vector<uint64_t> steps(items.size());
+    for (size_t k = 0; k < items.size(); ++k) steps[k] = (uint64_t)items[k].steps;
     pl->sw16_wide = 0;
     uint64_t bnd_bytes = 0;
     std::vector<uint64_t> bnd_rel;
@@ -632,7 +661,8 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
     L.rows = R;
     L.mode = ALN_LOCAL;
     L.first = 0;
-    for (const Item &it : items) {
+    for (const int32_t at : order_desc(steps)) {
+      const Item &it = items[(size_t)at];
       pl->sw16_items.push_back(
           alnk::Sw16Item{(int32_t)pl->sw16_tasks.size(), it.wide >= 0 ? -1 : it.end - it.first});
       pl->sw16_wide += it.wide >= 0;
@@ -717,43 +747,43 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
     int ring = 0;  // band strips: columns of the LDS boundary ring
     bool full = false; // rolling blocks: full matrix
   };
-  // Launch order: by kernel and tile, each longest first, equal ones by pair
-  // (a sort of 16-byte keys: a plan of 100 000 pairs is sorted on every batch).
+  // Launch order: by kernel and tile, each longest first, equal ones by pair.
   auto cls_of = [](const Item &it) {
     return ((it.kind * 128 + it.waves) * 64 + it.rows) * 2 + (it.full ? 1 : 0);
   };
   std::vector<int32_t> order; // of items
-  auto sort_items = [&](const std::vector<Item> &v) {
-    struct Key {
-      double cost;
-      int32_t cls, at;
-    };
-    std::vector<Key> keys(v.size());
-    for (size_t k = 0; k < v.size(); ++k) keys[k] = Key{v[k].cost, cls_of(v[k]), (int32_t)k};
-    std::sort(keys.begin(), keys.end(), [](const Key &x, const Key &y) {
-      if (x.cls != y.cls) return x.cls < y.cls;
-      if (x.cost != y.cost) return x.cost > y.cost;
-      return x.at < y.at;
-    });
-    order.resize(v.size());
-    for (size_t k = 0; k < v.size(); ++k) order[k] = keys[k].at;
-  };
-  // by class again, the order inside each kept
+  // by class, the order inside each kept
   auto regroup = [&](const std::vector<Item> &v) {
-    std::vector<int32_t> classes;
-    for (const Item &it : v)
-      if (classes.empty() ||
-          (classes.back() != cls_of(it) &&
-           std::find(classes.begin(), classes.end(), cls_of(it)) == classes.end()))
-        classes.push_back(cls_of(it));
+    std::vector<std::pair<int32_t, int32_t>> classes; // and how many
+    std::vector<int32_t> cls(v.size());
+    for (size_t k = 0; k < v.size(); ++k) {
+      cls[k] = cls_of(v[k]);
+      size_t c = 0;
+      while (c < classes.size() && classes[c].first != cls[k]) ++c;
+      if (c == classes.size()) classes.push_back({cls[k], 0});
+      ++classes[c].second;
+    }
     if (classes.size() < 2) return;
     std::sort(classes.begin(), classes.end());
-    std::vector<int32_t> out;
-    out.reserve(v.size());
-    for (int32_t c : classes)
-      for (int32_t k : order)
-        if (cls_of(v[(size_t)k]) == c) out.push_back(k);
+    int32_t sum = 0;
+    for (auto &c : classes) {
+      const int32_t here = c.second;
+      c.second = sum;
+      sum += here;
+    }
+    std::vector<int32_t> out(v.size());
+    for (const int32_t k : order) {
+      size_t c = 0;
+      while (classes[c].first != cls[(size_t)k]) ++c;
+      out[(size_t)classes[c].second++] = k;
+    }
     order.swap(out);
+  };
+  auto sort_items = [&](const std::vector<Item> &v) {
+    std::vector<uint64_t> cost(v.size()); // not negative, so its bits sort as it does
+    for (size_t k = 0; k < v.size(); ++k) memcpy(&cost[k], &v[k].cost, sizeof cost[k]);
+    order = order_desc(cost);
+    regroup(v);
   };
   std::vector<Item> items;
   items.reserve(n);
@@ -904,9 +934,10 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
     }
   }
   sort_items(items);
+  const bool codes = p.want_cigar && !dyn_prune; // the tasks' own (not X-drop's, below)
   std::vector<int64_t> slot;
   uint64_t cg_off = 0;
-  if (p.want_cigar && !dyn_prune) {
+  if (codes) {
     slot.resize(n);
     for (int32_t k : order) {
       const Item &it = items[(size_t)k];
@@ -914,12 +945,32 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       cg_off += (uint64_t)pl->qlen[it.pair] + pl->rlen[it.pair] + 1;
     }
   }
-  bool moved = false; // some pair runs elsewhere
+  // bytes of a pair's traceback codes where an item runs it
+  auto code_bytes = [&](const Item &it) -> uint64_t {
+    const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
+    const uint64_t strips = (uint64_t)((M + 64LL * it.rows - 1) / (64LL * it.rows));
+    if (it.kind == K_STRIP) return strips * (uint64_t)(N + 63) * 64 * (uint64_t)(it.rows / 2);
+    if (it.kind == K_BAND)
+      return strips * 64 * (uint64_t)alnk::band_code_steps(M, N, pl->strip_band_w, it.rows) *
+             (uint64_t)(it.rows / 2);
+    if (it.kind == K_ROLL)
+      return (uint64_t)((M + it.rows - 1) / it.rows) *
+             (uint64_t)alnk::roll_code_steps(M, N, it.full ? 1 << 28 : p.band_w, it.rows) *
+             (uint64_t)(it.rows / 2);
+    const uint64_t nk = (uint64_t)M + N + 1;
+    return (nk + 63) / 64 * 64 * 4 + ((uint64_t)(M + N) / 2 + 1) * 64 * 8;
+  };
+  std::vector<Item> own; // the choice so far, where a pair is moved and there are codes
+  bool moved = false;    // some pair runs elsewhere
+  auto move_away = [&] {
+    if (!moved && codes) own = items;
+    moved = true;
+  };
   // Narrow bands: rolling blocks where a shape fits, else the band strips.
   // (a tuned or forced choice of the antidiagonal kernel: rolling blocks only)
   const int band_asked = ctx->force_band_kernel ? ctx->force_band_kernel
                                                 : (ctx->tuning.valid ? ctx->tuning.band_kernel : 0);
-  if (!home && p.prune == ALN_BAND && band_asked <= 1 && n >= kStripBandPairs)
+  if (p.prune == ALN_BAND && band_asked <= 1 && n >= kStripBandPairs)
     for (Item &it : items) {
       if (it.kind != K_DIAG) continue;
       const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
@@ -928,12 +979,12 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       if (small && n >= kRollPairs) roll_shape(ctx, n, M, N, p.band_w, &rows, &lanes);
       const int64_t ring = (alnk::band_strip_cols(M, N, p.band_w, 2) + 10 + 15) / 16 * 16;
       if (rows) {
-        moved = true;
+        move_away();
         it.kind = K_ROLL;
         it.rows = rows;
         it.waves = lanes;
       } else if (band_asked == 0 && p.band_w < 128 && M >= 128 && ring <= 2048 && ((M + 127LL) / 128) * ((int64_t)N + 1) + N < (1LL << 31)) {
-        moved = true;
+        move_away();
         it.kind = K_BAND;
         it.rows = 2;
         it.waves = alnk::kStripPipeWaves;
@@ -955,7 +1006,7 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
   // wavefront, of 161..256 rows (16 a lane) twice as long, so those only past
   // two pairs a SIMD.  One launch, its rows a lane by the longest query, until
   // eight pairs a SIMD; from there on by each pair's, and beside longer pairs.
-  if (!home && srows == 0) {
+  if (srows == 0) {
     int64_t n_full = 0;
     int32_t fullM = 0, fullN = 0;
     auto whole = [&](const Item &it) {
@@ -978,7 +1029,7 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
       if (!whole(it) || M < 1 || N < 1) continue;
       if (few) {
-        moved = true;
+        move_away();
         it.kind = K_BAND;
         // as many strips at a time as there are, of the rows that run shortest: two or
         // four rows a lane on four / eight wavefronts, M = N, fill us:
@@ -996,7 +1047,7 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       } else if (it.kind == K_STRIP && small && n_full >= kRollPairs && N < 65536 && M <= 256 &&
                  (split || fullM <= 160 || (fullM <= 256 && n_full > 2 * simds))) {
         const int32_t top = split ? M : fullM;
-        moved = true;
+        move_away();
         it.kind = K_ROLL;
         it.full = true;
         it.rows = top <= 128 ? 8 : (top <= 160 ? 10 : 16);
@@ -1017,7 +1068,31 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       hs.mismatch - 2 * hs.gap_extend >= -128 && maxM <= 65535 && maxN <= 65535 &&
       ((int64_t)maxM + maxN) * (1 - hs.gap_extend + std::max(hs.match, 0)) < (1LL << 23);
   const bool lanes_ok = lanes_fit && !p.want_cigar;
-  pl->moved = moved;
+  // The other families' codes take up to three times the bytes of a pair's own (512 x 60
+  // full matrix, two rows a lane instead of eight: 2.2): not past what a call without
+  // allocation has where its own would fit.  (The workspace is the task list and the
+  // codes.)
+  std::vector<uint64_t> bytes; // of each item's codes
+  if (codes) {
+    auto workspace = [&](const std::vector<Item> &v) {
+      uint64_t sum = align_up(sizeof(PairTask) * (size_t)std::max(n, 1));
+      bytes.resize(v.size());
+      for (size_t k = 0; k < v.size(); ++k) sum += bytes[k] = align_up(code_bytes(v[k]));
+      return sum;
+    };
+    constexpr uint64_t lim = ALN_NOALLOC_WORKSPACE_BYTES;
+    const uint64_t now = workspace(items);
+    if (moved && now > lim && now <= 4 * lim && (uint64_t)pl->cells / 2 <= lim) { // 4 bits a cell at least
+      std::vector<uint64_t> elsewhere;
+      elsewhere.swap(bytes);
+      if (workspace(own) <= lim) {
+        items.swap(own);
+        moved = false;
+      } else {
+        bytes.swap(elsewhere);
+      }
+    }
+  }
   if (moved) regroup(items); // longest first by the first choice's cost
   uint64_t tb_off = 0;
   auto at = [&](size_t k) -> const Item & { return items[(size_t)order[k]]; };
@@ -1089,26 +1164,9 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       t.pair = i;
       t.rows = L.rows;
       t.tb_off = -1;
-      if (p.want_cigar && !dyn_prune) {
-        uint64_t bytes;
-        if (L.kind == K_STRIP) {
-          const int64_t ns = (M + 64LL * L.rows - 1) / (64LL * L.rows);
-          bytes = (uint64_t)ns * (uint64_t)(N + 63) * 64ULL * (uint64_t)(L.rows / 2);
-        } else if (L.kind == K_BAND) {
-          const int64_t ns = (M + 64LL * L.rows - 1) / (64LL * L.rows);
-          bytes = (uint64_t)ns * 64ULL *
-                  (uint64_t)alnk::band_code_steps(M, N, pl->strip_band_w, L.rows) *
-                  (uint64_t)(L.rows / 2);
-        } else if (L.kind == K_ROLL) {
-          bytes = (uint64_t)((M + L.rows - 1) / L.rows) *
-                  (uint64_t)alnk::roll_code_steps(M, N, L.full ? 1 << 28 : p.band_w, L.rows) *
-                  (uint64_t)(L.rows / 2);
-        } else {
-          const uint64_t nk = (uint64_t)M + N + 1;
-          bytes = (nk + 63) / 64 * 64 * 4 + ((uint64_t)(M + N) / 2 + 1) * 64 * 8;
-        }
+      if (codes) {
         t.tb_off = (int64_t)tb_off;
-        tb_off += align_up(bytes);
+        tb_off += bytes[(size_t)order[q]];
         t.cigar_off = slot[i];
         t.cigar_cap = M + N + 1;
       }
@@ -1137,12 +1195,9 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
       const int64_t fit = (int64_t)ctx->cus * alnk::xdrop_lanes_waves(true, false, pl->xtb_lps);
       pl->xtb_grid = (int)std::max<int64_t>(1, std::min(want, fit));
     }
-    std::vector<int32_t> order(n);
-    for (int32_t i = 0; i < n; ++i) order[i] = i;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
-      return (int64_t)pl->qlen[a] + pl->rlen[a] > (int64_t)pl->qlen[b] + pl->rlen[b];
-    });
-    for (int32_t i : order) {
+    std::vector<uint64_t> len(n);
+    for (int32_t i = 0; i < n; ++i) len[i] = (uint64_t)pl->qlen[i] + (uint64_t)pl->rlen[i];
+    for (const int32_t i : order_desc(len)) {
       const int32_t M = pl->qlen[i], N = pl->rlen[i];
       PairTask t;
       memset(&t, 0, sizeof t);
@@ -1195,24 +1250,6 @@ static aln_status plan_form(aln_ctx *ctx, int32_t scoring_id, const aln_params *
   pl->cigar_words = cg_off;
   *plan = pl;
   return ALN_OK;
-}
-
-aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params *params, int32_t n,
-                             const int32_t *q_len_host, const int32_t *r_len_host,
-                             aln_plan **plan) {
-  const aln_status st =
-      plan_form(ctx, scoring_id, params, n, q_len_host, r_len_host, false, plan);
-  // The other families' codes take up to three times the bytes of a pair's own (512 x 60
-  // full matrix, two rows a lane instead of eight: 2.2): not past what a call without
-  // allocation has where its own would fit.
-  constexpr uint64_t lim = ALN_NOALLOC_WORKSPACE_BYTES;
-  if (st != ALN_OK || !(*plan)->moved || (*plan)->ws_bytes <= lim || (*plan)->ws_bytes > 4 * lim)
-    return st;
-  aln_plan *own = nullptr;
-  if (plan_form(ctx, scoring_id, params, n, q_len_host, r_len_host, true, &own) != ALN_OK) return st;
-  if (own->ws_bytes <= lim) std::swap(*plan, own);
-  delete own;
-  return st;
 }
 
 void alnrt::plan_stage(const aln_plan *pl, void *dst) {

@@ -80,7 +80,6 @@ struct aln_plan {
   int32_t n = 0;
   std::vector<int32_t> qlen, rlen;
   int32_t max_m = 0, max_n = 0; // longest query and reference
-  bool moved = false;           // some pairs run on another family than their size's
   std::vector<alnk::PairTask> tasks;
   std::vector<alnrt::LaunchDesc> launches;
   // packed int16 path
