@@ -472,7 +472,9 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
       // sequences of four letters about half their length; at least the lengths'
       // difference), where LDS, and not the batch, limits the pairs a CU holds and it holds
       // few: 4 096 of 2 000 nt 163 -> 140 us, 1 000 of 7..8 knt 447 -> 354, the second
-      // launch that looks for marked pairs included.
+      // launch that looks for marked pairs included.  (Unrelated sequences of more letters
+      // lie further apart, five 0.58 of their length, twenty 0.86: those pairs leave the
+      // first pass early.)
       int32_t cap = (int32_t)(0.55 * std::max(maxM, maxN)) + 8;
       for (int32_t i = 0; i < n; ++i) cap = std::max(cap, std::abs(pl->qlen[i] - pl->rlen[i]) + 8);
       const int64_t full = (int64_t)L.lds_bnd + L.lds_prof + 2 * (int64_t)L.lds_f;
@@ -1413,6 +1415,11 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
         const int64_t held = std::min<int64_t>(ctx->lds_per_cu / lds,
                                                per_pair ? 1 : ((int64_t)L.count + ctx->cus - 1) / ctx->cus);
         x.waves = held >= (x.pen_x == 0 && x.dcap > 0 ? 24 : 16) ? 1 : held >= 8 ? 2 : held >= 3 ? 4 : 8;
+        // The edit distance's second launch of more than four symbols: the pairs in it have
+        // wide scores (unrelated, of 20 letters: 4 096 of 2 000 12.6 ms on four
+        // wavefronts, 18.7 on two).  Of four symbols it is as good as always empty, which
+        // takes longer with more wavefronts.
+        if (x.pass == 1 && x.pen_x == 0 && !x.two_bit) x.waves = std::max(x.waves, 4);
       }
       if (!per_pair) {
         HIP_TRY(ctx, timed_launch(ctx, passes[ip].first, st, [&] { return alnk::launch_search(x, st); }));

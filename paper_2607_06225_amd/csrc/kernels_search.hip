@@ -223,8 +223,13 @@ __global__ __launch_bounds__(64) void search_edit_kernel(SearchArgs a) {
 // still reads "not reached".
 // Rows first hold diagonals -dcap..dcap only where that lets more pairs share a CU; a
 // pair whose range would leave them is marked by its score and left to a second
-// launch with rows of every diagonal.
-template <int NWV, bool PK>
+// launch with rows of every diagonal.  With LOOK (more than four symbols: unrelated pairs
+// of four end within the cap, and the look's code takes 4% longer), so is one whose end
+// cell's diagonal has, an eighth of the way to the cap, come forward too slowly to end
+// within it: a pair that has to be searched twice costs the first search 1/64 of its
+// entries, not all.  4 096 unrelated pairs of 2 000 letters of 20: 27.3 ms before, 12.8 with
+// it (and four wavefronts a pair in the second launch); without capped rows 16.4.
+template <int NWV, bool PK, bool LOOK>
 __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
   const int tid = threadIdx.x;
@@ -265,6 +270,9 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
   const bool ends = dt >= lo_st && dt <= hi_st; // the end cell's diagonal is stored
   int s = 0, dmin = 0, dmax = 0;
   bool outgrown = false;
+  // LOOK: the diagonals at which the pair's course is looked at
+  const int look = a.dcap >> 3;
+  int lo_lim = LOOK ? max(lo_st, -look) : lo_st, hi_lim = LOOK ? min(hi_st, look) : hi_st;
   for (;;) {
     // is the end cell reached at score s?  Known once score s + 1 is computed, whose
     // reads need not wait for it.
@@ -272,7 +280,7 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
     if (ends) end = fload(Fp, dt + off);
     const int nmin = max(dmin - 1, -M), nmax = min(dmax + 1, N);
     const bool edge = nmin == lo_st || nmax == hi_st;
-    outgrown = nmin < lo_st || nmax > hi_st; // only with capped rows (uniform)
+    outgrown = nmin < lo_lim || nmax > hi_lim; // only with capped rows (uniform)
     for (int d0 = outgrown ? nmax + 1 : nmin + 64 * wave; d0 <= nmax; d0 += 64 * NWV) {
       const int d = d0 + lane;
       if (d <= nmax) {
@@ -297,7 +305,15 @@ __global__ __launch_bounds__(64 * NWV) void search_group_kernel(SearchArgs a) {
       outgrown = false;
       break;
     }
-    if (outgrown) break;
+    if (outgrown) {
+      if (!LOOK || nmin < lo_st || nmax > hi_st) break;
+      // (row M at this rate after M s / end edits, or an eighth more; a diagonal that s
+      // edits have just reached says nothing)
+      if (2 * abs(dt) <= look && M * s > __builtin_amdgcn_readfirstlane(end) * (a.dcap - a.dcap / 8)) break;
+      lo_lim = lo_st;
+      hi_lim = hi_st;
+      continue; // (nothing of this score has been written)
+    }
     __syncthreads();
     ++s;
     dmin = nmin;
@@ -471,6 +487,13 @@ static hipError_t launch_search_k(K kern, int threads, size_t lds, const SearchA
 #define SEARCH_LAUNCH(K, NWV, LDS)                                        \
   (a.two_bit ? launch_search_k((K<NWV, true>), 64 * NWV, (LDS), a, s) \
              : launch_search_k((K<NWV, false>), 64 * NWV, (LDS), a, s))
+template <int NWV>
+static hipError_t launch_search_group(const SearchArgs &a, hipStream_t s) {
+  const size_t lds = (size_t)a.lds_q + a.lds_r + 2 * (size_t)a.lds_f;
+  if (a.two_bit) return launch_search_k(search_group_kernel<NWV, true, false>, 64 * NWV, lds, a, s);
+  return a.dcap > 0 ? launch_search_k(search_group_kernel<NWV, false, true>, 64 * NWV, lds, a, s)
+                    : launch_search_k(search_group_kernel<NWV, false, false>, 64 * NWV, lds, a, s);
+}
 hipError_t launch_search(const SearchArgs &a, hipStream_t s) {
   if (a.ntasks <= 0) return hipSuccess;
   const size_t one = (size_t)a.lds_q + a.lds_r + a.lds_f;
@@ -489,10 +512,10 @@ hipError_t launch_search(const SearchArgs &a, hipStream_t s) {
     return a.two_bit ? launch_search_k(search_edit_kernel<true>, 64, one, a, s)
                      : launch_search_k(search_edit_kernel<false>, 64, one, a, s);
   switch (a.waves) {
-  case 1: return SEARCH_LAUNCH(search_group_kernel, 1, one + a.lds_f);
-  case 2: return SEARCH_LAUNCH(search_group_kernel, 2, one + a.lds_f);
-  case 4: return SEARCH_LAUNCH(search_group_kernel, 4, one + a.lds_f);
-  case 8: return SEARCH_LAUNCH(search_group_kernel, 8, one + a.lds_f);
+  case 1: return launch_search_group<1>(a, s);
+  case 2: return launch_search_group<2>(a, s);
+  case 4: return launch_search_group<4>(a, s);
+  case 8: return launch_search_group<8>(a, s);
   default: return hipErrorInvalidValue;
   }
 }

@@ -62,7 +62,8 @@ struct LaunchDesc {
   int32_t lds_f = 0;  // search: LDS bytes of one furthest-row array
   int32_t pen_x = 0, pen_o = 0, pen_e = 0, ring_h = 0, ring_e = 0; // gap-affine SEARCH,
   int32_t pen_g = 1;                                               // penalties in units of pen_g
-  int32_t dcap = 0, lds_fc = 0; // gap-affine: first-pass diagonal cap and its row bytes
+  int32_t dcap = 0, lds_fc = 0; // search, either form: diagonal cap of a first pass and its row
+                                // bytes (0: one pass, every diagonal)
 };
 
 constexpr uint64_t kAlign = 256;
