@@ -287,10 +287,17 @@ static int lanes_per_side(const aln_ctx *ctx, int64_t n) {
 }
 
 // Z-drop sides from which the lanes form (eight lanes, a window of 128 cells)
-// replaces one wavefront a side: 12 000 sides of 150..5 000 bp at Z = 100 take
-// 11.8 against 9.4 ms, 25 000 15.2 against 18.8, 100 000 43.7 against 73.1 (the
-// first and last before the lanes form's step took a quarter fewer instructions).
+// replaces one wavefront a side.  Sides of 150..5 000 bp at Z = 100, the first launch of
+// each form in ms, one a wavefront / lanes: 4 000 sides 5.2 / 11.0, 12 000 9.6 / 11.0,
+// 16 384 12.8 / 12.9, 20 000 15.3 / 14.4, 40 000 29.5 / 19.5.
 static int64_t zdrop_lanes_from(const aln_ctx *ctx) { return 16LL * 4 * ctx->cus + 1; }
+
+// Whether a Z-drop region stays within d diagonals either side of the best cell's: a gap
+// of L costs |o| + L |e| and is forgiven L, so it reaches about (Z - |o|) / (|e| - 1) (at
+// e = -1 any).
+static bool zdrop_within(const DevScoring &sc, const aln_params &p, int64_t d) {
+  return sc.gap_extend < -1 && (int64_t)p.xdrop + sc.gap_open <= d * (-sc.gap_extend - 1);
+}
 
 // Interior cells (1 <= i <= M, 1 <= j <= N) of the static band: row i keeps
 // floor(iN/M) - w <= j <= floor(iN/M) + w.  Rows whose band is clipped by
@@ -1115,20 +1122,21 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     L.mode = p.mode;
     if (L.kind == K_DIAG && dyn_prune) {
       // Z-drop by default takes the 128-cell window in large batches, which holds
-      // what the one-side kernel's first window holds.  Tuned to the lanes form
-      // it takes the 64-cell window where regions fit it: they reach about (Z - |o|)
-      // / (|e| - 1) diagonals either side of the best one, so as many cells (at Z =
+      // what the one-side kernel's first window holds, unless Z lets regions reach
+      // so far that nearly every side outgrows that (at e = -1, 17 000 sides of 150..1 500
+      // bp at Z = 15 / 30 / 60 / 100, ms with lanes 23.0 / 21.4 / 24.6 / 24.6, one side a
+      // wavefront 21.6 / 19.0 / 21.9 / 22.3).  Tuned to the
+      // lanes form it takes the 64-cell window where regions fit that (at Z =
       // 100, e = -2 nearly every side outgrows 64: 100 000 sides 111.5 ms there, 48.2 on
       // 128; at Z = 40 22.6 and 40.1).
       const bool lanes_asked =
           (ctx->force_xdrop_sides ? ctx->force_xdrop_sides : (ctx->tuning.valid ? ctx->tuning.xdrop_sides : 0)) == 16;
-      const bool narrow = hs.gap_extend < -1 &&
-                          (int64_t)p.xdrop + hs.gap_open <= 60LL * (-hs.gap_extend - 1);
+      const bool narrow = zdrop_within(hs, p, 60);
       const bool zd_wide =
           zd && lanes_ok &&
           (lanes_asked ? !narrow
                        : (!ctx->tuning.valid && !ctx->force_xdrop_sides &&
-                          (int64_t)(e - k) >= zdrop_lanes_from(ctx)));
+                          (int64_t)(e - k) >= zdrop_lanes_from(ctx) && zdrop_within(hs, p, 250)));
       L.sides = ctx->tuning.valid ? ctx->tuning.xdrop_sides : ((lanes_ok && (!zd || zd_wide)) ? 16 : 1);
       if (ctx->force_xdrop_sides) L.sides = ctx->force_xdrop_sides;
       if (L.sides == 16 && !lanes_ok) L.sides = 1;
@@ -1510,6 +1518,8 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   PairTask *wq1 = plan->xdrop ? reinterpret_cast<PairTask *>(ws + plan->widen_off[1]) : nullptr;
   // diagonals of the longest query and reference: no region is wider
   const int64_t span = (int64_t)plan->max_m + plan->max_n;
+  // cells a lane of the first widening pass (see there)
+  const int wide_rows = plan->p.prune == ALN_ZDROP && zdrop_within(hsc, plan->p, 250) ? 8 : 16;
   PairTask *wq2 = plan->xtb_lanes ? reinterpret_cast<PairTask *>(ws + plan->widen_off[2]) : nullptr;
   if (plan->xtb_lanes) {
     // codes from the lanes kernel; pairs whose region outgrows its
@@ -1553,7 +1563,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
     // writes the traceback codes; regions that outgrow its window go to the
     // widening queue below (score only) and the walk decides their CIGAR
     auto xtb = [&](int32_t first, int32_t count) {
-      alnk::DiagArgs d = diag_args(dtasks + first, count, nullptr, plan->p.prune == ALN_ZDROP ? 8 : 16,
+      alnk::DiagArgs d = diag_args(dtasks + first, count, nullptr, wide_rows,
                                    widen_cnt, wq0);
       return alnk::launch_diag(4, ALN_EXTEND, plan->p.prune, true, d, st);
     };
@@ -1567,7 +1577,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   for (const LaunchDesc &L : plan->launches) {
     if (L.kind == K_DIAG) {
       if (plan->xtb_count > 0) continue; // the traceback pass above replaces it
-      const int widen_rows = plan->xdrop ? (zd_lanes ? 4 : (plan->p.prune == ALN_ZDROP ? 8 : 16)) : 0;
+      const int widen_rows = plan->xdrop ? (zd_lanes ? 4 : wide_rows) : 0;
       if (L.sides == 16) {
         alnk::XdlArgs xa;
         xa.tb = nullptr;
@@ -1666,14 +1676,16 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   if (plan->xdrop) {
     // Pairs whose surviving region outgrew their window, in wider ones.  A
     // handful of long sides sets each pass's time, one wavefront each: Z-drop
-    // regions seldom pass 512 diagonals, where an antidiagonal takes two
-    // thirds of the 1024-diagonal kernel's (25 000 sides at Z = 100: 6.4
-    // against 9.5 ms), so that comes first; from the 64-cell lanes form even
-    // 256 diagonals hold most.
+    // regions that Z keeps within 250 diagonals of the best cell's seldom pass 512, where an
+    // antidiagonal takes two thirds of the 1024-diagonal kernel's (25 000 sides at Z = 100:
+    // 6.4 against 9.5 ms), so that comes first; from the 64-cell lanes form even
+    // 256 diagonals hold most.  (Where Z does not, nearly every side would run there in
+    // vain: 2 000 sides at Z = 300, e = -2 take 12.0 ms with that pass, 6.6 without, 20 000 at
+    // Z = 100, e = -1 66.7 and 51.4.)
     const int pr = plan->p.prune;
     const char *fam = pr == ALN_ZDROP ? "zdrop_wide" : "xdrop_wide";
     int rows[4] = {16, 32, 0, 0};
-    if (pr == ALN_ZDROP) {
+    if (wide_rows == 8) {
       rows[0] = zd_lanes ? 4 : 8;
       rows[1] = zd_lanes ? 8 : 16;
       rows[2] = 32;
