@@ -298,6 +298,11 @@ static int64_t zdrop_lanes_from(const aln_ctx *ctx) { return 16LL * 4 * ctx->cus
 static bool zdrop_within(const DevScoring &sc, const aln_params &p, int64_t d) {
   return sc.gap_extend < -1 && (int64_t)p.xdrop + sc.gap_open <= d * (-sc.gap_extend - 1);
 }
+// d of what counts on few regions past 512 diagonals, the lanes form and the widening pass
+// over them: the longer the sides, the further the widest regions go past the estimate, so
+// that they outgrow 512 from d = 235 on at 2 500 bp and from 205 at 6 000, not yet at 180
+// and 20 000.
+constexpr int kZdropReach = 180;
 
 // Interior cells (1 <= i <= M, 1 <= j <= N) of the static band: row i keeps
 // floor(iN/M) - w <= j <= floor(iN/M) + w.  Rows whose band is clipped by
@@ -1136,7 +1141,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
           zd && lanes_ok &&
           (lanes_asked ? !narrow
                        : (!ctx->tuning.valid && !ctx->force_xdrop_sides &&
-                          (int64_t)(e - k) >= zdrop_lanes_from(ctx) && zdrop_within(hs, p, 250)));
+                          (int64_t)(e - k) >= zdrop_lanes_from(ctx) && zdrop_within(hs, p, kZdropReach)));
       L.sides = ctx->tuning.valid ? ctx->tuning.xdrop_sides : ((lanes_ok && (!zd || zd_wide)) ? 16 : 1);
       if (ctx->force_xdrop_sides) L.sides = ctx->force_xdrop_sides;
       if (L.sides == 16 && !lanes_ok) L.sides = 1;
@@ -1519,7 +1524,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   // diagonals of the longest query and reference: no region is wider
   const int64_t span = (int64_t)plan->max_m + plan->max_n;
   // cells a lane of the first widening pass (see there)
-  const int wide_rows = plan->p.prune == ALN_ZDROP && zdrop_within(hsc, plan->p, 250) ? 8 : 16;
+  const int wide_rows = plan->p.prune == ALN_ZDROP && zdrop_within(hsc, plan->p, kZdropReach) ? 8 : 16;
   PairTask *wq2 = plan->xtb_lanes ? reinterpret_cast<PairTask *>(ws + plan->widen_off[2]) : nullptr;
   if (plan->xtb_lanes) {
     // codes from the lanes kernel; pairs whose region outgrows its
@@ -1676,12 +1681,12 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
   if (plan->xdrop) {
     // Pairs whose surviving region outgrew their window, in wider ones.  A
     // handful of long sides sets each pass's time, one wavefront each: Z-drop
-    // regions that Z keeps within 250 diagonals of the best cell's seldom pass 512, where an
+    // regions that Z keeps within 180 diagonals of the best cell's seldom pass 512, where an
     // antidiagonal takes two thirds of the 1024-diagonal kernel's (25 000 sides at Z = 100:
     // 6.4 against 9.5 ms), so that comes first; from the 64-cell lanes form even
-    // 256 diagonals hold most.  (Where Z does not, nearly every side would run there in
-    // vain: 2 000 sides at Z = 300, e = -2 take 12.0 ms with that pass, 6.6 without, 20 000 at
-    // Z = 100, e = -1 66.7 and 51.4.)
+    // 256 diagonals hold most.  Past that line both passes would be run for many: 3 000 sides of
+    // 2 500 bp, e = -2, ms without / with 512, Z = 180 8.2 / 5.3, Z = 240 5.5 / 8.1; 2 000 at Z =
+    // 300 6.5 / 12.1; 20 000 at e = -1, Z = 100 50.3 / 66.5.
     const int pr = plan->p.prune;
     const char *fam = pr == ALN_ZDROP ? "zdrop_wide" : "xdrop_wide";
     int rows[4] = {16, 32, 0, 0};

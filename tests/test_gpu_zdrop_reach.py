@@ -8,9 +8,9 @@ from paper_2607_06225_amd import aln, workloads as W
 from tests.parity import compare, oracle_batch
 
 
-@pytest.mark.parametrize("ge,Z,family", [(-2, 100, "zdrop_lanes"), (-2, 254, "zdrop_lanes"),
-                                         (-2, 255, "zdrop"), (-2, 700, "zdrop"), (-1, 40, "zdrop"),
-                                         (-3, 504, "zdrop_lanes"), (-3, 505, "zdrop")])
+@pytest.mark.parametrize("ge,Z,family", [(-2, 100, "zdrop_lanes"), (-2, 184, "zdrop_lanes"),
+                                         (-2, 185, "zdrop"), (-2, 700, "zdrop"), (-1, 40, "zdrop"),
+                                         (-3, 364, "zdrop_lanes"), (-3, 365, "zdrop")])
 def test_first_form_of_large_batches(ge, Z, family):
     c = aln.Context.host()
     sid = c.set_scoring(W.dna_matrix(2, -4), -4, ge)
@@ -24,8 +24,8 @@ def test_first_form_of_large_batches(ge, Z, family):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("cigar", [False, True])
-@pytest.mark.parametrize("ge,Z,passes", [(-2, 60, 3), (-2, 254, 3), (-2, 255, 2), (-2, 700, 2),
-                                         (-1, 30, 2), (-3, 504, 3), (-3, 505, 2)])
+@pytest.mark.parametrize("ge,Z,passes", [(-2, 60, 3), (-2, 184, 3), (-2, 185, 2), (-2, 254, 2),
+                                         (-2, 700, 2), (-1, 30, 2), (-3, 364, 3), (-3, 365, 2)])
 def test_wider_passes(ge, Z, passes, cigar):
     assert torch.cuda.is_available()
     rng = np.random.default_rng(Z - ge)
