@@ -188,11 +188,11 @@ typedef struct {
  * 64 lanes, 4 sides of 16 lanes each, or 16 sides of 4 lanes each).  Each
  * ms[] entry is the measured time of one candidate on the tuning batch (0:
  * not measured, negative: not runnable).  While `valid`, aln_plan_create uses the chosen tiles.
- * sw16_wide_pct sets when the packed kernel gives a pair-of-pairs a whole
- * 64-lane wavefront (64*R-row strips) instead of a 16-lane group: when the
+ * sw16_wide_pct sets when the packed kernel gives a task's two pairs, together
+ * or one each, a whole 64-lane wavefront instead of a 16-lane group: when the
  * task's serial column steps exceed that percent of the launch's balanced
- * load per wavefront slot (0: the default, 80; -1: never).  Tiles never
- * change results. */
+ * load per wavefront slot (0: the default, 80, or never where the planner's
+ * model says that takes less time; -1: never).  Tiles never change results. */
 typedef struct {
   int32_t valid;
   int32_t sw16_rows;      /* 4, 8, 12 or 16                                   */

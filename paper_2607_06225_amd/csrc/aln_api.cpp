@@ -559,22 +559,31 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     struct Item {
       int64_t steps;      // its serial time
       int32_t first, end; // tasks
-      int32_t wide;       // the one pair of a wide item, or -1
+      int32_t wide;       // the one pair of a wide item, or -1; kBoth: its task's two
     };
+    constexpr int32_t kBoth = -2;
+    // What a task that runs wide becomes: nothing runs wide; two items, a pair on all lanes
+    // each; one item, the two pairs in the halves of the lanes' words as on 16 lanes.
+    enum Form { kNarrow, kWideOne, kWideBoth };
     struct Layout {
       int R = 0;
+      Form form = kWideOne;
       std::vector<Item> items;
       double time = 0;    // estimate, instructions of one wavefront
       uint64_t bytes = 0; // boundary rows, all tasks narrow
     };
-    auto lay_out = [&](int R) {
+    const int pct_asked = ctx->force_sw16_wide_pct
+                              ? ctx->force_sw16_wide_pct
+                              : (ctx->tuning.valid ? ctx->tuning.sw16_wide_pct : 0);
+    auto lay_out = [&](int R, Form form) {
       Layout o;
       o.R = R;
+      o.form = form;
       const int32_t nt = (int32_t)td.size();
       // Serial column steps of one wavefront, in sixteenths of a step of R rows a lane
       // (the last strip's steps are shorter): a group of four tasks on 16-lane
       // groups runs the strips of the tallest over the widest reference (plus the
-      // lane skew); a wide item runs one pair in 128*R-row strips.
+      // lane skew); a wide item runs one pair in 128*R-row strips, or two in 64*R-row ones.
       auto strips16 = [&](int32_t m, int32_t lanes) -> int64_t {
         const int32_t full = std::max(nstr(m, lanes * R) - 1, 0);
         const int32_t last = std::max(4, nstr(m - full * lanes * R, 4 * lanes) * 4);
@@ -599,10 +608,10 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
       for (int32_t k = 0; k < nt; k += 4) total += narrow(k, std::min(nt, k + 4));
       // A task whose own strips take longer than most of a wave slot's share
       // of the launch would finish last: it runs wide.
-      int wide_pct = ctx->tuning.valid && ctx->tuning.sw16_wide_pct ? ctx->tuning.sw16_wide_pct : 80;
-      if (ctx->force_sw16_wide_pct) wide_pct = ctx->force_sw16_wide_pct;
-      const double wide_above =
-          wide_pct < 0 ? 1e300 : wide_pct / 100.0 * (double)total / capacity;
+      const int wide_pct = pct_asked ? pct_asked : 80;
+      const double wide_above = wide_pct < 0 || form == kNarrow
+                                    ? 1e300
+                                    : wide_pct / 100.0 * (double)total / capacity;
       // Narrow items hold up to four consecutive tasks that are not wide (a wide task
       // between them ends an item: the tallest come first, so there are few).
       int32_t open = -1;
@@ -614,7 +623,9 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
         if (nstr(td[k].mmax, 16 * R) > 1) o.bytes += align_up((uint64_t)(td[k].nmax + 1) * 8, 16);
         if ((double)narrow(k, k + 1) > wide_above) {
           close(k);
-          for (int32_t pair : {td[k].pa, td[k].pb})
+          if (form == kWideBoth)
+            o.items.push_back(Item{strips16(td[k].mmax, 64) * (td[k].nmax + 63), k, k + 1, kBoth});
+          else for (int32_t pair : {td[k].pa, td[k].pb})
             if (pair >= 0)
               o.items.push_back(Item{strips16(pl->qlen[pair], 128) * (pl->rlen[pair] + 127), k, k + 1,
                                      pair});
@@ -629,18 +640,46 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
         longest = std::max(longest, it.steps);
         all += it.steps;
       }
-      o.time = std::max((double)longest, (double)all / capacity) * (12 * R + 22) / 16;
+      o.time = std::max((double)longest, (double)all / capacity);
+      // (few items a slot: of the (r - 1) slots + 1 longest, r share a slot)
+      const size_t slots = (size_t)ctx->cus * std::min(wpc, 4);
+      if (o.items.size() > slots && o.items.size() <= 4 * slots) {
+        std::vector<int64_t> steps;
+        for (const Item &it : o.items) steps.push_back(it.steps);
+        for (size_t r = 2; (r - 1) * slots < steps.size(); ++r) {
+          std::nth_element(steps.begin(), steps.begin() + (r - 1) * slots, steps.end(), std::greater<int64_t>());
+          o.time = std::max(o.time, (double)r * (double)steps[(r - 1) * slots] * (double)slots / capacity);
+        }
+      }
+      o.time *= (12 * R + 22) / 16.;
       return o;
     };
+    // By the model's time.  A threshold in shares of a slot's load sends whole batches wide
+    // where their items are about as many as the slots, and a launch of nothing but wide
+    // items is bound by instructions: then four tasks a wavefront take the fewest, and two
+    // pairs an item fewer than one (less skew, and more rows a lane).  Four letters, us, one
+    // pair an item / none wide / the choice: 9 000 pairs of 210..300 letters 501 / 295 / 297,
+    // 6 000 of 490..700 against 196..280 515 / 476 / 304 (two), 4 000 of 35..50 129 / 42 / 42.
+    // A tuned threshold stands, and about a tie stays with one.
+    auto best_of = [&](int R) {
+      Layout b = lay_out(R, kWideOne);
+      if (pct_asked < 0) return b;
+      for (const Form f : {kWideBoth, kNarrow}) {
+        if (f == kNarrow && pct_asked) continue;
+        Layout o = lay_out(R, f);
+        if (o.time < 0.96 * b.time) b = std::move(o);
+      }
+      return b;
+    };
     make_tasks(64);
-    Layout lay = lay_out(tile ? tile : 16);
+    Layout lay = best_of(tile ? tile : 16);
     if (!tile && alnk::sw16_lds_bytes(16, hs.alphabet) * 4 > (size_t)ctx->lds_per_cu) {
       // Profiles of 16 rows a lane leave SIMDs without a wavefront (19 letters and
       // more), ones of 8 rows take more instructions a cell: the shorter of the two, by
       // the model above.  20 letters, 16 / 8 rows, ms: 1 024 pairs of about 350 0.70 /
       // 0.78, 8 192 0.95 / 0.98, 16 384 1.53 / 1.21, 40 000 3.54 / 2.49; 30 000 of about
       // 120 0.39 / 0.33.  (Four letters, 20 000 reads of 150: 0.27 / 0.35, so always 16.)
-      Layout small8 = lay_out(8);
+      Layout small8 = best_of(8);
       if (small8.time < lay.time) lay = std::move(small8);
     }
     // More strips and a finer order may take more boundary rows than 16 rows a lane and an
@@ -651,7 +690,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     if (lay.bytes + 160ull * n > ALN_NOALLOC_WORKSPACE_BYTES) {
       std::vector<TaskDim> fine = td;
       make_tasks(16 * (tile ? tile : 16));
-      Layout plain = lay_out(tile ? tile : 16);
+      Layout plain = lay_out(tile ? tile : 16, kWideOne);
       uint64_t least = 0; // boundary rows without those of short wide tasks
       for (const Item &it : plain.items)
         for (int32_t k = it.first; k < it.end; ++k)
@@ -662,7 +701,9 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     }
     const int R = lay.R;
     pl->sw16_rows = R;
-    const int32_t HS = 16 * R, HW = 128 * R; // strip heights: 16-lane group, wide item
+    pl->sw16_both = lay.form == kWideBoth;
+    const int32_t HS = 16 * R, HB = 64 * R, HW = 128 * R; // strip heights: 16-lane group, wide
+                                                          // item of two pairs, of one
     std::vector<Item> &items = lay.items;
     // longest item first: workgroups are dispatched in index order
     std::vector<uint64_t> steps(items.size());
@@ -678,8 +719,8 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
     for (const int32_t at : order_desc(steps)) {
       const Item &it = items[(size_t)at];
       pl->sw16_items.push_back(
-          alnk::Sw16Item{(int32_t)pl->sw16_tasks.size(), it.wide >= 0 ? -1 : it.end - it.first});
-      pl->sw16_wide += it.wide >= 0;
+          alnk::Sw16Item{(int32_t)pl->sw16_tasks.size(), it.wide != -1 ? -1 : it.end - it.first});
+      pl->sw16_wide += it.wide != -1;
       for (int32_t k = it.first; k < it.end; ++k) {
         const TaskDim &d = td[k];
         alnk::Sw16Task t;
@@ -691,7 +732,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
         } else {
           t.pa = d.pa;
           t.pb = d.pb;
-          t.nstrips = nstr(d.mmax, HS);
+          t.nstrips = nstr(d.mmax, it.wide == kBoth ? HB : HS);
           t.nmax = d.nmax;
         }
         t.bnd_off = 0;
@@ -1464,6 +1505,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
         a16.ntasks = L.count;
         a16.items = reinterpret_cast<const alnk::Sw16Item *>(ws + plan->sw16_items_off);
         a16.nitems = (int32_t)plan->sw16_items.size();
+        a16.wide_both = plan->sw16_both;
         HIP_TRY(ctx, timed_launch(ctx, "sw16", st, [&] {
                   return alnk::launch_sw16(L.rows, a16, st);
                 }));
@@ -1474,6 +1516,7 @@ static aln_status run_plan(aln_ctx *ctx, aln_plan *plan, const aln_batch *b, voi
         a16.ntasks = 1;
         a16.items = nullptr;
         a16.nitems = 0;
+        a16.wide_both = 0;
         HIP_TRY(ctx, alnk::launch_sw16(plan->sw16_single_rows[k], a16, st));
       }
     }

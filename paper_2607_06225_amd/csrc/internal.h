@@ -194,11 +194,11 @@ struct ValidateArgs {
   int32_t n_reset;
 };
 
-// Two pairs aligned by one 16-lane group of the packed int16 kernel, or one pair by the
-// 64 lanes of a wide item.
+// Two pairs aligned by one 16-lane group of the packed int16 kernel, or one pair (two, in
+// plans of such items) by the 64 lanes of a wide item.
 struct Sw16Task {
   int32_t pa, pb;    // pair indices (pb = -1: none)
-  int32_t nstrips;   // strips of the taller pair (16*R or, in a wide item, 128*R rows)
+  int32_t nstrips;   // strips of the taller pair (16*R rows; in a wide item 128*R, of two 64*R)
   int32_t nmax;      // max(N_a, N_b)
   int64_t bnd_off;   // byte offset of the group's strip-boundary row in ws
 };
@@ -224,6 +224,7 @@ struct Sw16Args {
   int32_t ntasks;
   const Sw16Item *items;   // work items, one per workgroup; null: every task wide
   int32_t nitems;
+  int32_t wide_both;       // wide items hold two pairs
   const DevScoring *sc;
   int32_t sc_alphabet;     // host copy of the alphabet (LDS sizing)
   uint8_t *ws;

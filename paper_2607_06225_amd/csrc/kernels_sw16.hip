@@ -13,7 +13,8 @@
 // lanes, in strips of 128*R rows: the low halves hold the upper 64*R rows, the high
 // halves the lower ones, 64 columns behind, fed from lane 63's low halves.  The
 // planner gives the wide form to pairs whose strips would otherwise make
-// the launch wait on one wavefront.
+// the launch wait on one wavefront.  (BOTH: two pairs on all 64 lanes, as on 16, in strips of
+// 64*R rows: of longer serial time, but fewer instructions where the whole batch runs wide.)
 //
 // The last strip takes only as many rows a lane as its longest query needs (a
 // multiple of 4), so tasks are sorted by that.
@@ -118,15 +119,16 @@ __device__ __forceinline__ uint32_t grp_shl1z(uint32_t v) {
 }
 
 // One work item of the packed kernel: `count` tasks (two pairs each) on the
-// four 16-lane groups of the wavefront (G = 16), or one pair on all 64 lanes
-// (G = 64).  A wide item runs 128*R-row strips, so a long pair takes an
+// four 16-lane groups of the wavefront (G = 16), or one pair (TALL), or one task's two,
+// on all 64 lanes (G = 64).  TALL items run 128*R-row strips, so a long pair takes an
 // eighth of the strips, and of the serial time, of a 16-lane group.
-template <int R, int G>
+template <int R, int G, bool TALL>
 __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const int8_t *smat,
                                           uint2 *stage_all, int first, int count) {
   static_assert(G == 16 || G == 64, "group width");
-  constexpr int NG = 64 / G;       // groups per wavefront
-  constexpr bool TALL = G == 64;   // one pair, the strip's lower half in the high halves
+  static_assert(!TALL || G == 64, "one pair takes all lanes");
+  constexpr int NG = 64 / G;       // groups per wavefront; TALL: one pair, the strip's lower
+                                   // half in the high halves
   constexpr int FOLD = TALL ? 2 : 1;
   constexpr int HS = FOLD * G * R; // strip height
   const int lane = threadIdx.x;
@@ -462,7 +464,8 @@ __device__ __forceinline__ void sw16_item(const Sw16Args &a, int8_t *prof, const
 // One workgroup (one wavefront) per work item.  Items come from the plan's
 // table in the order the planner chose (longest first); without a table
 // every task is its own wide item (one pair per launch).
-template <int R>
+// BOTH: wide items of two pairs.
+template <int R, bool BOTH>
 __global__ __launch_bounds__(64) void sw16_kernel(Sw16Args a) {
   extern __shared__ __align__(16) uint8_t smem[];
   static_assert(R % 4 == 0, "R must be a multiple of 4");
@@ -487,8 +490,8 @@ __global__ __launch_bounds__(64) void sw16_kernel(Sw16Args a) {
   } else if (item >= a.ntasks) {
     return;
   }
-  if (it.count < 0) sw16_item<R, 64>(a, prof, smat, stage, it.first, 1);
-  else sw16_item<R, 16>(a, prof, smat, stage, it.first, it.count);
+  if (it.count < 0) sw16_item<R, 64, !BOTH>(a, prof, smat, stage, it.first, 1);
+  else sw16_item<R, 16, false>(a, prof, smat, stage, it.first, it.count);
 }
 
 hipError_t launch_sw16(int rows, const Sw16Args &a, hipStream_t s) {
@@ -505,10 +508,10 @@ hipError_t launch_sw16(int rows, const Sw16Args &a, hipStream_t s) {
     return hipGetLastError();
   };
   switch (rows) {
-  case 4: return go(sw16_kernel<4>);
-  case 8: return go(sw16_kernel<8>);
-  case 12: return go(sw16_kernel<12>);
-  case 16: return go(sw16_kernel<16>);
+  case 4: return a.wide_both ? go(sw16_kernel<4, true>) : go(sw16_kernel<4, false>);
+  case 8: return a.wide_both ? go(sw16_kernel<8, true>) : go(sw16_kernel<8, false>);
+  case 12: return a.wide_both ? go(sw16_kernel<12, true>) : go(sw16_kernel<12, false>);
+  case 16: return a.wide_both ? go(sw16_kernel<16, true>) : go(sw16_kernel<16, false>);
   default: return hipErrorInvalidValue;
   }
 }

@@ -88,7 +88,8 @@ struct aln_plan {
   std::vector<alnk::Sw16Task> sw16_single;   // one pair per task (per-pair runs)
   std::vector<int> sw16_single_rows;         // tile of each single task
   std::vector<alnk::Sw16Item> sw16_items;    // one wavefront each, longest first
-  int32_t sw16_wide = 0;                     // items running one task on 64 lanes
+  int32_t sw16_wide = 0;                     // items running one pair (or, sw16_both, the two
+  bool sw16_both = false;                    // pairs of a task) on 64 lanes
   int sw16_rows = 16;
   uint64_t sw16_off = 0, sw16_items_off = 0, sw16_single_off = 0, rerun_cnt_off = 0, rerun_off = 0;
   alnrt::LaunchDesc rerun{};
