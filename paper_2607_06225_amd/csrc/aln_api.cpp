@@ -1074,8 +1074,13 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
   // reads of 150 bp against 150..320 bp windows, LOCAL with paths, 0.30 ms
   // against 0.88.  Up to 160 rows a pair takes no longer there than on its own
   // wavefront, of 161..256 rows (16 a lane) twice as long, so those only past
-  // two pairs a SIMD.  One launch, its rows a lane by the longest query, until
-  // eight pairs a SIMD; from there on by each pair's, and beside longer pairs.
+  // two pairs a SIMD (LOCAL with paths against longer references three: 2 100 pairs of
+  // 30..250 rows against 60..500 415 us on strips, 523 rolling).  One launch,
+  // its rows a lane by the longest query, until eight pairs a SIMD; from there on by each
+  // pair's, and beside longer pairs, but for rows a lane that few pairs take: beside the
+  // strips that is one more launch of a pair's time (9 000 pairs, half of 20..60 rows, half
+  // of 250..600, some hundred of them up to 256, LOCAL with paths: 1.99 ms all on strips, 2.15
+  // with such a launch, 1.96 without).
   if (srows == 0) {
     int64_t n_full = 0;
     int32_t fullM = 0, fullN = 0;
@@ -1095,6 +1100,21 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
         alnk::band_lds_bytes(alnk::kStripPipeWaves2, (fullN + 10 + 15) / 16 * 16,
                              small ? 0 : (int)align_up((uint64_t)hs.alphabet * 64 * 4, 16)) <= 160 * 1024;
     const bool split = n_full > 8 * simds;
+    const int64_t from16 = (p.mode == ALN_LOCAL && p.want_cigar && 10LL * fullN > 13LL * fullM ? 3 : 2) * simds;
+    auto roll_rows = [](int32_t top) { return top <= 128 ? 8 : (top <= 160 ? 10 : 16); };
+    auto rolls = [&](const Item &it) {
+      const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
+      return it.kind == K_STRIP && small && n_full >= kRollPairs && N < 65536 && M <= 256 && M >= 1 && N >= 1 &&
+             (split || fullM <= 160 || (fullM <= 256 && n_full > from16));
+    };
+    int64_t rolling = 0, by_rows[17] = {};
+    if (split && !few)
+      for (const Item &it : items)
+        if (whole(it) && rolls(it)) {
+          ++rolling;
+          ++by_rows[roll_rows(pl->qlen[it.pair])];
+        }
+    const bool beside = split && rolling < n_full;
     for (Item &it : items) {
       const int32_t M = pl->qlen[it.pair], N = pl->rlen[it.pair];
       if (!whole(it) || M < 1 || N < 1) continue;
@@ -1114,13 +1134,13 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
           it.waves = alnk::kStripPipeWaves;
         }
         it.ring = (int)std::max<int64_t>(64, ((int64_t)N + 10 + 15) / 16 * 16);
-      } else if (it.kind == K_STRIP && small && n_full >= kRollPairs && N < 65536 && M <= 256 &&
-                 (split || fullM <= 160 || (fullM <= 256 && n_full > 2 * simds))) {
-        const int32_t top = split ? M : fullM;
+      } else if (rolls(it)) {
+        const int rows = roll_rows(split ? M : fullM);
+        if (beside && by_rows[rows] * 2 < simds) continue;
         move_away();
         it.kind = K_ROLL;
         it.full = true;
-        it.rows = top <= 128 ? 8 : (top <= 160 ? 10 : 16);
+        it.rows = rows;
         it.waves = 16;
       }
     }
