@@ -735,6 +735,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
           t.nstrips = nstr(d.mmax, it.wide == kBoth ? HB : HS);
           t.nmax = d.nmax;
         }
+        if (t.nmax == 0) t.nstrips = 0; // no column (nor one that a strip could leave to the next)
         t.bnd_off = 0;
         bnd_rel.push_back(t.nstrips > 1 ? bnd_bytes : ~0ULL);
         if (t.nstrips > 1) bnd_bytes += align_up((uint64_t)(t.nmax + 1) * (it.wide >= 0 ? 4 : 8), 16);
@@ -748,7 +749,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
           alnk::Sw16Task u;
           u.pa = pp;
           u.pb = -1;
-          u.nstrips = nstr(pl->qlen[pp], HW);
+          u.nstrips = pl->rlen[pp] > 0 ? nstr(pl->qlen[pp], HW) : 0;
           u.nmax = pl->rlen[pp];
           u.bnd_off = (int64_t)(pl->sw16_tasks.size() - 1); // task index, resolved below
           pl->sw16_single.push_back(u);
