@@ -339,6 +339,11 @@ inline size_t fold_tile_lds_bytes(int max_n, int waves) {
   return (size_t)(rows * (rows + 1) / 2 + rows + waves) * 256 + 16 * rows + 32;
 }
 
+// A kernel's verdict on a pair; one with a bad symbol stays that.
+__device__ inline void set_status(aln_result *res, int32_t status) {
+  if (res->status == ALN_R_OK) res->status = status;
+}
+
 // Launchers (defined in the kernel translation units).
 hipError_t launch_validate(const ValidateArgs &a, hipStream_t s);
 hipError_t launch_strip(int rows, int mode, bool tb, bool small_alphabet,

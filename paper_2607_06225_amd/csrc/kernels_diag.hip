@@ -484,12 +484,12 @@ __device__ void diag_task(const DiagArgs &a, int task, int wave, int lane, uint8
         t.rows = a.widen_rows;
         a.widen[slot] = t;
       } else {
-        res->status = ALN_R_TOO_WIDE; // region wider than the widest window
+        set_status(res, ALN_R_TOO_WIDE); // region wider than the widest window
       }
     } else if (MODE == ALN_GLOBAL) {
       if (gh <= NEG32 / 2) {
         res->score = INT32_MIN;
-        res->status = ALN_R_UNREACHABLE;
+        set_status(res, ALN_R_UNREACHABLE);
       } else {
         res->score = gh;
       }
@@ -766,7 +766,7 @@ __device__ void xdrop_group(const DiagArgs &a, int task4, int ntasks, int lane, 
         t.rows = a.widen_rows;
         a.widen[slot] = t;
       } else {
-        res->status = ALN_R_TOO_WIDE;
+        set_status(res, ALN_R_TOO_WIDE);
       }
     } else {
       res->score = best;

@@ -416,7 +416,7 @@ __global__ __launch_bounds__(64) void roll_kernel(StripArgs a) {
     if (!run) res->score = (M + N == 0) ? 0 : go + (M + N) * ge;
     else if (gh <= NEG32 / 2) {
       res->score = INT32_MIN;
-      res->status = ALN_R_UNREACHABLE;
+      set_status(res, ALN_R_UNREACHABLE);
     } else {
       res->score = gh;
     }

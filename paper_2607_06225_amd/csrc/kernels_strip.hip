@@ -855,7 +855,7 @@ __device__ void band_task(const StripArgs &a, int task, int wave, int lane, uint
   if (MODE == ALN_GLOBAL) {
     if (gh <= NEG32 / 2) {
       res->score = INT32_MIN;
-      res->status = ALN_R_UNREACHABLE;
+      set_status(res, ALN_R_UNREACHABLE);
     } else {
       res->score = gh;
     }
