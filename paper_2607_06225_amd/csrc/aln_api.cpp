@@ -927,7 +927,7 @@ aln_status alnrt::plan_build(aln_ctx *ctx, int32_t scoring_id, const aln_params 
   // that kernel's rotating lane-0 feeds and eight-step code stores take
   // about 18% less time on 1 kbp pairs.  Its LDS ring holds a strip's
   // columns and 10 more, so N <= 2038.
-  pl->strip_band_w = p.prune == ALN_BAND ? p.band_w : (1 << 28);
+  pl->strip_band_w = p.prune == ALN_BAND ? std::min(p.band_w, 1 << 28) : (1 << 28); // (columns are added to it)
   if (srows == 0 || srows == 2 || srows == 4) {
     int64_t n_full = 0;
     for (const Item &it : items) n_full += it.kind == K_STRIP;
