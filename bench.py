@@ -14,12 +14,13 @@ one, X-drop seed extension: 200,000 seeds x 2 sides, int32, score + end
 cell + cells visited, every side checked against the oracle.  The other
 workloads (protein Smith-Waterman, global DNA with CIGAR, banded long reads
 with CIGAR, Z-drop, X-drop with CIGAR, the search schedule) are measured the
-same way under "configs", and the serving mix of four of them (Poisson
-arrivals through the request server) under "serving" with p50/p99 latency.
-The roofline of each dominant kernel is priced by the issue rates that
-aln_valu_probe measures per instruction class, at the spec clock and at the
-clock measured under load; the last key, "summary", repeats each workload's
-rate, roofline fraction and check in a few fields.
+same way, and so is the serving mix of four of them (Poisson arrivals through
+the request server) with p50/p99 latency.  The roofline of each dominant kernel
+is priced by the issue rates that aln_valu_probe measures per instruction class,
+at the spec clock and at the clock measured under load.  The line's "summary"
+holds each workload's rate, roofline fraction and check in a few fields, and of
+the edit-distance table [length, divergence, search ms, full-matrix ms, agree];
+each whole record goes to stderr, and all of them to the file that --record names.
 
 For each: per-kernel times from HIP events recorded on the launch stream
 during the timed steps (roofline of the dominant kernel), the same kernels
@@ -810,6 +811,8 @@ def main():
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="MIB",
                     help="only copy MIB MiB device-to-device 5 times (calibrates HBM "
                          "byte counters against a transfer of known size)")
+    ap.add_argument("--record", metavar="FILE",
+                    help="also write every workload's whole record to FILE as JSON")
     ap.add_argument("--serving-only", action="store_true",
                     help="measure only the serving mix (no headline line)")
     ap.add_argument("--serving-check", type=int, default=600,
@@ -900,18 +903,13 @@ def main():
         "step_ms_trimmed_mean": head["step_ms_trimmed_mean"],
         "step_ms_median": head["step_ms_median"],
         "plan_ms": head["plan_ms"],
-        "autotune": head["autotune"],
-        "machine": machine,
-        "configs": configs,
-        "edit_table": edit_table,
-        "serving": serving_out,
     }
     for k in ("int32_reruns", "statuses", "widened_pairs", "cigar_cap_pairs", "too_wide_pairs",
               "equivalent_gcups", "alignments_per_s", "mean_edit_distance", "mean_penalty"):
         if k in head:
             out[k] = head[k]
-    # last key: one short record per workload, so that a truncated copy of the
-    # line still holds every workload's rate, roofline fraction and check
+    # one short record per workload; the whole ones go to stderr as they are measured, and
+    # to --record, so that the line stays short enough to be kept whole
     out["summary"] = {w: summarize(r) for w, r in [(args.workload, head)] + list(configs.items())}
     if serving_out:
         out["summary"]["serving"] = {
@@ -920,6 +918,14 @@ def main():
             for lv in serving_out["levels"]}
         out["summary"]["serving"]["requests"] = serving_out["requests"]
         out["summary"]["serving"]["bit_exact"] = serving_out["bit_exact_check"]["mismatches"] == 0
+    if edit_table:
+        out["summary"]["edit_table"] = [
+            [r["length"], r["divergence"], r["search_ms"], r["full_ms"],
+             r["scores_agree"] and r["oracle_mismatches"] == 0] for r in edit_table["rows"]]
+    if args.record:
+        with open(args.record, "w") as f:
+            json.dump(dict(out, autotune=head["autotune"], machine=machine, configs=configs,
+                           edit_table=edit_table, serving=serving_out), f)
     print(json.dumps(out), flush=True)
     return 0
 
