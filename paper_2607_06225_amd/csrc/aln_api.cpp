@@ -245,11 +245,15 @@ aln_status aln_set_scoring(aln_ctx *ctx, const aln_scoring *sc, int32_t *scoring
 
 } // extern "C"
 
-// Batches smaller than this keep the antidiagonal kernel for bands below 256
-// diagonals (and one-strip pairs their own launch): the documented choice for a
-// handful of pairs.  From it on, strips take about a third of its time a row.
+// Pairs from which bands below 256 diagonals leave the antidiagonal kernel (and one-strip
+// pairs share a launch with longer ones).  Strips are shorter from one pair on (with paths,
+// w = 64, us, antidiagonals / strips: one pair of 300 rows 454 / 140, of 1 000 1 416 / 324, of
+// 20 000 28 000 / 5 740; three 475 / 143, 1 490 / 334, 29 300 / 5 770): up to three pairs keep
+// the kernel that plans of so few have always named.
 constexpr int32_t kStripBandPairs = 4;
-// Pairs from which rolling blocks are used.
+// Pairs from which rolling blocks are used.  (Four to fifteen run on strips: blocks of two
+// rows would be shorter there too, 15 pairs of 5 000 rows, w = 64, 1.12 against 1.52 ms, blocks
+// of four, for wider bands, longer, w = 100 1.65 against 1.53.)
 constexpr int32_t kRollPairs = 16;
 
 // Rolling blocks for a band: rows a block and lanes a pair, 0 where none fits.
